@@ -27,14 +27,26 @@ hipError_t mlp_gemm_gelu_back(const uint16_t* X, int64_t ldx, int M, const uint1
                               hipStream_t s);
 // X0[r] = bf16(Z[r] sqrt(d) / ||Z[r]||); Zout (optional) receives X0 widened to float32
 hipError_t mlp_embed_norm(const float* Z, int d, int p, uint16_t* X0, float* Zout, int64_t ldz_out, hipStream_t s);
-// weighted BCE with logits: S (logits, in place -> dl/ds / rows), D16 its bfloat16 copy, loss (device double)
-hipError_t mlp_bce_grad(float* S, int64_t lds, uint16_t* D16, int64_t ld16, int m, int mpad, int rows,
-                        const int* supp, int64_t ld_supp, const int* supp_len, float pos_w, float* rowloss,
-                        double* loss, hipStream_t s);
-hipError_t mlp_colsum(const float* in, int64_t ld, int rows, int cols, float* out, hipStream_t s);
-// out[c][r] = in[r][c]; zero for rows <= r < ldo (ldo % 64 == 0)
-hipError_t mlp_transpose(const uint16_t* in, int64_t ldi, int rows, int cols, uint16_t* out, int64_t ldo,
-                         hipStream_t s);
+// Weighted BCE with logits S [rows][lds >= mpad], mpad % 64 == 0: D16 = bf16(dl/ds / rows) (zero past m), DT its
+// transpose [m][ldt] (zero for rows up to the next multiple of 64), colpart [ceil(rows / 64)][ldc] and rowpart
+// [mpad / 64][ldr] the 64 x 64 tiles' sums of dl/ds over rows and of the loss over columns (mlp_partial_sums).
+hipError_t mlp_bce_tiles(const float* S, int64_t lds, uint16_t* D16, int64_t ld16, uint16_t* DT, int64_t ldt, int m,
+                         int mpad, int rows, const int* supp, int64_t ld_supp, const int* supp_len, float pos_w,
+                         double* colpart, int64_t ldc, double* rowpart, int64_t ldr, hipStream_t s);
+// DT[c][r] = bf16(in[r][c]) (zero rows as above), colpart the tiles' column sums; cols % 64 == 0
+hipError_t mlp_transpose_colsum(const float* in, int64_t ld, int rows, int cols, uint16_t* DT, int64_t ldt,
+                                double* colpart, int64_t ldc, hipStream_t s);
+// The bias gradients out[q][c < cols[q]] and the mean loss from the tiles' partial sums.
+struct PartialSums {
+    const double* part[3]; int64_t ldc[3]; int cols[3]; float* out[3];
+    const double* rowpart; int64_t ldr; int tile_cols; int rows; float* rowloss;
+    int start[4]; int tile_rows;   // set by the launcher
+};
+hipError_t mlp_partial_sums(PartialSums a, double* loss, hipStream_t s);
+// out[c][r] = in[r][c]; zero for rows <= r < ldo (ldo % 64 == 0, cols % 8 == 0); up to three in one launch
+struct TransposeJob { const uint16_t* in; int64_t ldi; int rows, cols; uint16_t* out; int64_t ldo; };
+struct TransposeJobs { TransposeJob job[3]; int start[3]; };
+hipError_t mlp_transposes(const TransposeJob* jobs, int count, hipStream_t s);
 hipError_t mlp_adam(float* P, float* m1, float* m2, const float* g, uint16_t* P16, int64_t count, float lr,
                     float beta1, float beta2, float eps, float bc1, float bc2, hipStream_t s);
 hipError_t mlp_params_bf16(const float* P, uint16_t* P16, int64_t count, hipStream_t s);

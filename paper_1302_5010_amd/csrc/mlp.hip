@@ -21,6 +21,7 @@
 #include "bmpl_internal.h"
 #include "gemm_tile.h"
 #include "mlp.h"
+#include "wave_ops.h"
 
 namespace bmpl {
 namespace {
@@ -221,48 +222,179 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(const float* __restrict
     }
 }
 
-// Weighted binary cross-entropy with logits, one workgroup per signal.  In place:
-// S[r][j] (logit) becomes dl/ds divided by the batch size; D16 gets its bfloat16 copy with zeros
-// in columns m..mpad-1; rowloss[r] = sum_j l(s_j, y_j).  Targets y_j = 1 for the atoms listed in
-// supp[r][0..len[r]).
-constexpr int BCE_MAX_WORDS = 4096;    // m <= 131072
-__global__ __launch_bounds__(256) void bce_grad_kernel(float* __restrict__ S, int64_t lds,
-                                                       uint16_t* __restrict__ D16, int64_t ld16, int m, int mpad,
+// The passes of the backward that read whole activation matrices work on 64 x 64 tiles (LT), a workgroup of
+// 256 threads each: a matrix is read once, in float4 / 16-byte rows, and its bfloat16 transpose leaves through
+// LDS in 128-byte rows, while the tile's sums over its rows or columns go to partial arrays that one small
+// kernel adds up at the end of the step.  One workgroup per 256 columns that walks every row by itself (the
+// plain column sum) leaves 8 to 79 of the 256 CUs with work: 246 us for 1024 x 2048 as for 1024 x 20000.  As
+// tiles: 5.7 us for 1024 x 2048 with its transpose, 88 us for the loss of 1024 x 20000 (bound by its expf, log1pf
+// and division; 377 us as loss, column sum and transpose before), and 12 us for the partial sums; a training step
+// at 1024 signals, d = h = 2048, m = 20000: 1.93 -> 1.11 ms.
+constexpr int LT = 64;
+constexpr int LTS = LT + 8;   // LDS row of bfloat16 values: 16-byte aligned, rows 4 banks apart
+
+// Write the transposed tile t[row][col] (bfloat16): out[c0 + col][r0 + row], col rows below `cols`, 16 bytes per
+// lane (ldo % 64 == 0 and r0 % 64 == 0, so a tile's 64 entries always lie inside a row of out).
+__device__ __forceinline__ void store_tile_transposed(const uint16_t (&t)[LT][LTS], uint16_t* __restrict__ out,
+                                                      int64_t ldo, int r0, int c0, int cols)
+{
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int e = threadIdx.x + 256 * q, col = e >> 3, rr = 8 * (e & 7);
+        if (c0 + col >= cols) continue;
+        uint32_t v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = (uint32_t)t[rr + 2 * i][col] | ((uint32_t)t[rr + 2 * i + 1][col] << 16);
+        *reinterpret_cast<uint4*>(out + (int64_t)(c0 + col) * ldo + r0 + rr) = make_uint4(v[0], v[1], v[2], v[3]);
+    }
+}
+
+// Column sums of a tile held by its threads (thread: columns 4 (tid % 16) .. + 3, rows tid / 16 + 16 q, already
+// added over q into cs) into part[col] (float64), through s_col.
+__device__ __forceinline__ void tile_column_sums(const double (&cs)[4], double (&s_col)[16][LT + 1],
+                                                 double* __restrict__ part, int c0, int cols)
+{
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s_col[tid >> 4][4 * (tid & 15) + i] = cs[i];
+    __syncthreads();
+    if (tid < LT && c0 + tid < cols) {
+        double v = 0.0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v += s_col[q][tid];
+        part[c0 + tid] = v;
+    }
+}
+
+// Weighted binary cross-entropy with logits on one tile of S (logits, [rows][lds], lds = mpad): with g = dl/ds
+// divided by the batch size, D16[r][j] = bf16(g) (zero in columns m..mpad-1), DT[j][r] = bf16(g) (zero for
+// rows..64 ceil(rows / 64) - 1), colpart[tile row][j] = the tile's sum of g over its rows, rowpart[tile col][r] =
+// its sum of l(s_j, y_j).  Targets y_j = 1 for the atoms listed in supp[r][0..len[r]).
+__global__ __launch_bounds__(256) void bce_tile_kernel(const float* __restrict__ S, int64_t lds,
+                                                       uint16_t* __restrict__ D16, int64_t ld16,
+                                                       uint16_t* __restrict__ DT, int64_t ldt, int m, int rows,
                                                        const int* __restrict__ supp, int64_t ld_supp,
                                                        const int* __restrict__ supp_len, float pos_w, float inv_batch,
-                                                       float* __restrict__ rowloss)
+                                                       double* __restrict__ colpart, int64_t ldc,
+                                                       double* __restrict__ rowpart, int64_t ldr)
 {
-    __shared__ uint32_t bits[BCE_MAX_WORDS];
-    __shared__ double red[4];
-    const int r = blockIdx.x;
-    const int words = (m + 31) >> 5;
-    for (int w = threadIdx.x; w < words; w += 256) bits[w] = 0u;
+    __shared__ uint32_t bits[LT][2];
+    __shared__ __attribute__((aligned(16))) uint16_t t[LT][LTS];
+    __shared__ double s_col[16][LT + 1];
+    const int c0 = blockIdx.x * LT, r0 = blockIdx.y * LT;
+    const int tid = threadIdx.x, tc = 4 * (tid & 15), tr = tid >> 4;
+    float4 x[4];   // four rows of four logits (mpad is a multiple of 64: every column is readable)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int r = r0 + tr + 16 * q;
+        x[q] = *reinterpret_cast<const float4*>(S + (int64_t)(r < rows ? r : rows - 1) * lds + c0 + tc);
+    }
+    if (tid < 2 * LT) bits[tid >> 1][tid & 1] = 0u;
     __syncthreads();
-    const int len = min(supp_len[r], (int)ld_supp);
-    for (int t = threadIdx.x; t < len; t += 256) {
-        const int j = supp[(int64_t)r * ld_supp + t];
-        if (j >= 0 && j < m) atomicOr(&bits[j >> 5], 1u << (j & 31));
+    for (int q = tid >> 2; q < LT; q += 64) {   // four lanes walk a row's support list
+        const int r = r0 + q;
+        if (r >= rows) continue;
+        const int len = min(supp_len[r], (int)ld_supp);
+        for (int e = tid & 3; e < len; e += 4) {
+            const int j = supp[(int64_t)r * ld_supp + e] - c0;
+            if (j >= 0 && j < LT && c0 + j < m) atomicOr(&bits[q][j >> 5], 1u << (j & 31));
+        }
     }
     __syncthreads();
-    double part = 0.0;
-    float* s = S + (int64_t)r * lds;
-    for (int j = threadIdx.x; j < mpad; j += 256) {
-        if (j >= m) { D16[(int64_t)r * ld16 + j] = 0; continue; }
-        const float x = s[j];
-        const bool y = (bits[j >> 5] >> (j & 31)) & 1u;
-        const float e = expf(-fabsf(x));
-        const float sp_pos = fmaxf(x, 0.f) + log1pf(e);     // log(1 + e^x)
-        const float sp_neg = fmaxf(-x, 0.f) + log1pf(e);    // log(1 + e^-x)
-        part += y ? (double)pos_w * sp_neg : (double)sp_pos;
-        const float sig = x >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
-        const float g = (y ? sig * pos_w - pos_w : sig) * inv_batch;
-        s[j] = g;
-        D16[(int64_t)r * ld16 + j] = bf16_round(g);
+    double cs[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int row = tr + 16 * q, r = r0 + row;
+        const float xv[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+        const uint32_t yb = bits[row][tc >> 5] >> (tc & 31);
+        uint16_t hv[4];
+        double part = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool in = r < rows && c0 + tc + i < m;
+            const float v = xv[i];
+            const bool y = (yb >> i) & 1u;
+            const float e = expf(-fabsf(v));
+            const float l1 = log1pf(e);
+            const float sp = fmaxf(y ? -v : v, 0.f) + l1;           // log(1 + e^-v) for a target, else log(1 + e^v)
+            const float sig = (v >= 0.f ? 1.f : e) / (1.f + e);
+            const float g = (y ? sig * pos_w - pos_w : sig) * inv_batch;
+            part += in ? (y ? (double)pos_w * sp : (double)sp) : 0.0;
+            cs[i] += in ? (double)g : 0.0;
+            hv[i] = in ? bf16_round(g) : (uint16_t)0;
+            t[row][tc + i] = hv[i];
+        }
+        part = row16_sum(part);                                      // the row's 16 threads
+        if (r < rows) {
+            *reinterpret_cast<uint2*>(D16 + (int64_t)r * ld16 + c0 + tc) =
+                make_uint2((uint32_t)hv[0] | ((uint32_t)hv[1] << 16), (uint32_t)hv[2] | ((uint32_t)hv[3] << 16));
+            if ((tid & 15) == 0) rowpart[(int64_t)blockIdx.x * ldr + r] = part;
+        }
     }
-    for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = part;
+    tile_column_sums(cs, s_col, colpart + (int64_t)blockIdx.y * ldc, c0, m);   // its barrier also publishes t
+    store_tile_transposed(t, DT, ldt, r0, c0, m);
+}
+
+// One tile of a float32 matrix: DT[c][r] = bf16(in[r][c]) (zero for rows past `rows`, up to a multiple of 64) and
+// colpart[tile row][c] = the tile's column sum.  cols is a multiple of 64.
+__global__ __launch_bounds__(256) void transpose_colsum_kernel(const float* __restrict__ in, int64_t ld, int rows,
+                                                               int cols, uint16_t* __restrict__ DT, int64_t ldt,
+                                                               double* __restrict__ colpart, int64_t ldc)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t t[LT][LTS];
+    __shared__ double s_col[16][LT + 1];
+    const int c0 = blockIdx.x * LT, r0 = blockIdx.y * LT;
+    const int tid = threadIdx.x, tc = 4 * (tid & 15), tr = tid >> 4;
+    float4 x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int r = r0 + tr + 16 * q;
+        x[q] = *reinterpret_cast<const float4*>(in + (int64_t)(r < rows ? r : rows - 1) * ld + c0 + tc);
+    }
+    double cs[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int row = tr + 16 * q;
+        const bool in_rows = r0 + row < rows;
+        const float xv[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            cs[i] += in_rows ? (double)xv[i] : 0.0;
+            t[row][tc + i] = in_rows ? bf16_round(xv[i]) : (uint16_t)0;
+        }
+    }
+    tile_column_sums(cs, s_col, colpart + (int64_t)blockIdx.y * ldc, c0, cols);
+    store_tile_transposed(t, DT, ldt, r0, c0, cols);
+}
+
+// The step's sums from the tiles' partial ones: out[c] = sum over the tile rows of colpart[.][c] for up to three
+// matrices (the bias gradients) and rowloss[r] = sum over the tile columns of rowpart[.][r] (four threads per
+// row).  Blocks [start[q], start[q + 1]) take job q, the last job the rows.
+__global__ __launch_bounds__(256) void partial_sums_kernel(PartialSums a)
+{
+    __shared__ double s_p[4][LT];
+    const int tid = threadIdx.x;
+    int q = 0;
+    while (q < 3 && (int)blockIdx.x >= a.start[q + 1]) ++q;
+    const int b = blockIdx.x - a.start[q];
+    if (q < 3) {
+        const int c = b * 256 + tid;
+        if (c >= a.cols[q]) return;
+        double s = 0.0;
+#pragma unroll 8
+        for (int r = 0; r < a.tile_rows; ++r) s += a.part[q][(int64_t)r * a.ldc[q] + c];
+        a.out[q][c] = (float)s;
+        return;
+    }
+    const int r = b * LT + (tid & (LT - 1)), g = tid >> 6;
+    double s = 0.0;
+    if (r < a.rows) {
+#pragma unroll 8
+        for (int c = g; c < a.tile_cols; c += 4) s += a.rowpart[(int64_t)c * a.ldr + r];
+    }
+    s_p[g][tid & (LT - 1)] = s;
     __syncthreads();
-    if (threadIdx.x == 0) rowloss[r] = (float)(red[0] + red[1] + red[2] + red[3]);
+    if (g == 0 && r < a.rows) a.rowloss[r] = (float)(((s_p[0][tid] + s_p[1][tid]) + s_p[2][tid]) + s_p[3][tid]);
 }
 
 // loss = sum_r rowloss[r] / rows (one workgroup).
@@ -277,33 +409,29 @@ __global__ __launch_bounds__(256) void loss_sum_kernel(const float* __restrict__
     if (threadIdx.x == 0) *loss = (red[0] + red[1] + red[2] + red[3]) / rows;
 }
 
-// out[c] = sum_{r < rows} in[r][c]  (bias gradients).
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ in, int64_t ld, int rows, int cols,
-                                                     float* __restrict__ out)
+// out[c][r] = in[r][c] for c < cols, r < rows; out[c][r] = 0 for rows <= r < ldo, for up to three matrices in one
+// launch (ldo % 64 == 0, ldi % 8 == 0; blocks [start[q], start[q + 1]) take matrix q, tile columns fastest).  A
+// thread moves 16 bytes each way: 90 -> 43 us for 20000 x 2048 and 2048 x 2048 (two bytes per access before).
+__global__ __launch_bounds__(256) void transpose_bf16_kernel(TransposeJobs a)
 {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= cols) return;
-    double s = 0.0;
-    for (int r = 0; r < rows; ++r) s += in[(int64_t)r * ld + c];
-    out[c] = (float)s;
-}
-
-// out[c][r] = in[r][c] for c < cols, r < rows; out[c][r] = 0 for rows <= r < ldo (ldo % 64 == 0).
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* __restrict__ in, int64_t ldi, int rows,
-                                                             int cols, uint16_t* __restrict__ out, int64_t ldo)
-{
-    __shared__ uint16_t t[64][66];
-    const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int q = ty; q < 64; q += 4) {
-        const int r = r0 + q, c = c0 + tx;
-        t[q][tx] = (r < rows && c < cols) ? in[(int64_t)r * ldi + c] : (uint16_t)0;
+    __shared__ __attribute__((aligned(16))) uint16_t t[LT][LTS];
+    int q = 0;
+    while (q < 2 && (int)blockIdx.x >= a.start[q + 1]) ++q;
+    const TransposeJob& J = a.job[q];
+    const int b = blockIdx.x - a.start[q];
+    const int tiles_c = (J.cols + LT - 1) / LT;
+    const int r0 = b / tiles_c * LT, c0 = b % tiles_c * LT;
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int e = tid + 256 * h, row = e >> 3, cc = 8 * (e & 7);
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (r0 + row < J.rows && c0 + cc < J.cols)   // cols % 8 == 0
+            v = *reinterpret_cast<const uint4*>(J.in + (int64_t)(r0 + row) * J.ldi + c0 + cc);
+        *reinterpret_cast<uint4*>(&t[row][cc]) = v;
     }
     __syncthreads();
-    for (int q = ty; q < 64; q += 4) {
-        const int c = c0 + q, r = r0 + tx;
-        if (c < cols && r < ldo) out[(int64_t)c * ldo + r] = t[tx][q];
-    }
+    store_tile_transposed(t, J.out, J.ldo, r0, c0, J.cols);
 }
 
 // Adam with bias correction (bc1 = 1 - beta1^t, bc2 = 1 - beta2^t); refreshes the bfloat16 copy.
@@ -587,30 +715,56 @@ hipError_t mlp_embed_norm(const float* Z, int d, int p, uint16_t* X0, float* Zou
     return hipGetLastError();
 }
 
-hipError_t mlp_bce_grad(float* S, int64_t lds, uint16_t* D16, int64_t ld16, int m, int mpad, int rows,
-                        const int* supp, int64_t ld_supp, const int* supp_len, float pos_w, float* rowloss,
-                        double* loss, hipStream_t s)
+hipError_t mlp_bce_tiles(const float* S, int64_t lds, uint16_t* D16, int64_t ld16, uint16_t* DT, int64_t ldt, int m,
+                         int mpad, int rows, const int* supp, int64_t ld_supp, const int* supp_len, float pos_w,
+                         double* colpart, int64_t ldc, double* rowpart, int64_t ldr, hipStream_t s)
 {
     if (rows <= 0) return hipSuccess;
-    if ((m + 31) / 32 > BCE_MAX_WORDS) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(bce_grad_kernel, dim3(rows), dim3(256), 0, s, S, lds, D16, ld16, m, mpad, supp, ld_supp,
-                       supp_len, pos_w, 1.0f / rows, rowloss);
-    hipLaunchKernelGGL(loss_sum_kernel, dim3(1), dim3(256), 0, s, rowloss, rows, loss);
+    if (mpad % LT || lds < mpad || ld16 < mpad || lds % 4 || ld16 % 4 || ldt % LT || ldt < (rows + LT - 1) / LT * LT)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(bce_tile_kernel, dim3(mpad / LT, (rows + LT - 1) / LT), dim3(256), 0, s, S, lds, D16, ld16, DT,
+                       ldt, m, rows, supp, ld_supp, supp_len, pos_w, 1.0f / rows, colpart, ldc, rowpart, ldr);
     return hipGetLastError();
 }
 
-hipError_t mlp_colsum(const float* in, int64_t ld, int rows, int cols, float* out, hipStream_t s)
+hipError_t mlp_transpose_colsum(const float* in, int64_t ld, int rows, int cols, uint16_t* DT, int64_t ldt,
+                                double* colpart, int64_t ldc, hipStream_t s)
 {
-    hipLaunchKernelGGL(colsum_kernel, dim3((cols + 255) / 256), dim3(256), 0, s, in, ld, rows, cols, out);
+    if (rows <= 0) return hipSuccess;
+    if (cols % LT || ld % 4 || ldt % LT || ldt < (rows + LT - 1) / LT * LT) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(transpose_colsum_kernel, dim3(cols / LT, (rows + LT - 1) / LT), dim3(256), 0, s, in, ld, rows,
+                       cols, DT, ldt, colpart, ldc);
     return hipGetLastError();
 }
 
-hipError_t mlp_transpose(const uint16_t* in, int64_t ldi, int rows, int cols, uint16_t* out, int64_t ldo,
-                         hipStream_t s)
+hipError_t mlp_partial_sums(PartialSums a, double* loss, hipStream_t s)
 {
-    if (ldo % 64 || ldo < rows) return hipErrorInvalidValue;
-    dim3 grid((unsigned)(ldo / 64), (cols + 63) / 64);
-    hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, s, in, ldi, rows, cols, out, ldo);
+    if (a.rows <= 0) return hipSuccess;
+    a.start[0] = 0;
+    for (int q = 0; q < 3; ++q) a.start[q + 1] = a.start[q] + (a.cols[q] + 255) / 256;
+    a.tile_rows = (a.rows + LT - 1) / LT;
+    const int blocks = a.start[3] + a.tile_rows;
+    hipLaunchKernelGGL(partial_sums_kernel, dim3(blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(loss_sum_kernel, dim3(1), dim3(256), 0, s, a.rowloss, a.rows, loss);
+    return hipGetLastError();
+}
+
+hipError_t mlp_transposes(const TransposeJob* jobs, int count, hipStream_t s)
+{
+    if (count < 1 || count > 3) return hipErrorInvalidValue;
+    TransposeJobs a{};
+    int64_t at = 0;
+    for (int q = 0; q < 3; ++q) {
+        a.start[q] = (int)at;
+        if (q >= count) continue;
+        const TransposeJob& J = jobs[q];
+        if (J.ldo % LT || J.ldo < J.rows || J.cols % 8 || J.ldi % 8) return hipErrorInvalidValue;
+        a.job[q] = J;
+        at += (J.ldo / LT) * ((J.cols + LT - 1) / LT);   // every tile row of out, the zero rows included
+        if (at > 0x7fffffff) return hipErrorInvalidValue;
+    }
+    for (int q = count; q < 3; ++q) a.start[q] = (int)at;
+    hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)at), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -58,6 +58,8 @@ struct bmpl_mlp {
     uint16_t* tdu = nullptr;     // [h][capP]
     uint16_t* tds = nullptr;     // [m][capP]
     float* rowloss = nullptr;    // [cap]
+    double* rowpart = nullptr;   // [mpad / 64][capP] the loss tiles' sums by row
+    double* colpart = nullptr;   // [capP / 64][mpad + 2 h] tile sums by column of dl/ds, dl/du2 and dl/du1
 };
 
 namespace {
@@ -68,6 +70,7 @@ void free_all(bmpl_mlp* q)
     dfree(q->apt); dfree(q->b16); dfree(q->z); dfree(q->x0); dfree(q->h1); dfree(q->h2); dfree(q->logits);
     dfree(q->u1); dfree(q->u2); dfree(q->ds16); dfree(q->du2); dfree(q->du2_16); dfree(q->du1); dfree(q->du1_16);
     dfree(q->tx0); dfree(q->th1); dfree(q->th2); dfree(q->tdu); dfree(q->tds); dfree(q->rowloss);
+    dfree(q->rowpart); dfree(q->colpart);
 }
 
 bmpl_status ensure_train_buffers(bmpl_mlp* q)
@@ -87,6 +90,8 @@ bmpl_status ensure_train_buffers(bmpl_mlp* q)
     HIPC(dalloc(&q->tdu, h * q->capP));
     HIPC(dalloc(&q->tds, (size_t)q->m * q->capP));
     HIPC(dalloc(&q->rowloss, cap));
+    HIPC(dalloc(&q->rowpart, (size_t)(q->mpad / 64) * q->capP));
+    HIPC(dalloc(&q->colpart, (size_t)(q->capP / 64) * (q->mpad + 2 * h)));
     return BMPL_OK;
 }
 
@@ -114,8 +119,9 @@ bmpl_status layers(bmpl_mlp* q, int rows, bool keep, float* S, int64_t lds, hipS
 bmpl_status refresh_transposes(bmpl_mlp* q, hipStream_t s)
 {
     if (!q->wt_stale) return BMPL_OK;
-    HIPC(mlp_transpose(q->w16 + q->oW2, q->h, q->h, q->h, q->w2t, q->h, s));
-    HIPC(mlp_transpose(q->w16 + q->oW3, q->h, q->m, q->h, q->w3t, q->mpad, s));
+    const TransposeJob jobs[2] = {{q->w16 + q->oW2, q->h, q->h, q->h, q->w2t, q->h},
+                                  {q->w16 + q->oW3, q->h, q->m, q->h, q->w3t, q->mpad}};
+    HIPC(mlp_transposes(jobs, 2, s));
     q->wt_stale = false;
     return BMPL_OK;
 }
@@ -276,25 +282,33 @@ bmpl_status bmpl_mlp_loss_grad(bmpl_mlp* q, const float* B_dev, int64_t ldb, int
     st = embed_rows(q, B_dev, ldb, p, nullptr, 0, s);
     if (st == BMPL_OK) st = layers(q, p, true, q->logits, mpad, s);
     if (st != BMPL_OK) return st;
-    // output layer: dS (in place of the scores, float32) and its bfloat16 copy
-    HIPC(mlp_bce_grad(q->logits, mpad, q->ds16, mpad, m, mpad, p, supp_dev, ld_supp, supp_len_dev, (float)pos_weight,
-                      q->rowloss, loss_dev, s));
-    HIPC(mlp_colsum(q->logits, mpad, p, m, g + q->ob3, s));                          // db3
-    HIPC(mlp_transpose(q->ds16, mpad, p, m, q->tds, capP, s));
-    HIPC(mlp_transpose(q->h2, h, p, h, q->th2, capP, s));
+    // the batch-contiguous copies of the layers' inputs for the weight gradients
+    const TransposeJob acts[3] = {{q->h2, h, p, h, q->th2, capP}, {q->h1, h, p, h, q->th1, capP},
+                                  {q->x0, d, p, d, q->tx0, capP}};
+    HIPC(mlp_transposes(acts, 3, s));
+    // output layer: dS in bfloat16, both ways round, and the tiles' sums for db3 and the loss
+    PartialSums ps{};
+    const int trows = (p + 63) / 64;
+    double* cp3 = q->colpart;
+    double* cp2 = cp3 + (int64_t)trows * mpad;
+    double* cp1 = cp2 + (int64_t)trows * h;
+    HIPC(mlp_bce_tiles(q->logits, mpad, q->ds16, mpad, q->tds, capP, m, mpad, p, supp_dev, ld_supp, supp_len_dev,
+                       (float)pos_weight, cp3, mpad, q->rowpart, capP, s));
     HIPC(mlp_gemm_store(q->tds, capP, m, q->th2, capP, h, kB, g + q->oW3, h, nullptr, s));   // dW3 = dS^T H2
     // second layer: dU2 = (dS W3) * gelu'(U2)
     HIPC(mlp_gemm_gelu_back(q->ds16, mpad, p, q->w3t, mpad, h, mpad, q->u2, h, q->du2, h, q->du2_16, h, s));
-    HIPC(mlp_colsum(q->du2, h, p, h, g + q->ob2, s));                                // db2
-    HIPC(mlp_transpose(q->du2_16, h, p, h, q->tdu, capP, s));
-    HIPC(mlp_transpose(q->h1, h, p, h, q->th1, capP, s));
+    HIPC(mlp_transpose_colsum(q->du2, h, p, h, q->tdu, capP, cp2, h, s));
     HIPC(mlp_gemm_store(q->tdu, capP, h, q->th1, capP, h, kB, g + q->oW2, h, nullptr, s));   // dW2 = dU2^T H1
     // first layer: dU1 = (dU2 W2) * gelu'(U1)
     HIPC(mlp_gemm_gelu_back(q->du2_16, h, p, q->w2t, h, h, h, q->u1, h, q->du1, h, q->du1_16, h, s));
-    HIPC(mlp_colsum(q->du1, h, p, h, g + q->ob1, s));                                // db1
-    HIPC(mlp_transpose(q->du1_16, h, p, h, q->tdu, capP, s));
-    HIPC(mlp_transpose(q->x0, d, p, d, q->tx0, capP, s));
+    HIPC(mlp_transpose_colsum(q->du1, h, p, h, q->tdu, capP, cp1, h, s));
     HIPC(mlp_gemm_store(q->tdu, capP, h, q->tx0, capP, d, kB, g + q->oW1, d, nullptr, s));   // dW1 = dU1^T Z
+    // db3, db2, db1 and the loss
+    ps.part[0] = cp3; ps.ldc[0] = mpad; ps.cols[0] = m; ps.out[0] = g + q->ob3;
+    ps.part[1] = cp2; ps.ldc[1] = h; ps.cols[1] = h; ps.out[1] = g + q->ob2;
+    ps.part[2] = cp1; ps.ldc[2] = h; ps.cols[2] = h; ps.out[2] = g + q->ob1;
+    ps.rowpart = q->rowpart; ps.ldr = capP; ps.tile_cols = mpad / 64; ps.rows = p; ps.rowloss = q->rowloss;
+    HIPC(mlp_partial_sums(ps, loss_dev, s));
     return BMPL_OK;
 }
 

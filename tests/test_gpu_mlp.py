@@ -309,3 +309,27 @@ def test_learned_proposal_gain_face_like():
     lam = P.lambda_rel * np.abs(P.At.astype(np.float64) @ P.Bt[rows].astype(np.float64).T).max(axis=0)
     ref = oracle.solve(P.At, P.Bt[rows], lam, P.rho)
     check_batch(P.At, P.Bt, lam, warm, ref, rows=range(len(rows)), gpu_rows=rows)
+
+
+@pytest.mark.parametrize("p,m", [(1, 65), (63, 128), (65, 640), (129, 641)])
+def test_loss_and_gradient_at_tile_edges(p, m):
+    """The loss's 64 x 64 tiles at their edges: one row or atom past a tile, a full last tile, and supports
+    with entries outside [0, m) and repeated ones.  Same bounds as above (8 u loss, 16 u per block)."""
+    pk = _lib()
+    P, Pm, params, (d, h, m) = _small(p + m, m=m, d=64, h=64, p=p, k=7)
+    net = pk.ProposalNet(to_dev(P.At), to_dev(Pm), h, max_batch=p)
+    net.set_params(to_dev(params))
+    supp = np.full((p, 10), -1, dtype=np.int32)
+    for i, s in enumerate(P.supports):
+        supp[i, :len(s)] = s
+        supp[i, len(s)] = s[0]                       # listed twice
+        supp[i, len(s) + 1] = m + i                  # no atom
+    lens = np.full(p, 10, dtype=np.int32)
+    pw = 5.0
+    loss, g = net.loss_grad(to_dev(P.Bt), to_dev(supp), to_dev(lens), pw)
+    Zr = mo.embed(mo.projected_dictionary(P.At, Pm), P.Bt)
+    loss_r, g_r = mo.loss_and_grad(oracle_params(params, d, h, m), Zr, mo.labels(P.supports, m), pw, d, h, m)
+    assert abs(float(loss.item()) - loss_r) <= 8 * U * loss_r
+    gb, rb = mo.unpack(g.cpu().numpy().astype(np.float64), d, h, m), mo.unpack(g_r, d, h, m)
+    for name in ("W1", "b1", "W2", "b2", "W3", "b3"):
+        assert rel(gb[name], rb[name]) <= 16 * U, (name, rel(gb[name], rb[name]))
