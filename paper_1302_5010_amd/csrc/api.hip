@@ -59,13 +59,50 @@ bmpl_status scratch_address(int device, void** out)
     return BMPL_OK;
 }
 
-// Rows 0..p-1 of dst = the residuals r_i = R + i ldr (n values, zeros up to kpad); row p all zero.
-__global__ __launch_bounds__(256) void stage_rows_kernel(const float* __restrict__ R, int64_t ldr, int n, int p,
-                                                         float* __restrict__ dst, int kpad)
+// Rows 0..p-1 of dst = the residuals r_i = R + i ldr (n values, zeros up to kpad) in the product's own type
+// (float32, or rounded to bfloat16); row p all zero.  Four values per thread: one 16-byte read when R's rows are
+// 16-byte aligned (the same for every thread), else four.
+__device__ __forceinline__ void put4(float* d, float4 v) { *reinterpret_cast<float4*>(d) = v; }
+__device__ __forceinline__ void put4(uint16_t* d, float4 v)
 {
-    const int i = blockIdx.x;
-    float* d = dst + (int64_t)i * kpad;
-    for (int r = threadIdx.x; r < kpad; r += 256) d[r] = (i < p && r < n) ? R[(int64_t)i * ldr + r] : 0.0f;
+    *reinterpret_cast<uint2*>(d) = make_uint2((uint32_t)bf16_round(v.x) | ((uint32_t)bf16_round(v.y) << 16),
+                                              (uint32_t)bf16_round(v.z) | ((uint32_t)bf16_round(v.w) << 16));
+}
+template <class T>
+__global__ __launch_bounds__(256) void stage_rows_kernel(const float* __restrict__ R, int64_t ldr, int n, int p,
+                                                         T* __restrict__ dst, int kpad)
+{
+    const int i = blockIdx.y;
+    const int r = 4 * (blockIdx.x * 256 + threadIdx.x);
+    if (r >= kpad) return;                       // kpad % 4 == 0
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < p && r < n) {
+        const float* s = R + (int64_t)i * ldr + r;
+        if (r + 4 <= n && (ldr & 3) == 0 && (reinterpret_cast<uintptr_t>(R) & 15) == 0) {
+            v = *reinterpret_cast<const float4*>(s);
+        } else {
+            v.x = s[0];
+            if (r + 1 < n) v.y = s[1];
+            if (r + 2 < n) v.z = s[2];
+            if (r + 3 < n) v.w = s[3];
+        }
+    }
+    put4(dst + (int64_t)i * kpad + r, v);
+}
+
+// In one launch: a clear, a strided copy and a conversion took 20 us for 1000 residuals of 1024 values, this 5 us.
+template <class T>
+hipError_t stage_rows(const float* R, int64_t ldr, int n, int p, T* dst, int kpad, hipStream_t s)
+{
+    // rows along y (at most 65535 per launch), so a row's chunk index needs no division
+    for (int64_t i0 = 0; i0 <= p; i0 += 65535) {
+        const int rows = (int)std::min<int64_t>(65535, (int64_t)p + 1 - i0);
+        hipLaunchKernelGGL(stage_rows_kernel<T>, dim3((kpad / 4 + 255) / 256, rows), dim3(256), 0, s,
+                           R + i0 * ldr, ldr, n, (int)(p - i0), dst + i0 * kpad, kpad);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace
@@ -98,7 +135,6 @@ struct bmpl_ctx {
     int* n_spill_dev = nullptr;   // their count
     int* cand = nullptr;          // [p_cap][CANDCAP] screening candidates
     int* ncand = nullptr;         // [p_cap]
-    uint16_t* diag16 = nullptr;   // bfloat16 staging of bmpl_correlate
     size_t lds_dyn_max = 0;       // dynamic LDS a solve workgroup may use (bytes)
     bool block_append = false;    // inverse-factor appends in blocks (BMPL_FLAG_BLOCK_APPEND sets it)
     bool qroute = false;          // correlation as beta - Q_{:,S} x_S after the first pass (BMPL_FLAG_Q_ROUTE)
@@ -127,9 +163,17 @@ struct bmpl_ctx {
     int corr_shape[3] = {0, 3, 4};
     int corr_variant(int n_act) const { return corr_shape[n_act >= 512 ? 0 : (n_act >= 64 ? 1 : 2)]; }
 
-    // diagnostic correlate staging
+    // bmpl_correlate's staged residuals, diag_cap + 1 rows: float32 (float32 product, and the e4m3 one's source),
+    // bfloat16 or e4m3 with its scales.  Kept between calls; a call on another stream than the last one waits
+    // for the last one's product (diag_done), since both use the same rows.
     float* diagR = nullptr;
+    uint16_t* diag16 = nullptr;
+    uint8_t* diag8 = nullptr;
+    float* diag_sc8 = nullptr;
     int diag_cap = 0;
+    hipEvent_t diag_done = nullptr;
+    hipStream_t diag_stream = nullptr;
+    bool diag_used = false;
     unsigned char* scratch = nullptr;   // this device's address of the no-allocation scratch
 
     // kernel timing (BMPL_FLAG_TIMING)
@@ -624,8 +668,11 @@ bmpl_status bmpl_destroy(bmpl_ctx* c)
     dfree(c->A16p);
     dfree(c->A8);
     dfree(c->ascale8);
-    dfree(c->diag16);
     dfree(c->diagR);
+    dfree(c->diag16);
+    dfree(c->diag8);
+    dfree(c->diag_sc8);
+    if (c->diag_done) (void)hipEventDestroy(c->diag_done);
     dfree(c->phase_dev);
     drop_graphs(c);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
@@ -648,39 +695,51 @@ bmpl_status bmpl_correlate(bmpl_ctx* c, const float* R_dev, int64_t ldr, int32_t
     if (p < 0 || ldr < c->n || ldg < c->m) return fail(BMPL_E_INVALID, "bmpl_correlate: bad shape");
     if (p == 0) return BMPL_OK;
     hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
+    const bool reduced = c->A8 || c->A16;
+    if (reduced) {
+        // the reduced-precision staging may allocate: not under capture (bmpl_correlate_noalloc is for that)
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        HIPC(hipStreamIsCapturing(s, &cap));
+        if (cap != hipStreamCaptureStatusNone)
+            return fail(BMPL_E_HIP, "bmpl_correlate: the reduced-precision product cannot be captured; use "
+                                    "bmpl_correlate_noalloc");
+    }
     if (p > c->diag_cap) {
         dfree(c->diagR);
-        HIPC(dalloc(&c->diagR, (size_t)(p + 1) * c->kpad));
-        c->diag_cap = p;
-    }
-    HIPC(hipMemsetAsync(c->diagR, 0, (size_t)(p + 1) * c->kpad * sizeof(float), s));
-    HIPC(hipMemcpy2DAsync(c->diagR, c->kpad * sizeof(float), R_dev, ldr * sizeof(float), c->n * sizeof(float), p,
-                          hipMemcpyDeviceToDevice, s));
-    if (c->A8) {
-        uint8_t* d8 = nullptr;
-        float* sc8 = nullptr;
-        hipError_t e = dalloc(&d8, (size_t)(p + 1) * c->kpad);
-        if (e == hipSuccess) e = dalloc(&sc8, (size_t)p + 1);
-        if (e == hipSuccess) e = launch_atoms_fp8(c->diagR, c->kpad, c->kpad, d8, sc8, p + 1, s);
-        if (e == hipSuccess)
-            e = launch_corr_gemm_fp8(c->corr_variant(p), c->A8, c->kpad, c->m, c->kpad, d8, c->kpad, nullptr,
-                                     nullptr, p, G_dev, ldg, p, 0, 1 << 30, c->ascale8, sc8, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        dfree(d8);
-        dfree(sc8);
-        HIPC(e);
-        return BMPL_OK;
-    }
-    if (c->A16) {
         dfree(c->diag16);
-        HIPC(dalloc(&c->diag16, (size_t)(p + 1) * c->kpad));
-        HIPC(launch_to_bf16(c->diagR, c->kpad, c->diag16, c->kpad, p + 1, c->kpad, s));
-        HIPC(launch_corr_gemm_bf16(c->corr_variant(p), c->A16, c->A16p, c->kpad, c->m, c->kpad, c->diag16, c->kpad, nullptr,
-                                   nullptr, p, G_dev, ldg, p, 0, 1 << 30, s));
-        HIPC(hipStreamSynchronize(s));
+        dfree(c->diag8);
+        dfree(c->diag_sc8);
+        c->diag_cap = 0;
+        const size_t rows = (size_t)p + 1;
+        if (!c->A16 || c->A8) HIPC(dalloc(&c->diagR, rows * c->kpad));
+        if (c->A16 && !c->A8) HIPC(dalloc(&c->diag16, rows * c->kpad));
+        if (c->A8) {
+            HIPC(dalloc(&c->diag8, rows * c->kpad));
+            HIPC(dalloc(&c->diag_sc8, rows));
+        }
+        if (reduced && !c->diag_done) HIPC(hipEventCreateWithFlags(&c->diag_done, hipEventDisableTiming));
+        c->diag_cap = p;
+        c->diag_used = false;   // freeing the old rows waited for the device
+    }
+    if (reduced && c->diag_used && c->diag_stream != s) HIPC(hipStreamWaitEvent(s, c->diag_done, 0));
+    if (c->A8) {
+        HIPC(stage_rows(R_dev, ldr, c->n, p, c->diagR, c->kpad, s));
+        HIPC(launch_atoms_fp8(c->diagR, c->kpad, c->kpad, c->diag8, c->diag_sc8, p + 1, s));
+        HIPC(launch_corr_gemm_fp8(c->corr_variant(p), c->A8, c->kpad, c->m, c->kpad, c->diag8, c->kpad, nullptr,
+                                  nullptr, p, G_dev, ldg, p, 0, 1 << 30, c->ascale8, c->diag_sc8, s));
+    } else if (c->A16) {
+        HIPC(stage_rows(R_dev, ldr, c->n, p, c->diag16, c->kpad, s));
+        HIPC(launch_corr_gemm_bf16(c->corr_variant(p), c->A16, c->A16p, c->kpad, c->m, c->kpad, c->diag16, c->kpad,
+                                   nullptr, nullptr, p, G_dev, ldg, p, 0, 1 << 30, s));
+    } else {
+        HIPC(stage_rows(R_dev, ldr, c->n, p, c->diagR, c->kpad, s));
+        HIPC(launch_corr_gemm_f32(c->corr_variant(p), c->At, c->kpad, c->m, c->kpad, c->diagR, c->kpad, nullptr,
+                                  nullptr, p, G_dev, ldg, p, 0, 1 << 30, s));
         return BMPL_OK;
     }
-    HIPC(launch_corr_gemm_f32(c->corr_variant(p), c->At, c->kpad, c->m, c->kpad, c->diagR, c->kpad, nullptr, nullptr, p, G_dev, ldg, p, 0, 1 << 30, s));
+    HIPC(hipEventRecord(c->diag_done, s));
+    c->diag_stream = s;
+    c->diag_used = true;
     return BMPL_OK;
 }
 
@@ -704,8 +763,7 @@ bmpl_status bmpl_correlate_noalloc(bmpl_ctx* c, const float* R_dev, int64_t ldr,
                     (size_t)BMPL_NOALLOC_SCRATCH_BYTES);
     hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
     float* stage = reinterpret_cast<float*>(c->scratch);
-    hipLaunchKernelGGL(stage_rows_kernel, dim3(p + 1), dim3(256), 0, s, R_dev, ldr, c->n, p, stage, c->kpad);
-    HIPC(hipGetLastError());
+    if (!c->A16 || c->A8) HIPC(stage_rows(R_dev, ldr, c->n, p, stage, c->kpad, s));
     if (c->A8) {
         uint8_t* r8 = c->scratch + o8;
         float* sc8 = reinterpret_cast<float*>(c->scratch + os);
@@ -716,7 +774,7 @@ bmpl_status bmpl_correlate_noalloc(bmpl_ctx* c, const float* R_dev, int64_t ldr,
     }
     if (c->A16) {
         uint16_t* r16 = reinterpret_cast<uint16_t*>(c->scratch + o16);
-        HIPC(launch_to_bf16(stage, c->kpad, r16, c->kpad, p + 1, c->kpad, s));
+        HIPC(stage_rows(R_dev, ldr, c->n, p, r16, c->kpad, s));
         HIPC(launch_corr_gemm_bf16(c->corr_variant(p), c->A16, c->A16p, c->kpad, c->m, c->kpad, r16, c->kpad, nullptr, nullptr,
                                    p, G_dev, ldg, p, 0, 1 << 30, s));
         return BMPL_OK;

@@ -926,3 +926,28 @@ def test_smpl_needs_the_gram_table_and_a_width_limit():
         pk.Solver(to_dev(P.At), 0.1, omega=3, gram_table=False)
     with pytest.raises(pk.BmplError):
         pk.Solver(to_dev(P.At), 0.1, rho=30, omega=3)
+
+
+@pytest.mark.parametrize("screen", ["fp32", "bf16", "fp8"])
+@pytest.mark.parametrize("n,p", [(1, 1), (63, 3), (130, 70), (1030, 5)])
+def test_correlate_staging(screen, n, p):
+    """bmpl_correlate's staged residuals: lengths that are no multiple of four (unaligned rows), one to several
+    chunks per row, and a second call on another stream with fewer rows, equal bit for bit to the
+    allocation-free call's."""
+    pk = _lib()
+    At = to_dev(bi.gaussian_dictionary(n, 300, 41))
+    s = pk.Solver(At, 0.1, screen=screen)
+    R = torch.randn(p, n, generator=torch.Generator().manual_seed(n + p)).cuda()
+    ref = torch.empty(p, 300, device="cuda")
+    s.correlate_noalloc(R, ref)
+    G = s.correlate(R)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        H = s.correlate(R[: (p + 1) // 2].contiguous(), stream=side)
+    torch.cuda.synchronize()
+    assert torch.equal(G, ref) and torch.equal(H, ref[: (p + 1) // 2])
+    tol = {"fp32": 2 * n * 2.0 ** -24, "bf16": 2.0 ** -7, "fp8": 2.0 ** -2}[screen]
+    exact = R.double() @ At.double().T
+    assert bool(((G.double() - exact).abs() <= tol * R.double().norm(dim=1, keepdim=True)).all())
+    s.close()
