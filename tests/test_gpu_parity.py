@@ -928,6 +928,25 @@ def test_smpl_needs_the_gram_table_and_a_width_limit():
         pk.Solver(to_dev(P.At), 0.1, rho=30, omega=3)
 
 
+@pytest.mark.parametrize("n,m", [(70, 1), (33, 33), (130, 700), (96, 2050), (40, 5761)])
+def test_gram_table_tile_sizes_and_reused_blocks(n, m):
+    """The Gram table on each tile size of its kernel (32, 64 and 128, with ragged last tiles), in a context that
+    takes over the device memory of a destroyed one: exactly symmetric, every entry within the bound of an
+    n-term float64 sum of exact products, 2 n 2^-53 for unit atoms."""
+    pk = _lib()
+    At = bi.gaussian_dictionary(n, m, 40)
+    stale = pk.Solver(to_dev(np.full((m, n), 3.0, dtype=np.float32)), 0.1)   # leaves its blocks behind
+    stale.close()
+    s = pk.Solver(to_dev(At), 0.1)
+    Q = s.gram_table().cpu().numpy()
+    G = s.correlate(to_dev(At[:5])).cpu().numpy()
+    s.close()
+    ref = At.astype(np.float64) @ At.astype(np.float64).T
+    assert np.array_equal(Q, Q.T)
+    assert np.abs(Q - ref).max() <= 2 * n * 2.0 ** -53
+    assert np.abs(G - ref[:5]).max() <= 2 * n * 2.0 ** -24
+
+
 @pytest.mark.parametrize("screen", ["fp32", "bf16", "fp8"])
 @pytest.mark.parametrize("n,p", [(1, 1), (63, 3), (130, 70), (1030, 5)])
 def test_correlate_staging(screen, n, p):
