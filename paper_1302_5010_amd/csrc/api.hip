@@ -185,6 +185,10 @@ struct bmpl_ctx {
     uint64_t* phase_dev = nullptr;     // [15] solve-kernel phase ticks and counters
     int wall_khz = 0;
 
+    // the create-time blocks (dictionary copies, Gram table) and their sizes: they return to the block pool
+    struct Pooled { void* p; size_t bytes; };
+    std::vector<Pooled> pooled;
+
     // graph capture of iteration segments (BMPL_FLAG_GRAPH)
     hipStream_t cap_stream = nullptr;
     long ws_gen = 0;                   // bumped whenever workspace buffers move
@@ -259,6 +263,34 @@ void fold_timing(bmpl_ctx* c, size_t first, size_t last)
 }  // namespace
 
 namespace {
+
+// A create-time block of `count` values from the block pool; bmpl_destroy puts it back.
+template <class T>
+hipError_t pool_alloc(bmpl_ctx* c, T** p, size_t count)
+{
+    void* q = nullptr;
+    size_t got = 0;
+    const hipError_t e = block_pool().take(c->device, &q, count * sizeof(T), &got);
+    *p = e == hipSuccess ? static_cast<T*>(q) : nullptr;
+    if (e == hipSuccess) c->pooled.push_back({q, got});
+    return e;
+}
+
+// Put the create-time blocks back once nothing on the device uses them (hipFree would wait for that as well).
+void pool_release(bmpl_ctx* c)
+{
+    int cur = 0;
+    const bool known = hipGetDevice(&cur) == hipSuccess;
+    const bool idle = known && hipSetDevice(c->device) == hipSuccess && hipDeviceSynchronize() == hipSuccess;
+    for (const auto& b : c->pooled) {
+        if (idle) block_pool().put(c->device, b.p, b.bytes);
+        else (void)hipFree(b.p);
+    }
+    c->pooled.clear();
+    block_pool().age(c->device);
+    if (known) (void)hipSetDevice(cur);
+    (void)hipGetLastError();
+}
 
 void free_signals(bmpl_ctx* c)
 {
@@ -531,7 +563,7 @@ bmpl_status bmpl_create(const float* A_dev, int64_t lda, int32_t n, int32_t m, b
     c->w.kpad = c->kpad;
     c->w.m = m;
     c->w.words = (m + 31) / 32;
-    e = dalloc(&c->At, (size_t)(m + 1) * c->kpad);   // row m stays zero
+    e = pool_alloc(c, &c->At, (size_t)(m + 1) * c->kpad);   // row m stays zero
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->h_count), sizeof(int), hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->h_arena), sizeof(Arena), hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->h_arena_rd), sizeof(Arena), hipHostMallocDefault);
@@ -573,10 +605,10 @@ bmpl_status bmpl_create(const float* A_dev, int64_t lda, int32_t n, int32_t m, b
     // bfloat16 copy of the dictionary and the factors of the screening band.
     if (e == hipSuccess && opt.screen != BMPL_PREC_FP32) {
         float* norms = nullptr;
-        e = dalloc(&c->A16, (size_t)(m + 1) * c->kpad);
+        e = pool_alloc(c, &c->A16, (size_t)(m + 1) * c->kpad);
         if (e == hipSuccess) e = hipMemsetAsync(c->A16, 0, (size_t)(m + 1) * c->kpad * sizeof(uint16_t), s);
         if (e == hipSuccess) e = launch_to_bf16(c->At, c->kpad, c->A16, c->kpad, m, c->kpad, s);
-        if (e == hipSuccess) e = dalloc(&c->A16p, packed_bf16_elems(m, c->kpad));
+        if (e == hipSuccess) e = pool_alloc(c, &c->A16p, packed_bf16_elems(m, c->kpad));
         if (e == hipSuccess) e = launch_pack_bf16(c->A16, c->kpad, m, c->kpad, c->A16p, s);
         if (e == hipSuccess) e = dalloc(&norms, (size_t)3 * m);
         if (e == hipSuccess) e = launch_atom_norms(c->At, c->kpad, c->kpad, norms, m, s);
@@ -599,7 +631,7 @@ bmpl_status bmpl_create(const float* A_dev, int64_t lda, int32_t n, int32_t m, b
     }
     // e4m3 copy with per-atom power-of-two scales for the FP8 ranking product (row m zero, scale 1)
     if (e == hipSuccess && opt.screen == BMPL_PREC_FP8) {
-        e = dalloc(&c->A8, (size_t)(m + 1) * c->kpad);
+        e = pool_alloc(c, &c->A8, (size_t)(m + 1) * c->kpad);
         if (e == hipSuccess) e = hipMemsetAsync(c->A8, 0, (size_t)(m + 1) * c->kpad, s);
         if (e == hipSuccess) e = dalloc(&c->ascale8, (size_t)m + 1);
         if (e == hipSuccess) e = launch_atoms_fp8(c->At, c->kpad, c->kpad, c->A8, c->ascale8, m, s);
@@ -612,7 +644,7 @@ bmpl_status bmpl_create(const float* A_dev, int64_t lda, int32_t n, int32_t m, b
     // Gram table Q = A^T A (float64) unless disabled or larger than the table budget.
     const double q_bytes = 8.0 * (double)m * (double)m;
     if (e == hipSuccess && !(opt.flags & BMPL_FLAG_NO_GRAM_TABLE) && q_bytes <= BMPL_GRAM_TABLE_MAX_BYTES) {
-        e = dalloc(&c->Q, (size_t)m * (size_t)m);
+        e = pool_alloc(c, &c->Q, (size_t)m * (size_t)m);
         if (e == hipSuccess) e = launch_gram_table(c->At, c->kpad, m, c->kpad, c->Q, m, s);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -661,12 +693,8 @@ bmpl_status bmpl_create(const float* A_dev, int64_t lda, int32_t n, int32_t m, b
 bmpl_status bmpl_destroy(bmpl_ctx* c)
 {
     if (!c) return BMPL_OK;
+    pool_release(c);
     free_signals(c);
-    dfree(c->At);
-    dfree(c->Q);
-    dfree(c->A16);
-    dfree(c->A16p);
-    dfree(c->A8);
     dfree(c->ascale8);
     dfree(c->diagR);
     dfree(c->diag16);
@@ -846,6 +874,7 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
             (void)hipGetLastError();
             free_b = 0;
         }
+        free_b += block_pool().kept(c->device);
         if (8.0 * (double)need <= 8.0 * (double)c->arena_total + 0.5 * (double)free_b) kfull = k;
     }
     const bool full = kfull > 0;

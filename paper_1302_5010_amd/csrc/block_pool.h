@@ -1,0 +1,129 @@
+// Device blocks of destroyed contexts, kept for the next context of the process.
+//
+// A context's dictionary copies and Gram table are allocated when it is created and freed when it is destroyed.
+// Programs that take one dictionary after another into use (an alternating dictionary update, a sweep) pay for
+// that each time: mapping and clearing 288 MB for 6000 atoms costs 0.4 ms as long as the driver has cleared memory
+// at hand and 7 ms when it does not, against 0.74 ms for computing the table itself.
+//
+// Bounded: at most POOL_BYTES per device stay here, the oldest block leaves first; a block that no context has
+// taken within POOL_AGE destroyed contexts is given back to the driver, and every block of the device is when an
+// allocation of the library fails (the allocation is then tried again).  Blocks are put here only after the device
+// has been synchronised, so a block taken has no work in flight on any stream; a mutex serialises the threads.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <mutex>
+#include <vector>
+
+namespace bmpl {
+
+constexpr size_t POOL_BYTES = (size_t)4 << 30;
+constexpr int POOL_AGE = 8;
+
+class BlockPool {
+public:
+    // A block of at least `bytes` on the current device `dev` (a kept one when its size is at most 1/8 larger).
+    hipError_t take(int dev, void** out, size_t bytes, size_t* got)
+    {
+        *out = nullptr;
+        if (bytes == 0) bytes = 1;
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            int best = -1;
+            for (int i = 0; i < (int)kept_.size(); ++i)
+                if (kept_[i].dev == dev && kept_[i].bytes >= bytes && kept_[i].bytes <= bytes + bytes / 8 &&
+                    (best < 0 || kept_[i].bytes < kept_[best].bytes))
+                    best = i;
+            if (best >= 0) {
+                *out = kept_[best].p;
+                *got = kept_[best].bytes;
+                kept_.erase(kept_.begin() + best);
+                return hipSuccess;
+            }
+        }
+        hipError_t e = hipMalloc(out, bytes);
+        if (e == hipErrorOutOfMemory && drop(dev)) {
+            (void)hipGetLastError();
+            e = hipMalloc(out, bytes);
+        }
+        *got = bytes;
+        return e;
+    }
+
+    // Take over a block (the device is synchronised and `dev` current).
+    void put(int dev, void* p, size_t bytes)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        if (bytes > POOL_BYTES) {
+            (void)hipFree(p);
+            return;
+        }
+        kept_.push_back({p, bytes, dev, 0});
+        size_t sum = 0;
+        for (const auto& b : kept_) sum += b.dev == dev ? b.bytes : 0;
+        for (size_t i = 0; i < kept_.size() && sum > POOL_BYTES;) {
+            if (kept_[i].dev == dev) {
+                sum -= kept_[i].bytes;
+                (void)hipFree(kept_[i].p);
+                kept_.erase(kept_.begin() + i);
+            } else {
+                ++i;
+            }
+        }
+    }
+
+    // One more context of `dev` was destroyed: blocks that have waited too long go back.
+    void age(int dev)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        for (size_t i = 0; i < kept_.size();) {
+            if (kept_[i].dev == dev && ++kept_[i].age > POOL_AGE) {
+                (void)hipFree(kept_[i].p);
+                kept_.erase(kept_.begin() + i);
+            } else {
+                ++i;
+            }
+        }
+    }
+
+    // Bytes kept for `dev`.
+    size_t kept(int dev)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        size_t sum = 0;
+        for (const auto& b : kept_) sum += b.dev == dev ? b.bytes : 0;
+        return sum;
+    }
+
+    // Give every block of `dev` back; true if there was one.
+    bool drop(int dev)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        bool any = false;
+        for (size_t i = 0; i < kept_.size();) {
+            if (kept_[i].dev == dev) {
+                (void)hipFree(kept_[i].p);
+                kept_.erase(kept_.begin() + i);
+                any = true;
+            } else {
+                ++i;
+            }
+        }
+        return any;
+    }
+
+private:
+    struct Block { void* p; size_t bytes; int dev; int age; };
+    std::mutex mu_;
+    std::vector<Block> kept_;
+};
+
+// Never destroyed: the HIP runtime may be gone before a static destructor runs (the process's end frees all).
+inline BlockPool& block_pool()
+{
+    static BlockPool* pool = new BlockPool;
+    return *pool;
+}
+
+}  // namespace bmpl

@@ -9,6 +9,7 @@
 #include <string>
 
 #include "../../include/bmpl.h"
+#include "block_pool.h"
 
 namespace bmpl {
 
@@ -30,7 +31,13 @@ hipError_t dalloc(T** p, size_t count)
 {
     *p = nullptr;
     if (count == 0) count = 1;
-    return hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
+    int dev = 0;
+    if (e == hipErrorOutOfMemory && hipGetDevice(&dev) == hipSuccess && block_pool().drop(dev)) {
+        (void)hipGetLastError();
+        e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
+    }
+    return e;
 }
 
 template <class T>
