@@ -107,8 +107,9 @@ typedef enum {
 
 /* Tile shapes of the correlation kernel (bmpl_autotune, bmpl_set_tuning), signals x atoms (waves of
  * 64 lanes, each computing the sub-tile in parentheses): 0 128x128 (64x64), 1 256x256 (64x64, 16 waves),
- * 2 256x128 (64x64), 3 64x128 (32x64), 4 32x64 (32x32), 5 64x64 (32x32), 6 256x256 (128x128, 4 waves),
- * 7 256x256 (128x64, 8 waves); bfloat16 screening only (the dictionary's fragments read from global
+ * 2 256x128 (64x64), 3 64x128 (32x64), 4 32x16 in float32 and 32x32 in the others (one
+ * wave, for a few signals: both operands read straight from global memory into registers), 5 64x64
+ * (32x32), 6 256x256 (128x128, 4 waves), 7 256x256 (128x64, 8 waves); bfloat16 screening only (the dictionary's fragments read from global
  * memory in the matrix instruction's order, the residual tile through LDS): 8 256x256 (128x64, 8 waves),
  * 9 128x256 (64x64, 8 waves), 10 256x128 (128x64, 4 waves); both operand tiles copied from global
  * memory straight into LDS (no staging registers): 11 256x256 (128x64, 8 waves), 12 256x256 (64x64, 16

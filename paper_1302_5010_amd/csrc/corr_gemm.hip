@@ -313,6 +313,217 @@ __global__ __launch_bounds__((TileShape<BM, BN, WM, WN>::THREADS)) void corr_gem
         }
 }
 
+// ---------------------------------------------------------------------------------------------------
+// The product for a few running signals (shape 4).  Below a few dozen signals the product reads the dictionary
+// once and does little with it: the bound is HBM (134 MB of float32 at 2048 x 16384), so what counts is how many
+// bytes are in flight and that no matrix work is done for padding.  One wave per workgroup, all its operands
+// straight from global memory into registers (16 bytes per lane, two or three stages of 256 or 128 bytes per row in
+// flight), no LDS and no barrier, so the waves of a CU drift freely; the signals' rows are shared through L1.
+// 8 residuals against 2048 x 16384: 43.7 -> 27.7 us (4.9 TB/s), one against 1000 x 5001: 22.8 -> 9.3 us (before: 32 x 64
+// tiles of two 32 x 32 waves through LDS).
+//
+// float32: 16 atoms x 32 signals per wave (16 when no more are running) by v_mfma_f32_16x16x4f32.  The float32
+// matrix instructions accumulate their k in order of the lane groups, one fused multiply-add each, so taking k in
+// the order of the 32 x 32 x 2 steps of the other shapes (8 b + t, 8 b + 4 + t, t = 0..3) gives the same bits: two
+// steps of four k, k = 8 b + {0, 4, 1, 5} and {2, 6, 3, 7} over the lane groups q = 0..3.  A lane loads k = 16 B +
+// 4 q .. + 3 of its row; v_permlane32_swap of the loaded .x and .y (.z and .w) pairs the lane groups 0, 1 with 2, 3
+// as those steps want them, for b = 2 B and 2 B + 1 at once.
+// ---------------------------------------------------------------------------------------------------
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void swap_halves(float& x, float& y)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r[0]);   // lanes 0..31 of x, then lanes 0..31 of y
+    y = __uint_as_float(r[1]);   // lanes 32..63 of x, then lanes 32..63 of y
+}
+
+constexpr int FEW_M = 32;        // signals per wave
+
+template <int GROUPS>
+__device__ __forceinline__ void few_f32_loop(const float* pa, const float* (&pr)[2], int stages, floatx4 (&acc)[2])
+{
+    constexpr int BUF = 3;       // stages of 64 k in registers
+    floatx4 a[BUF][4], r[BUF][GROUPS][4];   // native vectors: the compiler keeps each in one register tuple
+    auto load = [&](int st, floatx4 (&fa)[4], floatx4 (&fr)[GROUPS][4]) {
+        const int k0 = 64 * (st < stages ? st : stages - 1);   // past the end: re-read the last, never used
+#pragma unroll
+        for (int e = 0; e < 4; ++e) fa[e] = *reinterpret_cast<const floatx4*>(pa + k0 + 16 * e);
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) fr[g][e] = *reinterpret_cast<const floatx4*>(pr[g] + k0 + 16 * e);
+    };
+    auto compute = [&](const floatx4 (&va)[4], const floatx4 (&vr)[GROUPS][4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            floatx4 fa = va[e];
+            asm volatile("" : "+v"(fa));         // consumed here, not where it was loaded
+            float a0 = fa[0], a1 = fa[1], a2 = fa[2], a3 = fa[3];
+            swap_halves(a0, a1);
+            swap_halves(a2, a3);
+#pragma unroll
+            for (int g = 0; g < GROUPS; ++g) {
+                floatx4 fr = vr[g][e];
+                asm volatile("" : "+v"(fr));
+                float r0 = fr[0], r1 = fr[1], r2 = fr[2], r3 = fr[3];
+                swap_halves(r0, r1);
+                swap_halves(r2, r3);
+                acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(r0, a0, acc[g], 0, 0, 0);
+                acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(r2, a2, acc[g], 0, 0, 0);
+                acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(r1, a1, acc[g], 0, 0, 0);
+                acc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(r3, a3, acc[g], 0, 0, 0);
+            }
+        }
+    };
+    // whole groups of BUF stages without a branch (a join would make the loads before it wait), then the rest
+#pragma unroll
+    for (int d = 0; d < BUF - 1; ++d) load(d, a[d], r[d]);
+    int s0 = 0;
+    for (; s0 + BUF <= stages; s0 += BUF) {
+#pragma unroll
+        for (int d = 0; d < BUF; ++d) {
+            load(s0 + d + BUF - 1, a[(d + BUF - 1) % BUF], r[(d + BUF - 1) % BUF]);
+            __builtin_amdgcn_sched_barrier(0);   // the loads stay ahead of this stage's matrix work
+            compute(a[d], r[d]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < BUF - 1; ++d)
+        if (s0 + d < stages) compute(a[d], r[d]);
+}
+
+__global__ __launch_bounds__(64) void corr_few_f32_kernel(
+    const float* __restrict__ At, int64_t lda, int m, int kpad, const float* __restrict__ Rbuf, int64_t ldr,
+    const int* __restrict__ act, const int* __restrict__ n_act_dev, int p_grid, float* __restrict__ G, int64_t ldg,
+    int tiles_n, int zero_row, int n_lo, int n_hi)
+{
+    const int n_act = n_act_dev ? *n_act_dev : p_grid;
+    if (n_act < n_lo || n_act >= n_hi) return;   // another tile shape serves this running count
+    const int tiles_m = ((n_act < p_grid ? n_act : p_grid) + FEW_M - 1) / FEW_M;   // as in corr_gemm_kernel
+    const int nwg = tiles_m * tiles_n;
+    if ((int)blockIdx.x >= nwg) return;
+    const int tile = xcd_tile_index(blockIdx.x, nwg);
+    const int tm = tile % tiles_m, tn = tile / tiles_m;
+    const int sig0 = tm * FEW_M, atom0 = tn * 16;
+    const int lane = threadIdx.x, l16 = lane & 15, q = lane >> 4;
+    const float* pr[2];
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const int i = sig0 + 16 * g + l16;
+        pr[g] = Rbuf + (int64_t)(i < n_act ? (act ? act[i] : i) : zero_row) * ldr + 4 * q;
+    }
+    const int ja = atom0 + l16;
+    const float* pa = At + (int64_t)(ja < m ? ja : m) * lda + 4 * q;
+    floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+    const bool two = sig0 + 16 < n_act;          // the same for the whole wave
+    if (two) few_f32_loop<2>(pa, pr, kpad / 64, acc);
+    else few_f32_loop<1>(pa, pr, kpad / 64, acc);
+    if (ja >= m) return;
+    // D of a 16 x 16 block: lane l, register r -> row (signal) 4 (l / 16) + r, column (atom) l % 16
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = sig0 + 16 * g + 4 * q + r;
+            if (i < n_act) G[(int64_t)i * ldg + ja] = acc[g][r];
+        }
+}
+
+// 16- and 8-bit operands: 32 atoms x 32 signals per wave, the matrix steps and their k order of mfma_tile_stage.
+template <class E>
+__global__ __launch_bounds__(64) void corr_few_kernel(
+    const E* __restrict__ At, int64_t lda, int m, int kpad, const E* __restrict__ Rbuf, int64_t ldr,
+    const int* __restrict__ act, const int* __restrict__ n_act_dev, int p_grid, float* __restrict__ G, int64_t ldg,
+    int tiles_n, int zero_row, int n_lo, int n_hi, const float* __restrict__ ascale, const float* __restrict__ rscale)
+{
+    const int n_act = n_act_dev ? *n_act_dev : p_grid;
+    if (n_act < n_lo || n_act >= n_hi) return;   // another tile shape serves this running count
+    const int tiles_m = ((n_act < p_grid ? n_act : p_grid) + FEW_M - 1) / FEW_M;   // as in corr_gemm_kernel
+    const int nwg = tiles_m * tiles_n;
+    if ((int)blockIdx.x >= nwg) return;
+    const int tile = xcd_tile_index(blockIdx.x, nwg);
+    const int tm = tile % tiles_m, tn = tile / tiles_m;
+    const int sig0 = tm * FEW_M, atom0 = tn * 32;
+    const int lane = threadIdx.x, l32 = lane & 31, h = lane >> 5;
+    const int is = sig0 + l32, ja = atom0 + l32;
+    const char* pr = reinterpret_cast<const char*>(Rbuf + (int64_t)(is < n_act ? (act ? act[is] : is) : zero_row) * ldr);
+    const char* pa = reinterpret_cast<const char*>(At + (int64_t)(ja < m ? ja : m) * lda);
+    const int stages = kpad * (int)sizeof(E) / TILE_ROW_BYTES;
+    constexpr int BUF = 4;       // stages of 128 bytes per row in registers
+    // chunk e of a stage (16 bytes per lane): bfloat16 k = 64 st + 16 e + 8 h, e4m3 bytes 64 (e / 2) + 32 h + 16 (e % 2)
+    floatx4 a[BUF][4], r[BUF][4];
+    auto load = [&](int st, floatx4 (&fa)[4], floatx4 (&fr)[4]) {
+        const int b0 = TILE_ROW_BYTES * (st < stages ? st : stages - 1);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int o = b0 + (sizeof(E) == 1 ? 64 * (e >> 1) + 32 * h + 16 * (e & 1) : 32 * e + 16 * h);
+            fa[e] = *reinterpret_cast<const floatx4*>(pa + o);
+            fr[e] = *reinterpret_cast<const floatx4*>(pr + o);
+        }
+    };
+    floatx16 acc[1][1];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[0][0][i] = 0.f;
+    auto compute = [&](const floatx4 (&va)[4], const floatx4 (&vr)[4]) {
+        if constexpr (sizeof(E) == 1) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                // the two 16-byte halves of each operand as one 32-byte fragment
+                const auto wide = [](floatx4 lo, floatx4 hi) {
+                    return __builtin_bit_cast(intx8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                };
+                const intx8 fx = wide(vr[2 * t], vr[2 * t + 1]), fw = wide(va[2 * t], va[2 * t + 1]);
+                acc[0][0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fx, fw, acc[0][0], 0, 0, 0, 127, 0, 127);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    __builtin_bit_cast(bf16x8, vr[e]), __builtin_bit_cast(bf16x8, va[e]), acc[0][0], 0, 0, 0);
+        }
+    };
+    // as in few_f32_loop
+#pragma unroll
+    for (int d = 0; d < BUF - 1; ++d) load(d, a[d], r[d]);
+    int s0 = 0;
+    for (; s0 + BUF <= stages; s0 += BUF) {
+#pragma unroll
+        for (int d = 0; d < BUF; ++d) {
+            load(s0 + d + BUF - 1, a[(d + BUF - 1) % BUF], r[(d + BUF - 1) % BUF]);
+            __builtin_amdgcn_sched_barrier(0);   // the loads stay ahead of this stage's matrix work
+            compute(a[d], r[d]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < BUF - 1; ++d)
+        if (s0 + d < stages) compute(a[d], r[d]);
+    store_tile<E, 1, 1>(acc, sig0, 0, atom0, 0, l32, h, m, n_act, act, G, ldg, ascale, rscale);
+}
+
+template <class E>
+hipError_t launch_few(const E* At, int64_t lda, int m, int kpad, const E* Rbuf, int64_t ldr, const int* act,
+                      const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row, int n_lo, int n_hi,
+                      const float* ascale, const float* rscale, hipStream_t stream)
+{
+    constexpr int BN = sizeof(E) == 4 ? 16 : 32;
+    const int tiles_m = (p_grid + FEW_M - 1) / FEW_M;
+    const int tiles_n = (m + BN - 1) / BN;
+    const int64_t nwg = (int64_t)tiles_m * tiles_n;
+    if (nwg > 0x7fffffff) return hipErrorInvalidValue;
+    if constexpr (sizeof(E) == 4) {
+        if (kpad % 64) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(corr_few_f32_kernel, dim3((unsigned)nwg), dim3(64), 0, stream, At, lda, m, kpad, Rbuf, ldr, act,
+                           n_act_dev, p_grid, G, ldg, tiles_n, zero_row, n_lo, n_hi);
+    } else {
+        hipLaunchKernelGGL(corr_few_kernel<E>, dim3((unsigned)nwg), dim3(64), 0, stream, At, lda, m, kpad, Rbuf, ldr, act,
+                           n_act_dev, p_grid, G, ldg, tiles_n, zero_row, n_lo, n_hi, ascale, rscale);
+    }
+    return hipGetLastError();
+}
+
 template <int BM, int BN, int WM, int WN>
 hipError_t launch_direct(const uint16_t* Apk, int m, int kpad, const uint16_t* Rbuf, int64_t ldr, const int* act,
                          const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row, int n_lo, int n_hi,
@@ -376,7 +587,7 @@ hipError_t launch_variant(int variant, const E* At, int64_t lda, int m, int kpad
     case 1: return launch_shape<E, 256, 256, 64, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
     case 2: return launch_shape<E, 256, 128, 64, 64, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
     case 3: return launch_shape<E, 64, 128, 32, 64, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 4: return launch_shape<E, 32, 64, 32, 32, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
+    case 4: return launch_few<E>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
     case 5: return launch_shape<E, 64, 64, 32, 32, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
     case 6: return launch_shape<E, 256, 256, 128, 128>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
     case 7: return launch_shape<E, 256, 256, 128, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
@@ -400,7 +611,7 @@ const char* corr_shape_name(int v)
     case 1: return "256x256 (16 waves of 64x64)";
     case 2: return "256x128 (8 waves of 64x64)";
     case 3: return "64x128 (4 waves of 32x64)";
-    case 4: return "32x64 (2 waves of 32x32)";
+    case 4: return "32x16 (float32) or 32x32 (one wave, operands from global memory)";
     case 5: return "64x64 (4 waves of 32x32)";
     case 6: return "256x256 (4 waves of 128x128)";
     case 7: return "256x256 (8 waves of 128x64)";
