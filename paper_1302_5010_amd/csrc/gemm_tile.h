@@ -394,6 +394,136 @@ __device__ __forceinline__ void mfma_tile_loop_dma(const E* __restrict__ X, cons
     }
 }
 
+// ---------------------------------------------------------------------------------------------------
+// The bfloat16 contraction with direct-to-LDS copies, NBUF buffers, and the stage's three kinds of work taken in
+// turn.  In mfma_tile_loop_dma every wave first issues the next slice's copies, then reads fragments, then
+// multiplies, all waves of the CU at the same time: 4096 x 20000 x 2048 on 256 x 256 tiles takes 372 us without its
+// epilogue, 263 without the copies, 160 without the matrix instructions and 179 with only those, so the parts add up.
+// Here a stage's fragments are read one chunk of k ahead into a second register set, and the reads and copies
+// are spread between the matrix instructions (sched_group_barrier), which run on while they issue.  What is left is
+// mostly power: the same loop on zeros is a quarter faster.
+// NBUF = 2 where two or more workgroups share a CU or a stage is long; NBUF = 3 keeps two slices in flight where one
+// workgroup has a CU to itself and its stages are short.  A stage waits for its own slice only (the newer ones, (NBUF -
+// 2) G copies, stay in flight), with a barrier that has no memory fence: the copies of slice s + NBUF - 1 go into
+// the buffer that stage s - 1 read, after the barrier that every wave passes with its reads done.
+// Same fragments, same order of k as the other loops, so the same bits.  us, staged loop -> this one (output rows x
+// columns x k; tile):  4096 x 20000 x 2048 (256 x 256) 407 -> 392; 1024 x 20000 x 2048 (128 x 128) 115 -> 100; 4096 x
+// 2048 x 2048 (128 x 128) 46.9 -> 38.9; 1024 x 2048 x 20032 (64 x 64 -> 64 x 128) 175 -> 128; 1024 x 2048 x 2048 20.1 ->
+// 15.2; 96 x 2048 x 2048 (64 x 64) 11.4 -> 10.5.
+// ---------------------------------------------------------------------------------------------------
+typedef float frag4 __attribute__((ext_vector_type(4)));
+
+template <int BM, int BN, int NBUF>
+struct PipeLds {
+    char x[NBUF][BM * TILE_ROW_BYTES];
+    char w[NBUF][BN * TILE_ROW_BYTES];
+};
+
+template <int BM, int BN, int WM, int WN, int NBUF>
+__device__ __forceinline__ void mfma_tile_loop_pipe(const __bf16* __restrict__ X,
+                                                    const int64_t (&oX)[DmaShape<BM, BN, WM, WN>::GX],
+                                                    const __bf16* __restrict__ W,
+                                                    const int64_t (&oW)[DmaShape<BM, BN, WM, WN>::GW], int kpad,
+                                                    PipeLds<BM, BN, NBUF>& lds, int ws, int wa,
+                                                    floatx16 (&acc)[TileShape<BM, BN, WM, WN>::TI][TileShape<BM, BN, WM, WN>::TJ])
+{
+    using S = TileShape<BM, BN, WM, WN>;
+    using D = DmaShape<BM, BN, WM, WN>;
+    constexpr int BK = TILE_ROW_BYTES / 2;
+    constexpr int TI = S::TI, TJ = S::TJ, NM = TI * TJ;
+    constexpr int G = D::GX + D::GW;            // this wave's copies per stage
+    constexpr int CC = NM >= 8 ? 2 : 1;         // chunks of k over which they are spread
+    constexpr int PER = (G + CC - 1) / CC;
+    const int wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int l32 = lane & 31;
+    const int h = lane >> 5;
+    const int sw = dma_swz(l32);
+    const int nst = kpad / BK;
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    auto copy = [&](int c, int k0, int buf) {
+        if (c < D::GX)
+            __builtin_amdgcn_global_load_lds((global_cvoid*)(X + oX[c < D::GX ? c : 0] + k0),
+                                             (lds_void*)(lds.x[buf] + (wave + S::WAVES * c) * 1024), 16, 0, 0);
+        else
+            __builtin_amdgcn_global_load_lds((global_cvoid*)(W + oW[c < D::GX ? 0 : c - D::GX] + k0),
+                                             (lds_void*)(lds.w[buf] + (wave + S::WAVES * (c - D::GX)) * 1024), 16, 0, 0);
+    };
+    frag4 fx[2][TI], fw[2][TJ];
+    auto read = [&](const char* cX, const char* cW, int kb, frag4 (&x)[TI], frag4 (&w)[TJ]) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+            x[i] = *reinterpret_cast<const frag4*>(cX + (ws + 32 * i + l32) * TILE_ROW_BYTES + (((2 * kb + h) ^ sw) << 4));
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+            w[j] = *reinterpret_cast<const frag4*>(cW + (wa + 32 * j + l32) * TILE_ROW_BYTES + (((2 * kb + h) ^ sw) << 4));
+    };
+    // slices past the last one copy the last again (into a buffer that no stage reads any more)
+#pragma unroll
+    for (int d = 0; d < NBUF - 1; ++d)
+#pragma unroll
+        for (int c = 0; c < G; ++c) copy(c, (d < nst ? d : nst - 1) * BK, d);
+    int cur = 0, nxt = NBUF - 1;
+    for (int st = 0; st < nst; ++st) {
+        const int kn = (st + NBUF - 1 < nst ? st + NBUF - 1 : nst - 1) * BK;
+        // this wave's copies of slice st have landed and its reads of stage st - 1 are done; then everyone's
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NBUF - 2) * G) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");          // no read or copy of this stage moves above the barrier
+        const char* cX = lds.x[cur];
+        const char* cW = lds.w[cur];
+        read(cX, cW, 0, fx[0], fw[0]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            if (kb < 3) read(cX, cW, kb + 1, fx[(kb + 1) & 1], fw[(kb + 1) & 1]);
+            int nc = 0;
+            if (kb < CC) {
+#pragma unroll
+                for (int c = kb * PER; c < (kb + 1) * PER && c < G; ++c) {
+                    copy(c, kn, nxt);
+                    ++nc;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fx[kb & 1][i]),
+                                                                       __builtin_bit_cast(bf16x8, fw[kb & 1][j]),
+                                                                       acc[i][j], 0, 0, 0);
+            // the order of issue: after each matrix instruction its share of the reads and copies
+            const int nr = kb < 3 ? TI + TJ : 0;
+#pragma unroll
+            for (int q = 0; q < NM; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);            // matrix
+#pragma unroll
+                for (int z = nr * q / NM; z < nr * (q + 1) / NM; ++z) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
+#pragma unroll
+                for (int z = nc * q / NM; z < nc * (q + 1) / NM; ++z) __builtin_amdgcn_sched_group_barrier(0x10, 1, 0);    // vector memory
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        cur = cur + 1 == NBUF ? 0 : cur + 1;
+        nxt = nxt + 1 == NBUF ? 0 : nxt + 1;
+    }
+    wait_vm0();   // no copy into this workgroup's LDS is left in flight
+}
+
+// The element `off` bytes past a row address that is the same in every lane (a scalar base and a 32-bit lane offset
+// in the instruction).
+template <class T>
+__device__ __forceinline__ T& at_bytes(T* row, uint32_t off)
+{
+    return *reinterpret_cast<T*>(reinterpret_cast<char*>(row) + off);
+}
+
 // XCD-aware tile order: workgroups are dealt round-robin to the 8 XCDs, so give each XCD a
 // contiguous run of tile indices (neighbouring tiles share operand rows in that XCD's L2).
 __device__ __forceinline__ int xcd_tile_index(int wid, int nwg)

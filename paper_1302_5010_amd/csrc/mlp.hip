@@ -36,95 +36,137 @@ __device__ inline float gelu_prime_f(float u)
 }
 
 // ---------------------------------------------------------------------------
-// Epilogues of C = X W^T: called once per output element (row r of X, row c of W).
+// Epilogues of C = X W^T, called once per 32 x 32 block of a wave: column c = c0 + l32 (a column below N), rows
+// r0 + 4 h + 8 (r / 4) + r % 4 for r < 16 with values v[r], rows below M stored (all of them when FULL).  r0 and c0
+// are the same in every lane, so a row's address is scalar arithmetic and a lane's part of it one 32-bit offset.
+// What a column shares (col: the bias) is loaded before the tile's first store and what a block needs from memory
+// (U) before the block's: a load behind a store waits until the store has been acknowledged, and the compiler has to
+// assume that a store changes what is loaded, so the bias read at each element cost 128 such waits per tile (scores
+// of 4096 signals, 2048 -> 20000: 446 -> 352 us with the loop of mfma_tile_loop_pipe, of which 15 are the loop's).
 // ---------------------------------------------------------------------------
+template <class T>
+__device__ __forceinline__ T* epi_row(T* base, int64_t ld, int r0, int c0, int r)
+{
+    return base + (int64_t)(r0 + 8 * (r >> 2) + (r & 3)) * ld + c0;
+}
+template <bool BIAS>
 struct EpiStore {            // C[r][c] = v (+ bias[c])
+    static constexpr bool TILE256 = true;
     float* C; int64_t ldc; const float* bias;
-    __device__ void operator()(int r, int c, float v) const
+    __device__ __forceinline__ float col(int c) const { return BIAS ? bias[c] : 0.f; }
+    template <bool FULL>
+    __device__ __forceinline__ void block(const floatx16& v, float b, int r0, int c0, int h, int l32, int M) const
     {
-        C[(int64_t)r * ldc + c] = bias ? v + bias[c] : v;
+        const uint32_t off = 4u * (uint32_t)(4 * h * (int)ldc + l32);
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (FULL || r0 + 4 * h + 8 * (r >> 2) + (r & 3) < M)
+                at_bytes(epi_row(C, ldc, r0, c0, r), off) = BIAS ? v[r] + b : v[r];
     }
 };
 struct EpiBiasGelu {         // u = v + bias[c]; U[r][c] = u (if kept); H[r][c] = bf16(gelu(u))
+    static constexpr bool TILE256 = true;
     const float* bias; float* U; int64_t ldu; uint16_t* H; int64_t ldh;
-    __device__ void operator()(int r, int c, float v) const
+    __device__ __forceinline__ float col(int c) const { return bias[c]; }
+    template <bool FULL>
+    __device__ __forceinline__ void block(const floatx16& v, float b, int r0, int c0, int h, int l32, int M) const
     {
-        const float u = v + bias[c];
-        if (U) U[(int64_t)r * ldu + c] = u;
-        H[(int64_t)r * ldh + c] = bf16_round(gelu_f(u));
+        const uint32_t offu = 4u * (uint32_t)(4 * h * (int)ldu + l32), offh = 2u * (uint32_t)(4 * h * (int)ldh + l32);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            if (!FULL && r0 + 4 * h + 8 * (r >> 2) + (r & 3) >= M) continue;
+            const float u = v[r] + b;
+            if (U) at_bytes(epi_row(U, ldu, r0, c0, r), offu) = u;
+            at_bytes(epi_row(H, ldh, r0, c0, r), offh) = bf16_round(gelu_f(u));
+        }
     }
 };
 struct EpiGeluBack {         // d = v * gelu'(U[r][c]); D[r][c] = d; D16[r][c] = bf16(d)
+    static constexpr bool TILE256 = false;   // its loads on top of 128 x 64 per wave would spill
     const float* U; int64_t ldu; float* D; int64_t ldd; uint16_t* D16; int64_t ld16;
-    __device__ void operator()(int r, int c, float v) const
+    __device__ __forceinline__ float col(int) const { return 0.f; }
+    template <bool FULL>
+    __device__ __forceinline__ void block(const floatx16& v, float, int r0, int c0, int h, int l32, int M) const
     {
-        const float d = v * gelu_prime_f(U[(int64_t)r * ldu + c]);
-        D[(int64_t)r * ldd + c] = d;
-        D16[(int64_t)r * ld16 + c] = bf16_round(d);
+        const uint32_t offd = 4u * (uint32_t)(4 * h * (int)ldd + l32), off16 = 2u * (uint32_t)(4 * h * (int)ld16 + l32);
+        float u[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int row = r0 + 4 * h + 8 * (r >> 2) + (r & 3);
+            u[r] = U[(int64_t)(FULL || row < M ? row : M - 1) * ldu + c0 + l32];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            if (!FULL && r0 + 4 * h + 8 * (r >> 2) + (r & 3) >= M) continue;
+            const float d = v[r] * gelu_prime_f(u[r]);
+            at_bytes(epi_row(D, ldd, r0, c0, r), offd) = d;
+            at_bytes(epi_row(D16, ld16, r0, c0, r), off16) = bf16_round(d);
+        }
     }
 };
 
 // C[r][c] = sum_k X[r][k] W[c][k] for r < M, c < N; kpad % 64 == 0 and both operands hold
 // zeros in columns past the true contraction length.  Rows past M (N) re-read row M-1 (N-1);
 // their results are never stored.
-template <int BM, int BN, int WM, int WN, class Epi>
+template <int BM, int BN, int WM, int WN, int NBUF, class Epi>
 __global__ __launch_bounds__((TileShape<BM, BN, WM, WN>::THREADS)) void mlp_gemm_kernel(
     const __bf16* __restrict__ X, int64_t ldx, int M, const __bf16* __restrict__ W, int64_t ldw, int N, int kpad,
     int tiles_m, int tiles_n, Epi epi)
 {
     using S = TileShape<BM, BN, WM, WN>;
+    using D = DmaShape<BM, BN, WM, WN>;
     const int tile = xcd_tile_index(blockIdx.x, gridDim.x);
     int tm, tn;                              // grouped order: an XCD's concurrent tiles share X and W rows
     grouped_tile<8>(tile, tiles_m, tiles_n, tm, tn);
     if (tn >= tiles_n) return;
     const int row0 = tm * BM, col0 = tn * BN;
 
-    __shared__ __attribute__((aligned(16))) TileLds<BM, BN> lds;
+    __shared__ __attribute__((aligned(1024))) PipeLds<BM, BN, NBUF> lds;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    const int c4 = tile_c4(tid);
-    const int r0 = tile_r0(tid);
-    int64_t oX[S::LX], oW[S::LW];
+    int64_t oX[D::GX], oW[D::GW];
 #pragma unroll
-    for (int q = 0; q < S::LX; ++q) {
-        const int r = row0 + r0 + S::RSTEP * q;
-        oX[q] = (int64_t)(r < M ? r : M - 1) * ldx + 8 * c4;
+    for (int i = 0; i < D::GX; ++i) {
+        const int g = wave + S::WAVES * i;
+        const int r = row0 + dma_row(g, lane);
+        oX[i] = (int64_t)(r < M ? r : M - 1) * ldx + 8 * dma_chunk(g, lane);
     }
 #pragma unroll
-    for (int q = 0; q < S::LW; ++q) {
-        const int c = col0 + r0 + S::RSTEP * q;
-        oW[q] = (int64_t)(c < N ? c : N - 1) * ldw + 8 * c4;
+    for (int i = 0; i < D::GW; ++i) {
+        const int g = wave + S::WAVES * i;
+        const int c = col0 + dma_row(g, lane);
+        oW[i] = (int64_t)(c < N ? c : N - 1) * ldw + 8 * dma_chunk(g, lane);
     }
     const int ws = (wave % S::WAVES_M) * WM;
     const int wa = (wave / S::WAVES_M) * WN;
     floatx16 acc[S::TI][S::TJ];
-    mfma_tile_loop<__bf16, BM, BN, WM, WN>(X, oX, W, oW, kpad, lds, ws, wa, acc);
+    mfma_tile_loop_pipe<BM, BN, WM, WN, NBUF>(X, oX, W, oW, kpad, lds, ws, wa, acc);
 
     const int l32 = lane & 31;
     const int h = lane >> 5;
+    const int r0 = __builtin_amdgcn_readfirstlane(row0 + ws), c0 = __builtin_amdgcn_readfirstlane(col0 + wa);
+    float cv[S::TJ];
+#pragma unroll
+    for (int j = 0; j < S::TJ; ++j) cv[j] = epi.col(c0 + 32 * j + l32 < N ? c0 + 32 * j + l32 : N - 1);
 #pragma unroll
     for (int i = 0; i < S::TI; ++i)
 #pragma unroll
         for (int j = 0; j < S::TJ; ++j) {
-            const int c = col0 + wa + 32 * j + l32;
-            if (c >= N) continue;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = row0 + ws + 32 * i + 8 * (r >> 2) + 4 * h + (r & 3);
-                if (row < M) epi(row, c, acc[i][j][r]);
-            }
+            if (c0 + 32 * j + l32 >= N) continue;
+            if (r0 + 32 * i + 32 <= M) epi.template block<true>(acc[i][j], cv[j], r0 + 32 * i, c0 + 32 * j, h, l32, M);
+            else epi.template block<false>(acc[i][j], cv[j], r0 + 32 * i, c0 + 32 * j, h, l32, M);
         }
 }
 
-template <int BM, int BN, int WM, int WN, class Epi>
+template <int BM, int BN, int WM, int WN, int NBUF, class Epi>
 hipError_t launch_gemm_shape(const uint16_t* X, int64_t ldx, int M, const uint16_t* W, int64_t ldw, int N, int kpad,
                              const Epi& epi, hipStream_t s)
 {
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int64_t nwg = (int64_t)tiles_m * tiles_n;
     if (nwg > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((mlp_gemm_kernel<BM, BN, WM, WN, Epi>), dim3((unsigned)nwg),
+    hipLaunchKernelGGL((mlp_gemm_kernel<BM, BN, WM, WN, NBUF, Epi>), dim3((unsigned)nwg),
                        dim3(TileShape<BM, BN, WM, WN>::THREADS), 0, s, reinterpret_cast<const __bf16*>(X), ldx, M,
                        reinterpret_cast<const __bf16*>(W), ldw, N, kpad, tiles_m, tiles_n, epi);
     return hipGetLastError();
@@ -135,14 +177,22 @@ hipError_t launch_gemm(const uint16_t* X, int64_t ldx, int M, const uint16_t* W,
                        const Epi& epi, hipStream_t s)
 {
     if (M <= 0 || N <= 0) return hipSuccess;
-    if (kpad <= 0 || kpad % 64 || ldx % 8 || ldw % 8 || ldx < kpad || ldw < kpad) return hipErrorInvalidValue;
+    if (kpad <= 0 || kpad % 64 || ldx % 8 || ldw % 8 || ldx < kpad || ldw < kpad ||
+        (reinterpret_cast<uintptr_t>(X) & 15) || (reinterpret_cast<uintptr_t>(W) & 15) || N > (1 << 26))
+        return hipErrorInvalidValue;
     // very large outputs (four or more rounds of 256 x 256 tiles on 256 CUs): eight 128 x 64 waves per
-    // tile; large ones: 128 x 128 tiles of four 64 x 64 waves; small ones: 64 x 64 tiles of 32 x 32 waves
-    if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) >= 1024)
-        return launch_gemm_shape<256, 256, 128, 64>(X, ldx, M, W, ldw, N, kpad, epi, s);
-    if ((int64_t)((M + 127) / 128) * ((N + 127) / 128) >= 512)
-        return launch_gemm_shape<128, 128, 64, 64>(X, ldx, M, W, ldw, N, kpad, epi, s);
-    return launch_gemm_shape<64, 64, 32, 32>(X, ldx, M, W, ldw, N, kpad, epi, s);
+    // tile; large ones (two or more 128 x 128 tiles per CU): four 64 x 64 waves; below that 64 x 128 tiles of eight
+    // 32 x 32 waves while they still give every CU one, else 64 x 64 tiles of four (512 x 2048 x 2048: 11.3 us against
+    // 13.7; 1024 x 2048 x 20032: 64 x 128 128 us, 64 x 64 125, at 2048 x 2048 x 1024 15.5 against 17.9)
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    if constexpr (Epi::TILE256)
+        if (tiles(256, 256) >= 1024)
+            return launch_gemm_shape<256, 256, 128, 64, 2>(X, ldx, M, W, ldw, N, kpad, epi, s);
+    if (tiles(128, 128) >= 512)
+        return launch_gemm_shape<128, 128, 64, 64, 2>(X, ldx, M, W, ldw, N, kpad, epi, s);
+    if (tiles(64, 128) >= 256)
+        return launch_gemm_shape<64, 128, 32, 32, 3>(X, ldx, M, W, ldw, N, kpad, epi, s);
+    return launch_gemm_shape<64, 64, 32, 32, 3>(X, ldx, M, W, ldw, N, kpad, epi, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -692,7 +742,8 @@ hipError_t mlp_signals_bf16(const float* B, int64_t ldb, int n, int p, uint16_t*
 hipError_t mlp_gemm_store(const uint16_t* X, int64_t ldx, int M, const uint16_t* W, int64_t ldw, int N, int kpad,
                           float* C, int64_t ldc, const float* bias, hipStream_t s)
 {
-    return launch_gemm(X, ldx, M, W, ldw, N, kpad, EpiStore{C, ldc, bias}, s);
+    if (bias) return launch_gemm(X, ldx, M, W, ldw, N, kpad, EpiStore<true>{C, ldc, bias}, s);
+    return launch_gemm(X, ldx, M, W, ldw, N, kpad, EpiStore<false>{C, ldc, nullptr}, s);
 }
 
 hipError_t mlp_gemm_bias_gelu(const uint16_t* X, int64_t ldx, int M, const uint16_t* W, int64_t ldw, int N, int kpad,

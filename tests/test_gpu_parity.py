@@ -970,3 +970,19 @@ def test_correlate_staging(screen, n, p):
     exact = R.double() @ At.double().T
     assert bool(((G.double() - exact).abs() <= tol * R.double().norm(dim=1, keepdim=True)).all())
     s.close()
+
+
+@pytest.mark.parametrize("screen", ["fp32", "bf16", "fp8"])
+@pytest.mark.parametrize("n,m,p", [(40, 300, 1), (64, 511, 300), (130, 257, 70), (200, 33, 513)])
+def test_correlation_shapes_at_their_edges(screen, n, m, p):
+    """Every tile shape on one to four slices of k, ragged tiles of both operands and full ones: the same bits as
+    shape 0 (all shapes sum k in the same order)."""
+    pk = _lib()
+    s = pk.Solver(to_dev(bi.gaussian_dictionary(n, m, 42)), 0.1, screen=screen)
+    R = torch.randn(p, n, generator=torch.Generator().manual_seed(p)).cuda()
+    s.set_tuning([0, 0, 0])
+    ref = s.correlate(R)
+    for v in [1, 2, 3, 4, 5, 6, 7] + ([8, 9, 10] if screen == "bf16" else []) + [11, 12, 13, 14]:
+        s.set_tuning([v, v, v])
+        assert torch.equal(s.correlate(R), ref), v
+    s.close()
