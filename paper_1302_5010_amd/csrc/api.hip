@@ -1289,9 +1289,14 @@ bmpl_status bmpl_autotune(bmpl_ctx* c, int32_t p, int32_t* shapes, double* ms, v
     bmpl_status st = ensure_workspace(c, std::max(p, c->p_cap), std::max(c->selcap, rho));
     if (st != BMPL_OK) return st;
     Workspace& w = c->w;
-    HIPC(hipMemsetAsync(w.R, 0, (size_t)p * c->kpad * sizeof(float), s));
-    if (w.R16) HIPC(hipMemsetAsync(w.R16, 0, (size_t)p * c->kpad * sizeof(uint16_t), s));
-    if (w.R8) HIPC(hipMemsetAsync(w.R8, 0, (size_t)p * c->kpad, s));
+    // the dictionary's own rows stand in for residuals: the shapes have to be timed on values that switch the matrix
+    // cores as real ones do (on zeros the clocks stay up and another shape can win than on data)
+    for (int r0 = 0; r0 < p; r0 += c->m) {
+        const size_t at = (size_t)r0 * c->kpad, cnt = (size_t)std::min(c->m, p - r0) * c->kpad;
+        HIPC(hipMemcpyAsync(w.R + at, c->At, cnt * sizeof(float), hipMemcpyDeviceToDevice, s));
+        if (w.R16) HIPC(hipMemcpyAsync(w.R16 + at, c->A16, cnt * sizeof(uint16_t), hipMemcpyDeviceToDevice, s));
+        if (w.R8) HIPC(hipMemcpyAsync(w.R8 + at, c->A8, cnt, hipMemcpyDeviceToDevice, s));
+    }
     if (w.rscale8) {
         std::vector<float> ones(p, 1.0f);
         HIPC(hipMemcpyAsync(w.rscale8, ones.data(), sizeof(float) * p, hipMemcpyHostToDevice, s));
