@@ -17,6 +17,7 @@
 #include <float.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "bmpl_internal.h"
 #include "gemm_tile.h"
@@ -515,12 +516,14 @@ __global__ __launch_bounds__(256) void params_bf16_kernel(const float* __restric
 //   1. Each thread keeps the two largest order keys of its entries; the k-th largest of
 //      those 512 keys, T, is at most the row's k-th largest key (they are distinct
 //      entries of the row), so every entry of the top k has a key >= T.
-//   2. Each wave compacts, in index order, the entries of its quarter of the row with a
-//      key >= T (typically a few hundred in all) into LDS as (key, index) pairs.
-//   3. A bitonic sort orders the candidates by key, then lower index; the first k are
-//      the answer, whose indices a second bitonic sort puts in ascending order.
-// If a quarter holds more candidates than its LDS share (many equal keys), the row is
-// done by an exact radix select over the keys in global memory instead.
+//   2. The entries with a key >= T (typically a few hundred) are appended to an LDS list.
+//   3. A radix select over the list finds the k-th largest key; the entries above it and the lowest-indexed
+//      ones equal to it are the answer, each placed by counting the answer's entries below it.
+// If more entries pass than the list holds (many equal keys), the row is done by an exact radix select over the
+// keys in global memory instead.
+// With 16-byte rows the whole row stays in registers between steps 1 and 2 (NQ float4 per thread, all loads in flight
+// at once), so it is read once; the k-th of a list costs 4 digit passes of three barriers where a bitonic sort took 36
+// to 66 steps of one.  4096 rows of 20000, k = 64: 161 -> 73 us (328 MB: 4.5 TB/s), k = 256: 165 -> 91 us.
 // ---------------------------------------------------------------------------
 __device__ inline uint32_t order_key(float x)
 {
@@ -544,134 +547,83 @@ __device__ inline int block_excl_count(bool flag, int* s_wave, int& total)
     return before + within;
 }
 
-// In-place bitonic sort of N (a power of two) LDS elements by 256 threads, descending or ascending.
-template <class T, int N, bool DESC>
-__device__ inline void bitonic_sort(T* v)
+constexpr int TOPK_CAP = 1024;   // list entries per row
+
+struct TopkLds {
+    uint32_t key[TOPK_CAP];
+    int idx[TOPK_CAP];
+    uint32_t t[512];
+    int hist[256];
+    int sel[256];
+    int wave[4];
+    int n, digit, need, ties;
+};
+
+// The k-th largest of key[0 .. n) (1 <= k <= n) by 8-bit digits from the top; `need` receives how many entries equal to
+// it belong to the k largest, `ties` how many there are.  Called by the whole workgroup (256 threads).
+__device__ inline uint32_t radix_kth(const uint32_t* key, int n, int k, TopkLds& s, int& need, int& ties)
 {
-    for (int size = 2; size <= N; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int t = threadIdx.x; t < N / 2; t += 256) {
-                const int i = ((t & ~(stride - 1)) << 1) | (t & (stride - 1));   // stride is a power of two
-                const int j = i + stride;
-                const bool first_up = ((i & size) == 0) == DESC;   // this block ends in the final order
-                const T x = v[i], y = v[j];
-                if (first_up ? (x < y) : (x > y)) { v[i] = y; v[j] = x; }
+    const int tid = threadIdx.x;
+    uint32_t prefix = 0u, mask = 0u;
+    need = k;
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        s.hist[tid] = 0;
+        __syncthreads();
+        for (int e0 = 0; e0 < n; e0 += 256) {
+            const int e = e0 + tid;
+            const uint32_t u = e < n ? key[e] : 0u;
+            bool left = e < n && (u & mask) == prefix;
+            const uint32_t d = (u >> shift) & 255u;
+            if (shift == 24) {
+                // sign and exponent: a few distinct values, so one addition per value and wave
+                unsigned long long rest = __ballot(left);
+                while (rest) {
+                    const uint32_t d0 = __shfl(d, __ffsll((long long)rest) - 1);
+                    const unsigned long long same = __ballot(left && d == d0);
+                    if ((tid & 63) == 0) atomicAdd(&s.hist[d0], __popcll(same));
+                    left = left && d != d0;
+                    rest &= ~same;
+                }
+            } else if (left) {
+                atomicAdd(&s.hist[d], 1);
             }
-            __syncthreads();
         }
+        __syncthreads();
+        if (tid < 64) {
+            // lane l owns digits 255 - 4 l .. 252 - 4 l, so the lanes before it hold the larger ones
+            const int4 hv = *reinterpret_cast<const int4*>(&s.hist[252 - 4 * tid]);
+            const int c[4] = {hv.w, hv.z, hv.y, hv.x};
+            const int own = c[0] + c[1] + c[2] + c[3];
+            int incl = own;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int v = __shfl_up(incl, o);
+                incl += tid >= o ? v : 0;
+            }
+            int above = incl - own;
+            if (above < need && need <= incl) {      // exactly one lane
+                int q = 0, cq = c[0];
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (q == e && above + c[e] < need) { above += c[e]; q = e + 1; cq = c[e + 1]; }
+                s.digit = 255 - 4 * tid - q;
+                s.need = need - above;
+                s.ties = cq;
+            }
+        }
+        __syncthreads();
+        prefix |= (uint32_t)s.digit << shift;
+        mask |= 0xFFu << shift;
+        need = s.need;
+        ties = s.ties;
     }
+    return prefix;
 }
 
-constexpr int TOPK_CAP = 2048;   // candidates per row in LDS, a quarter per wave
-
-__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ S, int64_t lds, int L, int k,
-                                                   int* __restrict__ out, int64_t ldo)
+// The exact radix select of a row over its keys in global memory.
+__device__ void topk_sweeps(const float* s, int L, int k, int kk, int* o, int* hist, int* s_wave, int& s_digit, int& s_need)
 {
-    __shared__ uint32_t s_t[512];
-    __shared__ uint64_t s_c[TOPK_CAP];
-    __shared__ int s_sel[256];
-    __shared__ int s_over;
-    __shared__ int hist[256];
-    __shared__ int s_digit, s_need;
-    __shared__ int s_wave[4];
-    const int row = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float* s = S + (int64_t)row * lds;
-    int* o = out + (int64_t)row * ldo;
-    const int kk = k < L ? k : L;
-
-    // 1. per-thread two largest keys, then their kk-th largest over the workgroup.  A thread's eight loads
-    //    are unconditional whenever every thread's lie inside the row (a guarded load compiles to a branch
-    //    that waits for its data, so the loads would run one after another).
-    uint32_t t1 = 0u, t2 = 0u;
-    for (int j0 = tid; j0 < L; j0 += 256 * 8) {
-        uint32_t key[8];
-        if (j0 - tid + 256 * 8 <= L) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) key[e] = order_key(s[j0 + 256 * e]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int j = j0 + 256 * e;
-                key[e] = j < L ? order_key(s[j]) : 0u;
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const uint32_t u = key[e];
-            if (u > t1) { t2 = t1; t1 = u; } else if (u > t2) { t2 = u; }
-        }
-    }
-    s_t[2 * tid] = t1;
-    s_t[2 * tid + 1] = t2;
-    if (tid == 0) s_over = 0;
+    const int tid = threadIdx.x;
     __syncthreads();
-    bitonic_sort<uint32_t, 512, true>(s_t);
-    const uint32_t T = kk > 0 ? s_t[kk - 1] : 0xFFFFFFFFu;
-
-    // 2. per-wave ordered compaction of the keys >= T over the wave's quarter of the row
-    constexpr int CW = TOPK_CAP / 4;
-    const int q4 = (L + 3) / 4;
-    const int lo = wave * q4, hi = lo + q4 < L ? lo + q4 : L;
-    int cnt = 0;
-    uint64_t* mine = s_c + wave * CW;
-    for (int b0 = lo; b0 < hi; b0 += 64 * 4) {
-        uint32_t key[4];
-        if (b0 + 64 * 4 <= hi) {   // the whole step inside the quarter (the same for the whole wave)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) key[e] = order_key(s[b0 + 64 * e + lane]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int j = b0 + 64 * e + lane;
-                key[e] = j < hi ? order_key(s[j]) : 0u;
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int j = b0 + 64 * e + lane;
-            const bool take = j < hi && key[e] >= T && kk > 0;
-            const uint64_t bal = __ballot(take);
-            const int pos = cnt + __popcll(bal & ((1ull << lane) - 1ull));
-            if (take && pos < CW) mine[pos] = ((uint64_t)key[e] << 32) | (uint64_t)(~(uint32_t)j);
-            cnt += __popcll(bal);
-        }
-    }
-    if (cnt > CW && lane == 0) s_over = 1;
-    for (int q = cnt + lane; q < CW; q += 64) mine[q] = 0ull;   // below every real (key, index) pair
-    __syncthreads();
-
-    if (!s_over) {
-        // 3. gather the four quarters' candidates to the front (through registers: the moves overlap),
-        //    order them, take the first kk, list their indices ascending
-        if (lane == 0) s_wave[wave] = cnt;
-        __syncthreads();
-        const int off = (wave > 0 ? s_wave[0] : 0) + (wave > 1 ? s_wave[1] : 0) + (wave > 2 ? s_wave[2] : 0);
-        const int c = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
-        uint64_t mv[CW / 64];
-#pragma unroll
-        for (int q = 0; q < CW / 64; ++q) mv[q] = mine[lane + 64 * q];
-        __syncthreads();
-        int N = 256;
-        while (N < c) N <<= 1;
-#pragma unroll
-        for (int q = 0; q < CW / 64; ++q) {
-            const int e = lane + 64 * q;
-            if (e < cnt) s_c[off + e] = mv[q];
-        }
-        for (int e = c + tid; e < N; e += 256) s_c[e] = 0ull;
-        __syncthreads();
-        if (N == 256) bitonic_sort<uint64_t, 256, true>(s_c);
-        else if (N == 512) bitonic_sort<uint64_t, 512, true>(s_c);
-        else if (N == 1024) bitonic_sort<uint64_t, 1024, true>(s_c);
-        else bitonic_sort<uint64_t, TOPK_CAP, true>(s_c);
-        s_sel[tid] = tid < kk ? (int)(~(uint32_t)(s_c[tid] & 0xFFFFFFFFull)) : 0x7FFFFFFF;
-        __syncthreads();
-        bitonic_sort<int, 256, false>(s_sel);
-        if (tid < k) o[tid] = tid < kk ? s_sel[tid] : -1;
-        return;
-    }
-
     // Fallback: exact radix select over the keys in global memory.  Four 8-bit passes find the
     // kk-th largest key P and how many keys equal to P to take; a final pass compacts in index order.
     uint32_t prefix = 0u, mask = 0u;
@@ -717,6 +669,158 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ S, 
         base_out += tot_sel;
     }
     for (int q = base_out + tid; q < k; q += 256) o[q] = -1;
+}
+
+template <int NQ>   // 0: any row alignment and length, read twice
+__global__ __launch_bounds__(256, NQ > 20 ? 2 : 4) void topk_kernel(const float* __restrict__ S, int64_t lds, int L, int k,
+                                                                    int* __restrict__ out, int64_t ldo)
+{
+    __shared__ __attribute__((aligned(16))) TopkLds w;
+    const int row = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const float* s = S + (int64_t)row * lds;
+    int* o = out + (int64_t)row * ldo;
+    const int kk = k < L ? k : L;                  // >= 1
+
+    // 1. per-thread two largest values, then the kk-th largest over the workgroup.  With t1 >= t2 the median of t1, t2
+    //    and v is the new second largest; a NaN changes neither (the median instruction returns the least of the others)
+    float t1 = -INFINITY, t2 = -INFINITY;
+    auto top2 = [&](float v) {
+        t2 = __builtin_amdgcn_fmed3f(t1, t2, v);
+        t1 = fmaxf(t1, v);
+    };
+    constexpr int NR = NQ > 0 ? NQ : 1;
+    float4 f[NR];
+    if constexpr (NQ > 0) {
+        // chunks past the row read its last one (the row is padded to 16 bytes: lds % 4 == 0)
+        const int last = (L - 1) / 4;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int c = tid + 256 * q;
+            f[q] = reinterpret_cast<const float4*>(s)[c < last ? c : last];
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int j = 4 * (tid + 256 * q);
+            if (4 * 256 * (q + 1) > L) {           // the row's end (the same for the whole workgroup): NaN past it
+                f[q].x = j < L ? f[q].x : NAN;
+                f[q].y = j + 1 < L ? f[q].y : NAN;
+                f[q].z = j + 2 < L ? f[q].z : NAN;
+                f[q].w = j + 3 < L ? f[q].w : NAN;
+            }
+            top2(f[q].x);
+            top2(f[q].y);
+            top2(f[q].z);
+            top2(f[q].w);
+        }
+    } else {
+        for (int j0 = tid; j0 < L; j0 += 256 * 8) {   // eight loads in flight (clamped: no branch waits for them)
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = s[j0 + 256 * e < L ? j0 + 256 * e : L - 1];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) top2(j0 + 256 * e < L ? v[e] : NAN);
+        }
+    }
+    w.t[tid] = order_key(t1);
+    w.t[256 + tid] = order_key(t2);
+    if (tid == 0) w.n = 0;
+    __syncthreads();
+    int need, ties;
+    const uint32_t Tk = radix_kth(w.t, 512, kk, w, need, ties);
+    // the value of a key (of +0 for the zeros, which compare equal)
+    const float T = __uint_as_float((Tk & 0x80000000u) ? Tk & 0x7fffffffu : ~Tk);
+
+    // 2. the entries at or above T (never NaN) into the list, in any order
+    if constexpr (NQ > 0) {
+        // which of the thread's entries pass, as bits (straight-line code: appending at each of the 4 NQ places would be
+        // larger than the instruction cache); the few that do are read again
+        constexpr int NW = (NQ + 7) / 8;
+        uint32_t bits[NW];
+        int cnt = 0;
+#pragma unroll
+        for (int v = 0; v < NW; ++v) {
+            bits[v] = 0u;
+#pragma unroll
+            for (int q = 8 * v; q < NQ && q < 8 * v + 8; ++q) {
+                const int b = 4 * (q - 8 * v);
+                bits[v] |= (f[q].x >= T ? 1u << b : 0u) | (f[q].y >= T ? 2u << b : 0u) | (f[q].z >= T ? 4u << b : 0u) |
+                           (f[q].w >= T ? 8u << b : 0u);
+            }
+            cnt += __popc(bits[v]);
+        }
+        int incl = cnt;
+        for (int o2 = 1; o2 < 64; o2 <<= 1) {
+            const int v = __shfl_up(incl, o2);
+            incl += lane >= o2 ? v : 0;
+        }
+        int base = 0;
+        if (lane == 63) base = atomicAdd(&w.n, incl);
+        int pos = __shfl(base, 63) + incl - cnt;
+#pragma unroll
+        for (int v = 0; v < NW; ++v)
+            for (uint32_t m = bits[v]; m; m &= m - 1u) {
+                const int b = __ffs(m) - 1;
+                const int j = 4 * (tid + 256 * (8 * v + (b >> 2))) + (b & 3);
+                if (pos < TOPK_CAP) { w.key[pos] = order_key(s[j]); w.idx[pos] = j; }
+                ++pos;
+            }
+    } else {
+        for (int j0 = 0; j0 < L; j0 += 256 * 8) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = s[j0 + 256 * e + tid < L ? j0 + 256 * e + tid : L - 1];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int j = j0 + 256 * e + tid;
+                const bool t = j < L && v[e] >= T;
+                const unsigned long long bal = __ballot(t);
+                if (!bal) continue;
+                int base = 0;
+                if (lane == 0) base = atomicAdd(&w.n, __popcll(bal));
+                base = __builtin_amdgcn_readfirstlane(base);
+                const int pos = base + __popcll(bal & ((1ull << lane) - 1ull));
+                if (t && pos < TOPK_CAP) { w.key[pos] = order_key(v[e]); w.idx[pos] = j; }
+            }
+        }
+    }
+    __syncthreads();
+    const int n = w.n;
+    if (n > TOPK_CAP || n < kk) {                  // many equal values, or fewer than kk that are not NaN
+        topk_sweeps(s, L, k, kk, o, w.hist, w.wave, w.digit, w.need);
+        return;
+    }
+    // 3. the kk-th largest key P of the list (n >= kk: T is a lower bound); entries above P are in, and the `need`
+    //    lowest-indexed of the entries equal to it
+    const uint32_t P = radix_kth(w.key, n, kk, w, need, ties);
+    if (tid == 0) w.n = 0;
+    __syncthreads();
+    for (int e0 = 0; e0 < n; e0 += 256) {          // the same number of steps in every lane
+        const int e = e0 + tid;
+        const uint32_t u = e < n ? w.key[e] : 0u;
+        const int j = e < n ? w.idx[e] : 0;
+        bool in = e < n && u > P;
+        if (e < n && u == P) {
+            int before = 0;
+            if (ties > need)
+                for (int d = 0; d < n; ++d) before += w.key[d] == P && w.idx[d] < j;
+            in = before < need;
+        }
+        const unsigned long long bal = __ballot(in);
+        int base = 0;
+        if (lane == 0 && bal) base = atomicAdd(&w.n, __popcll(bal));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (in) w.sel[base + __popcll(bal & ((1ull << lane) - 1ull))] = j;
+    }
+    __syncthreads();
+    if (tid < kk) {
+        const int j = w.sel[tid];
+        int rank = 0;
+        for (int d = 0; d < kk; ++d) rank += w.sel[d] < j;
+        o[rank] = j;
+    } else if (tid < k) {
+        o[tid] = -1;
+    }
 }
 
 }  // namespace
@@ -840,7 +944,15 @@ hipError_t mlp_topk(const float* S, int64_t lds, int rows, int L, int k, int* ou
     if (rows <= 0) return hipSuccess;
     if (k < 1 || k > 256 || L < 1 || ldo < k) return hipErrorInvalidValue;
     if ((size_t)L * 4 > TOPK_MAX_LDS) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(topk_kernel, dim3(rows), dim3(256), 0, s, S, lds, L, k, out, ldo);
+    // rows on 16-byte boundaries stay in registers: 4, 8, 20 or 38 float4 per thread by the row's length
+    auto launch = [&](auto nq) {
+        hipLaunchKernelGGL(topk_kernel<decltype(nq)::value>, dim3(rows), dim3(256), 0, s, S, lds, L, k, out, ldo);
+    };
+    if (lds % 4 || (reinterpret_cast<uintptr_t>(S) & 15)) launch(std::integral_constant<int, 0>());
+    else if (L <= 4096) launch(std::integral_constant<int, 4>());
+    else if (L <= 8192) launch(std::integral_constant<int, 8>());
+    else if (L <= 20480) launch(std::integral_constant<int, 20>());
+    else launch(std::integral_constant<int, 38>());
     return hipGetLastError();
 }
 

@@ -333,3 +333,27 @@ def test_loss_and_gradient_at_tile_edges(p, m):
     gb, rb = mo.unpack(g.cpu().numpy().astype(np.float64), d, h, m), mo.unpack(g_r, d, h, m)
     for name in ("W1", "b1", "W2", "b2", "W3", "b3"):
         assert rel(gb[name], rb[name]) <= 16 * U, (name, rel(gb[name], rb[name]))
+
+
+@pytest.mark.parametrize("L,lds,k", [(1, 4, 3), (4095, 4096, 64), (4097, 4100, 256), (8192, 8192, 32), (8193, 8196, 100),
+                                     (20480, 20480, 256), (20481, 20484, 64), (513, 513, 256), (2049, 2051, 17)])
+def test_topk_row_lengths_and_strides(L, lds, k):
+    """The top-k kernel's forms by row length (in registers up to 4096, 8192, 20480 and 38912 entries; unaligned rows
+    read twice), with values past the row that must not be seen, ties, infinities, and rows of NaN or of fewer than k
+    numbers; compared exactly."""
+    pk = _lib()
+    rng = np.random.default_rng(L)
+    S = rng.standard_normal((6, lds)).astype(np.float32)
+    S[:, L:] = 1e30                                  # not part of the rows
+    S[1, :L] = np.round(S[1, :L], 1)                 # ties
+    S[2, :L] = np.nan
+    S[3, :L] = np.nan
+    S[3, : L // 3] = -5.0                            # equal numbers, fewer than k of them for short rows
+    S[4, :L:3] = np.inf
+    S[4, 1:L:3] = -np.inf
+    S[5, :L] = -np.inf
+    got = pk.topk(to_dev(S), k, L=L).cpu().numpy()
+    kk = min(k, L)
+    ref = mo.propose(S[:, :L].astype(np.float64), kk)
+    np.testing.assert_array_equal(got[:, :kk], ref)
+    assert np.all(got[:, kk:] == -1)
