@@ -986,3 +986,43 @@ def test_correlation_shapes_at_their_edges(screen, n, m, p):
         s.set_tuning([v, v, v])
         assert torch.equal(s.correlate(R), ref), v
     s.close()
+
+
+@pytest.mark.parametrize("n,m,p,k,classes", [(5, 40, 3, 0, 4), (63, 90, 7, 5, 90), (1030, 700, 20, 600, 2),
+                                             (130, 256, 2050, 9, 11), (1024, 1200, 2048, 3, 1)])
+def test_classification_kernel_forms(n, m, p, k, classes):
+    """Class residuals of hand-made codes against the float64 reference: empty supports, one class per atom, a class
+    of more atoms than the kernel lists at once, one and four waves per signal, rows that are no multiple of 16
+    bytes, entries outside [0, m).  Float64 sums of at most n + k terms: 1e-12 relative."""
+    from oracle import src_oracle
+    pk = _lib()
+    rng = np.random.default_rng(n + p)
+    At = bi.gaussian_dictionary(n, m, 43)
+    cls = rng.integers(0, classes, m).astype(np.int32)
+    Bt = rng.standard_normal((p, n)).astype(np.float32)
+    ld = k + 3
+    idx = np.full((p, ld), -1, dtype=np.int32)
+    val = np.zeros((p, ld), dtype=np.float32)
+    lens = np.full(p, k, dtype=np.int32)
+    for i in range(p):
+        idx[i, :k] = np.sort(rng.choice(m, k, replace=False))
+        val[i, :k] = rng.standard_normal(k) / max(1.0, k ** 0.5)
+        if i % 5 == 1 and k:
+            idx[i, 0] = m + 7                     # not an atom: ignored
+        if i % 7 == 2:
+            lens[i] = 0
+    rows = list(range(p)) if p < 100 else list(range(0, p, 97)) + [p - 1]
+    X = np.zeros((len(rows), m))
+    for q, i in enumerate(rows):
+        for s in range(lens[i]):
+            if 0 <= idx[i, s] < m:
+                X[q, idx[i, s]] = val[i, s]
+    s = pk.Solver(to_dev(At), 0.1, gram_table=False)
+    code = {"x_idx": to_dev(idx), "x_val": to_dev(val), "supp_len": to_dev(lens)}
+    labels, resid = s.classify(to_dev(Bt), code, to_dev(cls))
+    labels, resid = labels.cpu().numpy()[rows], resid.cpu().numpy()[rows]
+    lab_ref, res_ref = src_oracle.classify(At, Bt[rows], X, cls)
+    np.testing.assert_array_equal(labels, lab_ref)
+    np.testing.assert_allclose(resid[lab_ref >= 0], res_ref[lab_ref >= 0], rtol=1e-12)
+    assert np.all(resid[lab_ref < 0] == 0.0)
+    s.close()
