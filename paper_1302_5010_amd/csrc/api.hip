@@ -17,6 +17,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/bmpl.h"
@@ -157,7 +158,8 @@ struct bmpl_ctx {
     int64_t ldg = 0;
     int* act[2] = {nullptr, nullptr};
     int* n_act_dev = nullptr;     // [2] running counts (inside the arena header)
-    int* h_count = nullptr;       // pinned host int
+    PassReport* h_report = nullptr;    // pinned [PASS_REPORTS]: the stop tests' reports, pass s in s % PASS_REPORTS
+    unsigned long long pass_seq = 0;   // passes numbered so far
 
     // correlation tile shape per running-signal bucket (>= 512, 64..511, < 64), set by bmpl_autotune
     int corr_shape[3] = {0, 3, 4};
@@ -443,6 +445,13 @@ bmpl_status ensure_workspace(bmpl_ctx* c, int p, int selcap)
     return BMPL_OK;
 }
 
+// Running signals up to which the host loop enqueues an iteration ahead of the count (the bucket of the product
+// for few signals, so an older count never picks another tile shape).  A few signals' iteration takes 45-75 us
+// on the GPU; waiting for its count and launching the next took 30 us more (16 signals of 128 x 512 with the
+// copy and the stream wait: 396 us per solve, 324 without; one signal of 1000 x 5001: 420 and 369).  With
+// hundreds of signals the older count's larger grids take back what the wait costs.
+constexpr int AHEAD_MAX = 64;
+constexpr unsigned PASS_REPORTS = 16;   // pinned reports in turn (two passes are unread at most)
 constexpr int GRAPH_DEPTH = 4;   // outer iterations per captured segment (even: act buffers return)
 constexpr size_t VEC_LDS_QUARTER = 38 * 1024;   // a quarter of a CU's 160 KB of LDS, less static LDS
 constexpr int FULL_DEPTH_MAX = 64;   // the most iterations captured as one graph for a whole solve
@@ -564,7 +573,10 @@ bmpl_status bmpl_create(const float* A_dev, int64_t lda, int32_t n, int32_t m, b
     c->w.m = m;
     c->w.words = (m + 31) / 32;
     e = pool_alloc(c, &c->At, (size_t)(m + 1) * c->kpad);   // row m stays zero
-    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->h_count), sizeof(int), hipHostMallocDefault);
+    if (e == hipSuccess) {
+        e = hipHostMalloc(reinterpret_cast<void**>(&c->h_report), PASS_REPORTS * sizeof(PassReport), hipHostMallocDefault);
+        if (e == hipSuccess) std::memset(c->h_report, 0, PASS_REPORTS * sizeof(PassReport));
+    }
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->h_arena), sizeof(Arena), hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->h_arena_rd), sizeof(Arena), hipHostMallocDefault);
     if (e == hipSuccess) e = dalloc(reinterpret_cast<char**>(&c->arena_dev), sizeof(Arena));
@@ -705,7 +717,7 @@ bmpl_status bmpl_destroy(bmpl_ctx* c)
     drop_graphs(c);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
-    if (c->h_count) (void)hipHostFree(c->h_count);
+    if (c->h_report) (void)hipHostFree(c->h_report);
     if (c->h_arena) {
         for (int k = 0; k < c->h_arena->nchunks; ++k) (void)hipFree(c->h_arena->base[k]);
         (void)hipHostFree(c->h_arena);
@@ -881,7 +893,9 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
     // Slot blocks for every signal up to the first host read-back: the first master problem (a
     // proposal's atoms or rho) and, in graph mode, the iterations of the first segment; in full depth,
     // the whole solve.
-    const int iters0 = (graph && !warm) ? 1 + GRAPH_DEPTH : 1;
+    const bool tm = timing_on(c);
+    auto ahead_of = [&](int n) { return !graph && !tm && n <= AHEAD_MAX; };
+    const int iters0 = (graph && !warm) ? 1 + GRAPH_DEPTH : (ahead_of(p) ? 2 : 1);
     st = arena_ensure(c, 0, (unsigned long long)p *
                                (full ? (unsigned long long)block_doubles(kfull, c->n)
                                      : block_reserve(0, 0, first_add, iters0, rho, slack, max_active, c->n)), s);
@@ -890,7 +904,6 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
     w.p = p;
 
     const bool rel = c->mode == BMPL_LAMBDA_REL_MAX_ATB && !lambda_dev;
-    const bool tm = timing_on(c);
     c->spans.clear();
     c->ev_used = 0;
     const bool phases = tm && (c->opt.flags & BMPL_FLAG_PHASES);
@@ -918,15 +931,9 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
     sa.grow_list = c->grow_list; sa.n_grow = c->n_grow; sa.grow_off = c->grow_off; sa.kmin = kfull;
     hipLaunchKernelGGL(status_compact_kernel, dim3(1), dim3(1024), 0, s, sa);
     HIPC(hipGetLastError());
-    // In graph mode the host does not wait for the running count until the first captured segment has
-    // been launched: every kernel reads the count on the device, p bounds it, and the GPU runs set-up,
-    // the first pass and the first segment back to back.
+    // The host does not wait for the running count before the first pass (in graph mode: until the first
+    // captured segment has been launched): every kernel reads the count on the device, and p bounds it.
     int n_act = p;
-    if (!graph) {
-        HIPC(hipMemcpyAsync(c->h_count, c->n_act_dev, sizeof(int), hipMemcpyDeviceToHost, s));
-        HIPC(hipStreamSynchronize(s));
-        n_act = *c->h_count;
-    }
     if (tm) span(c, ev_first, mark(c, s), K_OTHER);
 
     bool merge_mid = false;   // graph segments: see the gated product below
@@ -1092,6 +1099,11 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         sb.act_in = c->act[cur]; sb.n_in_dev = c->n_act_dev + cur; sb.n_in = n_grid;
         sb.act_out = c->act[nxt]; sb.n_out_dev = c->n_act_dev + nxt;
         sb.warm_check = warm_check ? 1 : 0;
+        if (!gated && !graph) {
+            const unsigned long long seq = ++c->pass_seq;
+            sb.reserve_iters = ahead_of(n_act) ? 2 : 1;
+            sb.report = &c->h_report[seq % PASS_REPORTS]; sb.seq = seq;
+        }
         hipLaunchKernelGGL(status_compact_kernel, dim3(1), dim3(1024), 0, q, sb);
         HIPC(hipGetLastError());
         if (ev) span(c, e0, mark(c, q), K_OTHER);
@@ -1164,17 +1176,36 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         return arena_ensure(c, R.top, R.reserve, s);
     };
 
+    // The report of pass `seq`, polled in pinned memory (the stream is asked now and then, so an error of
+    // the device, or a stream that has ended without the report, ends the wait).
+    auto wait_report = [&](unsigned long long seq) -> bmpl_status {
+        const PassReport& r = c->h_report[seq % PASS_REPORTS];
+        for (unsigned spin = 1;; ++spin) {
+            if (__atomic_load_n(&r.seq, __ATOMIC_ACQUIRE) == seq) return BMPL_OK;
+            if (spin % 4096 == 0) {
+                const hipError_t q = hipStreamQuery(s);
+                if (q == hipSuccess) {
+                    if (__atomic_load_n(&r.seq, __ATOMIC_ACQUIRE) == seq) return BMPL_OK;
+                    return fail(BMPL_E_HIP, "bmpl_solve: a pass ended without its report");
+                }
+                if (q != hipErrorNotReady) HIPC(q);
+                (void)hipGetLastError();   // "not ready" is no error of the next launch
+                std::this_thread::yield();
+            } else {
+                __builtin_ia32_pause();
+            }
+        }
+    };
+
     // Iteration 0: lambda rule and the first selection (or the warm-start proposal).
     int cur = 0;
-    if (n_act > 0) {
-        c->timing.outer_iters += tm ? 1 : 0;
-        st = enqueue_select_pass(s, 0, n_act, true, false, false);
+    c->timing.outer_iters += tm ? 1 : 0;
+    st = enqueue_select_pass(s, 0, n_act, true, false, false);
+    if (st != BMPL_OK) return st;
+    cur = 1;
+    if (graph && warm && !full) {
+        st = read_count(cur);
         if (st != BMPL_OK) return st;
-        cur = 1;
-        if (!graph || (warm && !full)) {
-            st = read_count(cur);
-            if (st != BMPL_OK) return st;
-        }
     }
     if (full && n_act > 0) {
         // every pass of the solve in one graph: max_outer master problems and selection passes (the stop
@@ -1201,8 +1232,49 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
     // Then per iteration: master problem on I_t, next selection pass.
     int imax = 0;
     bool after_warm = warm;
+    auto one_iteration = [&](int n_grid) -> bmpl_status {
+        const int add = after_warm ? std::max(warm_k, rho) : rho;
+        imax = std::min(max_active, imax + add);
+        c->timing.outer_iters += tm ? 1 : 0;
+        // a warm start's proposal is mostly zeros: an LDS factor for WARM_KL support positions
+        bmpl_status r = enqueue_master(s, cur, n_grid, after_warm ? std::min(imax, WARM_KL) : imax, imax, false,
+                                       !after_warm);
+        if (r != BMPL_OK) return r;
+        r = enqueue_select_pass(s, cur, n_grid, false, after_warm, false);
+        after_warm = false;
+        cur = 1 - cur;
+        return r;
+    };
+    // Without graphs: with at most AHEAD_MAX signals the host enqueues an iteration before it reads the report
+    // of the pass in front of it, so the GPU does not wait for the host.  The kernels read the count on the
+    // device and the last count read bounds it; each report reserves blocks for the two iterations after its
+    // pass, and the launches after the last stop are empty.
+    unsigned long long unread = 0;   // the number of a pass whose report is still to come
+    if (!graph) {
+        const unsigned long long seq0 = c->pass_seq;   // the first pass
+        int it = 0, read = -1, covered = iters0;       // iterations enqueued, passes read, iterations with blocks
+        int cover[2] = {iters0, 0};                    // iterations that the report of an unread pass covers
+        for (;;) {
+            const bool ahead = ahead_of(n_act);
+            if (it < covered && it - read < (ahead ? 2 : 1)) {
+                st = one_iteration(n_act);
+                if (st != BMPL_OK) return st;
+                cover[++it % 2] = ahead ? 2 : 1;
+                continue;
+            }
+            st = wait_report(seq0 + (unsigned long long)++read);
+            if (st != BMPL_OK) return st;
+            const PassReport r = c->h_report[(seq0 + (unsigned long long)read) % PASS_REPORTS];
+            n_act = r.n_act;
+            if (n_act == 0) break;
+            covered = read + cover[read % 2];
+            st = arena_ensure(c, r.top, r.reserve, s);
+            if (st != BMPL_OK) return st;
+        }
+        if (it > read) unread = seq0 + (unsigned long long)it;
+    }
     while (n_act > 0) {
-        if (graph && !after_warm) {
+        if (!after_warm) {
             // GRAPH_DEPTH iterations as one captured graph launch (two once fewer than 64 signals run: the
             // last few usually stop within two).  The kernels read the running count on the device, so
             // iterations past the last signal's stop are empty launches.
@@ -1231,16 +1303,8 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
             if (st != BMPL_OK) return st;
             continue;
         }
-        const int add = after_warm ? std::max(warm_k, rho) : rho;
-        imax = std::min(max_active, imax + add);
-        c->timing.outer_iters += tm ? 1 : 0;
-        // a warm start's proposal is mostly zeros: an LDS factor for WARM_KL support positions
-        st = enqueue_master(s, cur, n_act, after_warm ? std::min(imax, WARM_KL) : imax, imax, false, !after_warm);
+        st = one_iteration(n_act);
         if (st != BMPL_OK) return st;
-        st = enqueue_select_pass(s, cur, n_act, false, after_warm, false);
-        if (st != BMPL_OK) return st;
-        after_warm = false;
-        cur = 1 - cur;
         st = read_count(cur);
         if (st != BMPL_OK) return st;
     }
@@ -1252,6 +1316,10 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
                 stage_max};
     hipLaunchKernelGGL(pack_kernel, dim3(p), dim3(256), pk.stage ? pack_lds : 0, s, pk);
     HIPC(hipGetLastError());
+    if (unread) {   // as without it, only the packing may still run when the call returns
+        st = wait_report(unread);
+        if (st != BMPL_OK) return st;
+    }
     if (tm) {
         const size_t e_last = mark(c, s);
         span(c, e_pack, e_last, K_OTHER);

@@ -14,6 +14,13 @@ struct PrepArgs {
     int lam_rel_mode;              // lambda set later from the first correlation pass
 };
 
+// What the host loop reads after a pass, in pinned host memory: written by the stop test, `seq` last.
+struct PassReport {
+    unsigned long long seq;       // the pass's number in the context
+    unsigned long long top, reserve;   // the arena's offset and the reserve, as in Arena
+    int n_act;                    // signals still running
+};
+
 struct StatusArgs {
     Workspace w;
     const int* act_in; const int* n_in_dev; int n_in;
@@ -33,6 +40,7 @@ struct StatusArgs {
     int* grow_list; int* n_grow;   // kept signals whose block must grow for this pass's selection
     unsigned long long* grow_off;  // their new blocks' offsets from arena->grow_base (one fetch-and-add)
     int kmin;                      // smallest capacity handed out (as GrowArgs::kmin)
+    PassReport* report; unsigned long long seq;   // written at the end when report is set
 };
 
 struct WarmArgs {

@@ -1026,3 +1026,28 @@ def test_classification_kernel_forms(n, m, p, k, classes):
     np.testing.assert_allclose(resid[lab_ref >= 0], res_ref[lab_ref >= 0], rtol=1e-12)
     assert np.all(resid[lab_ref < 0] == 0.0)
     s.close()
+
+
+@pytest.mark.parametrize("p", [1, 64, 65, 96])
+@pytest.mark.parametrize("opts", [{}, {"screen": "bf16"}, {"max_outer": 3}, {"max_active": 7}])
+def test_host_loop_sizes(p, opts):
+    """Batches around the size up to which the host loop runs an iteration ahead of the count, against the same
+    signals in captured segments: the kernels are the same, so every result is.  One signal is not finite, one is
+    zero, and the last batch's is all of them not finite."""
+    pk = _lib()
+    n, m = 100, 700
+    At, Bt = to_dev(bi.gaussian_dictionary(n, m, 71)), torch.randn(p, n, generator=torch.Generator().manual_seed(p))
+    if p > 2:
+        Bt[1, 3], Bt[2] = float("nan"), 0.0
+    if p == 96:
+        Bt[:, 0] = float("inf")
+    Bt = Bt.cuda()
+    a = pk.Solver(At, 0.1, mode="rel", rho=4, **opts)
+    b = pk.Solver(At, 0.1, mode="rel", rho=4, graph=True, **opts)
+    warm = torch.arange(20, dtype=torch.int32, device="cuda").repeat(p, 1) * 3
+    for w in (None, warm, None):
+        ra, rb = a.solve(Bt, warm=w), b.solve(Bt, warm=w)
+        for key in ("x_val", "x_idx", "supp_len", "iters", "lambda", "objective", "status"):
+            assert torch.equal(ra[key].nan_to_num(), rb[key].nan_to_num()), (key, w is None)
+    a.close()
+    b.close()
