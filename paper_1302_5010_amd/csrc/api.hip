@@ -137,6 +137,7 @@ struct bmpl_ctx {
     int* cand = nullptr;          // [p_cap][CANDCAP] screening candidates
     int* ncand = nullptr;         // [p_cap]
     size_t lds_dyn_max = 0;       // dynamic LDS a solve workgroup may use (bytes)
+    size_t lds_fold_max = 0;      // the same for the kernel of factors in global memory
     bool block_append = false;    // inverse-factor appends in blocks (BMPL_FLAG_BLOCK_APPEND sets it)
     bool qroute = false;          // correlation as beta - Q_{:,S} x_S after the first pass (BMPL_FLAG_Q_ROUTE)
     double* beta = nullptr;       // [p_cap][ldg] beta = A^T b in float64 (Q-route)
@@ -688,7 +689,10 @@ bmpl_status bmpl_create(const float* A_dev, int64_t lda, int32_t n, int32_t m, b
                                     optin - (int)fa.sharedSizeBytes) == hipSuccess)
                 total = (size_t)optin;
             (void)hipGetLastError();
-            dyn = std::min(dyn, total > fa.sharedSizeBytes + 256 ? total - fa.sharedSizeBytes - 256 : (size_t)0);
+            const size_t left = total > fa.sharedSizeBytes + 256 ? total - fa.sharedSizeBytes - 256 : (size_t)0;
+            // (the fold kernel's own LDS does not narrow the others': it takes at most VEC_LDS_QUARTER)
+            if (fn == reinterpret_cast<const void*>(solve_fold_kernel)) c->lds_fold_max = std::min(left, VEC_LDS_QUARTER);
+            else dyn = std::min(dyn, left);
         }
         if (e == hipSuccess) c->lds_dyn_max = dyn;
     }
@@ -1134,12 +1138,11 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         const size_t stage = c->Q ? 0 : GRAM_STAGE_BYTES;   // direct Gram staging, only without the table
         so.kl = std::min(kl, so.kv);
         const size_t rinv_bytes = 8 * (size_t)tri(so.kl);
-        // With the factor in LDS the vectors go there too.  With a factor in global memory, vectors of
-        // more than a quarter of the CU's LDS would cap the workgroups per CU below the four the kernel's
-        // registers allow, and the latency-bound solve gains more from the extra workgroups than it
-        // loses to vectors in global memory (4096-signal ragged batch: 13.2 -> 12.4 s).
+        // With the factor in LDS the vectors go there too.  With a factor in global memory, the kernel's registers
+        // and its own LDS allow two workgroups per CU, and vectors of more than a quarter of the CU's LDS would
+        // leave one.
         const bool rinv_fits = vec_bytes + rinv_bytes + stage <= c->lds_dyn_max;
-        so.vec_lds = vec_bytes + stage <= (rinv_fits ? c->lds_dyn_max : std::min(c->lds_dyn_max, VEC_LDS_QUARTER)) ? 1 : 0;
+        so.vec_lds = vec_bytes + stage <= (rinv_fits ? c->lds_dyn_max : c->lds_fold_max) ? 1 : 0;
         so.rinv_lds = (so.vec_lds && rinv_fits) ? 1 : 0;
         size_t lds = (so.rinv_lds ? rinv_bytes : 0) + (so.vec_lds ? vec_bytes : 0) + stage;
         // block appends pay off when the factor streams from global memory; with an LDS-resident

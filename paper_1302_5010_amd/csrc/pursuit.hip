@@ -27,6 +27,8 @@
 #include <float.h>
 #include <limits.h>
 
+#include <type_traits>
+
 #include "../../include/bmpl.h"
 #include "bmpl_internal.h"
 #include "pursuit.h"
@@ -317,7 +319,7 @@ __device__ inline double col_dot(const Sig& f, const double* v, int k, int s)
 }
 
 // Rinv^T (Rinv w) in one pass over a factor in global memory with s <= 1024 positions:
-// z_i = sum_{k <= i} R(i, k) w[k] and out_k = sum_i z_i R(i, k) / div.  The columns are split over
+// z_i = sum_{k <= i} R(i, k) w[k] and out_k = sum_i z_i R(i, k).  The columns are split over
 // the waves (wave v owns the 64-column chunks v, v + 4, v + 8, v + 12, lane l column l of each), the
 // rows taken in batches: a wave loads its chunks of the batch's rows (chunks past a row's diagonal
 // are skipped by a test on the row index, a scalar branch that leaves the loads in flight; the chunk
@@ -328,18 +330,14 @@ __device__ inline double col_dot(const Sig& f, const double* v, int k, int s)
 // z_i, which each lane folds into its columns' sums while the rows are still in registers.  A row
 // below 512 has at most two chunks per wave, so batches there take 8 rows (4 beyond): up to sixteen
 // loads per lane in flight in every batch.  One read of the factor, instead of a row pass
-// and a column pass that waits for its loads row by row.  Every thread ends with the same sum of
-// z_i^2; z_i goes to z[i] when z is not null.
-//   append (gjj > 0): returns the pivot gjj - sum_i z_i^2; when it exceeds 1e-11 gjj, out receives
-//     the new factor row (div = -sqrt(pivot)), else out is left alone.
-//   solve (gjj = 0): div = 1; returns 0.
-// Ends with a barrier when it writes out.
+// and a column pass that waits for its loads row by row.  z_i goes to z[i].  Ends with a barrier.  (For the
+// sign-fixed minimiser alone, after a pruning; an append's comes with its pass, chol_append_fold.)
 constexpr int FOLD_MAX = 1024;
 
 // Rows [i_begin, i_end) of the one-pass product, RB at a time, each lane's chunks j < NJ.
 template <int RB, int NJ>
 __device__ inline void fold_rows(global_cdouble* R, int i_begin, int i_end, const double (&g)[4], double (&acc)[4],
-                                 double& zz, int& buf, double* z, double (*part)[NT / 64][8])
+                                 int& buf, double* z, double (*part)[NT / 64][8])
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -376,8 +374,7 @@ __device__ inline void fold_rows(global_cdouble* R, int i_begin, int i_end, cons
 #pragma unroll
         for (int q = 0; q < RB; ++q) {
             const double zi = ((part[buf][0][q] + part[buf][1][q]) + part[buf][2][q]) + part[buf][3][q];
-            zz += zi * zi;                       // zero past i_end
-            if (z && threadIdx.x == 0 && i0 + q < i_end) z[i0 + q] = zi;
+            if (threadIdx.x == 0 && i0 + q < i_end) z[i0 + q] = zi;
 #pragma unroll
             for (int j = 0; j < NJ; ++j) acc[j] += zi * r[q][j];
         }
@@ -385,8 +382,7 @@ __device__ inline void fold_rows(global_cdouble* R, int i_begin, int i_end, cons
     }
 }
 
-__device__ inline double fold_pass_global(const double* R, const double* w, int s, double* out, double* z,
-                                          double gjj)
+__device__ __noinline__ void fold_pass_global(const double* R, const double* w, int s, double* out, double* z)
 {
     __shared__ double part_lds[2][NT / 64][8];
     const int lane = threadIdx.x & 63;
@@ -400,40 +396,423 @@ __device__ inline double fold_pass_global(const double* R, const double* w, int 
         g[j] = w[k < s ? k : last];
         acc[j] = 0.0;
     }
-    double zz = 0.0;
     int buf = 0;
     global_cdouble* Rg = to_global(R);
-    fold_rows<8, 2>(Rg, 0, s < 512 ? s : 512, g, acc, zz, buf, z, part_lds);
-    fold_rows<4, 4>(Rg, 512, s, g, acc, zz, buf, z, part_lds);
-    double div = 1.0, pivot = 0.0;
-    if (gjj > 0.0) {
-        pivot = gjj - zz;
-        if (!(pivot > 1e-11 * gjj)) return pivot;
-        div = -sqrt(pivot);
-    }
-    // (out's own memory: a generic store would hold up the barrier until it reaches global memory)
-    if (is_lds(out)) {
+    fold_rows<8, 2>(Rg, 0, s < 512 ? s : 512, g, acc, buf, z, part_lds);
+    fold_rows<4, 4>(Rg, 512, s, g, acc, buf, z, part_lds);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int k = 64 * (wave + 4 * j) + lane;
-            if (k < s) to_lds(out)[k] = acc[j] / div;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int k = 64 * (wave + 4 * j) + lane;
-            if (k < s) to_global(out)[k] = acc[j] / div;
-        }
+    for (int j = 0; j < 4; ++j) {
+        const int k = 64 * (wave + 4 * j) + lane;
+        if (k < s) out[k] = acc[j];
     }
     __syncthreads();
-    return pivot;
+}
+
+// x over the lower half of the wave added to x over the upper half in lanes 0..31, the same of y in lanes 32..63.
+__device__ __forceinline__ double fold_half(double x, double y)
+{
+    const uint64_t bx = (uint64_t)__double_as_longlong(x), by = (uint64_t)__double_as_longlong(y);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)bx, (uint32_t)by, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(bx >> 32), (uint32_t)(by >> 32), false, false);
+    return __longlong_as_double((int64_t)(((uint64_t)hi[0] << 32) | lo[0])) +
+           __longlong_as_double((int64_t)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+
+// The same between the two rows of 16 lanes of each half: x in the even rows, y in the odd ones.
+__device__ __forceinline__ double fold_rows16(double x, double y)
+{
+    const uint64_t bx = (uint64_t)__double_as_longlong(x), by = (uint64_t)__double_as_longlong(y);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)bx, (uint32_t)by, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(bx >> 32), (uint32_t)(by >> 32), false, false);
+    return __longlong_as_double((int64_t)(((uint64_t)hi[0] << 32) | lo[0])) +
+           __longlong_as_double((int64_t)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+
+constexpr int DPP_ROR8 = 0x128;   // row_ror:8, lane ^ 8 within a row of 16
+
+// Eight values per lane summed over the lanes with the same low three bits: lane l gets the sum for value l >> 3.
+__device__ __forceinline__ double fold_eight(const double (&a)[8])
+{
+    const bool b3 = (threadIdx.x >> 3) & 1;
+    double u[4], w[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) u[i] = fold_half(a[i], a[i + 4]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) w[i] = fold_rows16(u[i], u[i + 2]);
+    return (b3 ? w[1] : w[0]) + lane_move<DPP_ROR8>(b3 ? w[0] : w[1]);
+}
+
+// The sum over the low three lane bits (every lane of a group of eight gets it).
+__device__ __forceinline__ double sum_low8(double t)
+{
+    t += lane_move<DPP_HALF_MIRROR>(t);
+    t += lane_move<DPP_XOR2>(t);
+    return t + lane_move<DPP_XOR1>(t);
+}
+
+typedef uint32_t uint2_t __attribute__((ext_vector_type(2)));
+
+// Rows of a packed factor in global memory, one buffer per row: a load past the row's diagonal returns zero and a
+// store past it is dropped, by the buffer's bound, so neither needs an address or a mask per lane.
+struct RowBuffers {
+    uint64_t base;
+    __device__ __forceinline__ explicit RowBuffers(const double* R)
+    {
+        const uint64_t p = reinterpret_cast<uint64_t>(R);
+        base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(p >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+    }
+    // row i (the same on every lane); empty: no entry
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t row(int i, bool empty) const
+    {
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(base + 4ull * (uint32_t)(i * (i + 1))), 0,
+                                                 empty ? 0 : 8 * (i + 1), 0x00027000);
+    }
+};
+__device__ __forceinline__ double row_load(__amdgpu_buffer_rsrc_t r, int c8)
+{
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, c8, 0, 0));
+}
+__device__ __forceinline__ void row_store(__amdgpu_buffer_rsrc_t r, int c8, double v)
+{
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2_t, v), r, c8, 0, 0);
+}
+
+// chol_append_fold: J <= 8 single appends to a factor in global memory from one pass over it.  One append at a time,
+// each over all rows, was a chain of batches (load, sum over the wave, barrier): 50 us an atom on supports around
+// 300 to 480, half of the ragged batch's time (300 signals of 512 x 4096, supports up to 480).  The rows before s0 are
+// the same for all J atoms: they are read once, give each atom's z_i and are folded into each atom's column sums.
+// The new rows, which later atoms of the list also need, stay in registers: a lane keeps the sums of its columns,
+// which become the row's entries, so atom e takes one more round over the e rows before it.
+// One pass for up to eight atoms takes 65 us there (9 us an atom), and its arithmetic bounds it: three quarters of the
+// instructions are sums over lanes and broadcasts, not the products.  With the columns split over the waves (a sum over
+// the waves and a barrier per eight rows, as beyond 512 columns) it took 82 us; prefetching rows, or skipping columns a row does not have,
+// each gave a tenth.
+// Excluded atoms (no pivot) leave a zero row here and take no support position.
+// xs (J <= 7): the eighth right-hand side is w = c_S - lambda theta_S, whose z (vzc) and sums (vx) are the
+// sign-fixed minimiser's (sign_fixed_solve) on the s0 positions before.
+struct FoldLds {
+    static constexpr int C = 2 * NT;              // columns of fold_rows_wave
+    double part[2][NT / 64][64];
+    double gl[8][8];                              // Gram entries of the list
+    double z[C];                                  // fold_rows_wave: the eighth right-hand side's z
+    double zz[NT / 64][8];
+    double g[8][C];                               // fold_rows_wave: the right-hand sides, then the waves' sums;
+                                                  // fold_rows_split: the eighth right-hand side's z
+};
+
+// The rows before s0, s0 > 256 NJ / 2 columns split over the waves (wave v, lane l: columns 64 (v + 4 j) + l): eight
+// rows at a time give each right-hand side's z_i by a sum over the wave and one over the waves (a barrier).
+// acc: this lane's columns' sums; zz: sum z_i^2 of right-hand side l & 7 (every lane with those low bits).
+template <int NJ>
+__device__ __forceinline__ void fold_rows_split(const RowBuffers& rows, int s0, const double (&g)[8][NJ],
+                                                double (&acc)[8][NJ], double& zz, int& buf, FoldLds& w)
+{
+    constexpr int NR = 8, NW = NT / 64, RB = 8;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    double zzl = 0.0;
+    // rows [i0, i1) with the first JL of each lane's columns
+    auto pass = [&](auto jl, int i0, int i1) {
+        constexpr int JL = decltype(jl)::value;
+        for (int i = i0; i < i1; i += RB) {
+            double r[RB][JL];
+#pragma unroll
+            for (int q = 0; q < RB; ++q) {
+                const auto b = rows.row(i + q, i + q >= s0);
+#pragma unroll
+                for (int j = 0; j < JL; ++j) r[q][j] = row_load(b, 8 * (64 * (wave + NW * j) + lane));
+            }
+            // lane l: the products of row l >> 3 with right-hand side l & 7
+            double t[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                double p8[8];
+#pragma unroll
+                for (int q = 0; q < RB; ++q) {
+                    double d = 0.0;
+#pragma unroll
+                    for (int j = 0; j < JL; ++j) d += r[q][j] * g[e][j];
+                    p8[q] = d;
+                }
+                t[e] = fold_eight(p8);
+                if (e & 1) __builtin_amdgcn_sched_barrier(0);   // two right-hand sides' products at a time
+            }
+            const bool b0 = lane & 1, b1 = (lane >> 1) & 1, b2 = (lane >> 2) & 1;
+            double t4[4], t2[2];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                t4[q] = (b2 ? t[q + 4] : t[q]) + lane_move<DPP_HALF_MIRROR>(b2 ? t[q] : t[q + 4]);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) t2[q] = (b1 ? t4[q + 2] : t4[q]) + lane_move<DPP_XOR2>(b1 ? t4[q] : t4[q + 2]);
+            w.part[buf][wave][lane] = (b0 ? t2[1] : t2[0]) + lane_move<DPP_XOR1>(b0 ? t2[0] : t2[1]);
+            __syncthreads();
+            const double z = ((w.part[buf][0][lane] + w.part[buf][1][lane]) + w.part[buf][2][lane]) + w.part[buf][3][lane];
+            buf ^= 1;
+            zzl += z * z;                         // zero past s0
+            if (wave == 0 && (lane & 7) == 7) w.g[0][i + (lane >> 3)] = z;
+#pragma unroll
+            for (int e = 0; e < NR; ++e) {
+#pragma unroll
+                for (int q = 0; q < RB; ++q) {
+                    const double zi = read_lane(z, 8 * q + e);
+#pragma unroll
+                    for (int j = 0; j < JL; ++j) acc[e][j] += zi * r[q][j];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    pass(std::integral_constant<int, NJ / 2>{}, 0, min(s0, NT * (NJ / 2)));
+    if (s0 > NT * (NJ / 2)) pass(std::integral_constant<int, NJ>{}, NT * (NJ / 2), s0);
+    zzl += lane_move<DPP_ROR8>(zzl);
+    zzl = fold_rows16(zzl, zzl);
+    zz = fold_half(zzl, zzl);
+}
+
+// The same for s0 <= 512 with the rows split over the waves: a wave takes whole rows (lane l: columns 64 c + l), so
+// a row's sum needs no other wave, no barrier, and a quarter of the reductions, and the load of the next rows
+// runs under these rows' arithmetic; the waves' column sums meet in LDS at the end.  The arithmetic, not the bytes,
+// takes the time.  w.g holds the right-hand sides; the right-hand sides' entries of this lane's columns of the
+// column split are left in g.
+__device__ __forceinline__ void fold_rows_wave(const RowBuffers& rows, int s0, double (&g)[8][2], double (&acc)[8][2],
+                                               double& zz, FoldLds& w)
+{
+    constexpr int NR = 8, NW = NT / 64, NC = FoldLds::C / 64;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool b1 = (lane >> 1) & 1, b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1;
+    double sum[NR][NC];
+#pragma unroll
+    for (int e = 0; e < NR; ++e)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) sum[e][c] = 0.0;
+    double zs = 0.0;                              // sum of z^2 of this lane's right-hand side
+    // rows [i0, i1), RB per wave at a time, with the first CL chunks of columns
+    auto pass = [&](auto cl, auto rb, int i0, int i1) {
+        constexpr int CL = decltype(cl)::value, RB = decltype(rb)::value;
+        auto load = [&](int i, double (&r)[RB][CL]) {
+#pragma unroll
+            for (int q = 0; q < RB; ++q) {
+                const auto b = rows.row(i + q, i + q >= i1);
+#pragma unroll
+                for (int c = 0; c < CL; ++c) r[q][c] = row_load(b, 8 * (64 * c + lane));
+            }
+        };
+        double zl = 0.0;
+        auto batch = [&](int i, const double (&r)[RB][CL]) {
+            double t[NR];
+#pragma unroll
+            for (int e = 0; e < NR; ++e) {
+                double d[RB];
+#pragma unroll
+                for (int q = 0; q < RB; ++q) d[q] = 0.0;
+#pragma unroll
+                for (int c = 0; c < CL; ++c) {
+                    const double ge = w.g[e][64 * c + lane];
+#pragma unroll
+                    for (int q = 0; q < RB; ++q) d[q] += r[q][c] * ge;
+                }
+                if constexpr (RB == 4)            // row 2 b5 + b4
+                    t[e] = fold_rows16(fold_half(d[0], d[2]), fold_half(d[1], d[3]));
+                else                              // row b5
+                    t[e] = fold_half(d[0], d[1]);
+                if (e & 1) __builtin_amdgcn_sched_barrier(0);
+            }
+            // the right-hand sides over the next three lane bits, then the sum over the rest
+            double u[4], v[2], z;
+            if constexpr (RB == 4) {              // right-hand side 4 b3 + 2 b2 + b1
+#pragma unroll
+                for (int k = 0; k < 4; ++k) u[k] = (b3 ? t[k + 4] : t[k]) + lane_move<DPP_ROR8>(b3 ? t[k] : t[k + 4]);
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    v[k] = (b2 ? u[k + 2] : u[k]) + lane_move<DPP_HALF_MIRROR>(b2 ? u[k] : u[k + 2]);
+                z = (b1 ? v[1] : v[0]) + lane_move<DPP_XOR2>(b1 ? v[0] : v[1]);
+                z += lane_move<DPP_XOR1>(z);
+            } else {                              // right-hand side 4 b4 + 2 b3 + b2
+#pragma unroll
+                for (int k = 0; k < 4; ++k) u[k] = fold_rows16(t[k], t[k + 4]);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) v[k] = (b3 ? u[k + 2] : u[k]) + lane_move<DPP_ROR8>(b3 ? u[k] : u[k + 2]);
+                z = (b2 ? v[1] : v[0]) + lane_move<DPP_HALF_MIRROR>(b2 ? v[0] : v[1]);
+                z += lane_move<DPP_XOR2>(z);
+                z += lane_move<DPP_XOR1>(z);
+            }
+            zl += z * z;                          // zero past i1
+            const int rhs = RB == 4 ? (lane >> 1) & 7 : (lane >> 2) & 7;
+            if (rhs == 7) w.z[i + (RB == 4 ? lane >> 4 : lane >> 5)] = z;
+#pragma unroll
+            for (int e = 0; e < NR; ++e) {
+#pragma unroll
+                for (int q = 0; q < RB; ++q) {
+                    const double zi = read_lane(z, RB == 4 ? 16 * q + 2 * e : 32 * q + 4 * e);
+#pragma unroll
+                    for (int c = 0; c < CL; ++c) sum[e][c] += zi * r[q][c];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        double ra[RB][CL], rb_[RB][CL];           // the next rows are in flight during these rows' arithmetic
+        constexpr int STEP = RB * NW;
+        int i = i0 + RB * wave;
+        load(i, ra);
+        for (; i < i1; i += 2 * STEP) {
+            load(i + STEP, rb_);
+            batch(i, ra);
+            if (i + STEP >= i1) break;
+            load(i + 2 * STEP, ra);
+            batch(i + STEP, rb_);
+        }
+        // rows over the lanes: right-hand side e in lane 2 e (4 e)
+        if constexpr (RB == 4) zl = fold_rows16(zl, zl);
+        zl = fold_half(zl, zl);
+        zs += __shfl(zl, RB == 4 ? 2 * (lane & 7) : 4 * (lane & 7));
+    };
+    pass(std::integral_constant<int, NC / 2>{}, std::integral_constant<int, 4>{}, 0, min(s0, NT));
+    if (s0 > NT) pass(std::integral_constant<int, NC>{}, std::integral_constant<int, 2>{}, NT, s0);
+    if (lane < 8) w.zz[wave][lane] = zs;
+#pragma unroll
+    for (int e = 0; e < NR; ++e)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) g[e][j] = w.g[e][64 * (wave + NW * j) + lane];
+    __syncthreads();                              // every wave is done with w.g: its memory takes the sums now
+    zz = ((w.zz[0][lane & 7] + w.zz[1][lane & 7]) + w.zz[2][lane & 7]) + w.zz[3][lane & 7];
+#pragma unroll
+    for (int e = 0; e < NR; ++e) {
+        double(*m)[FoldLds::C] = &w.g[4 * (e & 1)];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) m[wave][64 * c + lane] = sum[e][c];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int k = 64 * (wave + NW * j) + lane;
+            acc[e][j] = ((m[0][k] + m[1][k]) + m[2][k]) + m[3][k];
+        }
+    }
+}
+
+template <int NJ>
+__device__ __forceinline__ void chol_append_fold(Sig& v, int& nS, const int* list, int J, const double* vg, bool xs,
+                                                 double lam, double* vzc, double* vx, FoldLds& w)
+{
+    constexpr int NR = 8, NW = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int s0 = __builtin_amdgcn_readfirstlane(nS);
+    J = __builtin_amdgcn_readfirstlane(J);
+    global_cdouble* G = to_global((const double*)v.G);
+    int slot[NR];                                 // past J the last atom again: computed, never used
+#pragma unroll
+    for (int e = 0; e < NR; ++e) slot[e] = __builtin_amdgcn_readfirstlane(list[e < J ? e : J - 1]);
+    if (tid < NR * NR) {
+        const int e = tid / NR, f = tid % NR;
+        w.gl[e][f] = G[(int64_t)list[e < J ? e : J - 1] * v.K + list[f < J ? f : J - 1]];
+    }
+    double g[NR][NJ], acc[NR][NJ];
+    double zzl = 0.0;
+    int buf = 0;
+    {
+        int sk[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int k = 64 * (wave + NW * j) + lane;
+            sk[j] = s0 > 0 ? v.so[k < s0 ? k : s0 - 1] : slot[0];
+        }
+#pragma unroll
+        for (int e = 0; e < NR; ++e)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                g[e][j] = G[(int64_t)slot[e] * v.K + sk[j]];
+                acc[e][j] = 0.0;
+            }
+        if (xs)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) g[NR - 1][j] = v.c[sk[j]] - lam * (double)v.th[sk[j]];
+    }
+    const RowBuffers rows(v.R);
+    if (s0 > 0) {
+        if constexpr (NJ == 2) {
+#pragma unroll
+            for (int e = 0; e < NR; ++e)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) w.g[e][64 * (wave + NW * j) + lane] = g[e][j];
+            __syncthreads();
+            fold_rows_wave(rows, s0, g, acc, zzl, w);
+        } else {
+            fold_rows_split<NJ>(rows, s0, g, acc, zzl, buf, w);
+        }
+    }
+    __syncthreads();   // w.gl (when there were no rows), and the readers of w.part are done
+    int s = s0;
+#pragma unroll
+    for (int e = 0; e < NR; ++e) {
+        if (e >= J) break;                        // the same in every thread
+        double zz = read_lane(zzl, e);
+        if (e > 0) {
+            // this atom's products with the new rows 0 .. e - 1 (zero rows for the excluded atoms)
+            double pq[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                double a = 0.0;
+                if (t < e)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) a += acc[t < NR ? t : 0][j] * g[e][j];
+                pq[t] = a;
+            }
+            w.part[buf][wave][lane] = sum_low8(fold_eight(pq));
+            __syncthreads();
+            const double z = ((w.part[buf][0][lane] + w.part[buf][1][lane]) + w.part[buf][2][lane]) + w.part[buf][3][lane];
+            buf ^= 1;
+#pragma unroll
+            for (int t = 0; t < e; ++t) {
+                const double zi = read_lane(z, 8 * t);
+                zz += zi * zi;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) acc[e][j] += zi * acc[t][j];
+            }
+        }
+        const double gjj = w.gl[e][e];
+        const double dd = gjj - zz;
+        const bool ok = dd > 1e-11 * gjj;
+        const double d = sqrt(dd);
+        const auto out = rows.row(s, !ok);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int k = 64 * (wave + NW * j) + lane;
+            double o = 0.0;
+            if (ok) o = k < s ? acc[e][j] / -d : (k == s ? 1.0 / d : 0.0);
+            acc[e][j] = o;
+            row_store(out, 8 * k, o);
+#pragma unroll
+            for (int f = e + 1; f < NR; ++f) g[f][j] = ok && k == s ? w.gl[f][e] : g[f][j];
+        }
+        if (tid == 0) {
+            if (ok) {
+                v.so[s] = slot[e];
+                v.th[slot[e]] = vg[slot[e]] > 0.0 ? 1 : -1;
+            } else {
+                v.ex[slot[e]] = 1; v.th[slot[e]] = 0; v.x[slot[e]] = 0.0;
+            }
+        }
+        s += ok ? 1 : 0;
+    }
+    if (xs) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int k = 64 * (wave + NW * j) + lane;
+            if (k < s0) vx[k] = acc[NR - 1][j];
+        }
+        const double* wz = NJ == 2 ? w.z : w.g[0];
+        for (int k = tid; k < s0; k += NT) vzc[k] = wz[k];
+    }
+    nS = s;
+    __syncthreads();
 }
 
 // Append slot j with sign th at support position s = nS (a Cholesky row append
 // held as the inverse factor).  Returns false and excludes j if its Schur
 // complement pivot vanishes, i.e. a_j is numerically in the span of A_S.
-template <bool FOLD>
-__device__ bool chol_append(Sig& v, int& nS, int j, signed char th, double* vw, double* vz, double* red,
+__device__ __forceinline__ bool chol_append(const Sig& v, int& nS, int j, signed char th, double* vw, double* vz, double* red,
                             uint64_t* cnt)
 {
     const int s = nS;
@@ -462,21 +841,15 @@ __device__ bool chol_append(Sig& v, int& nS, int j, signed char th, double* vw, 
     __syncthreads();
     double* Rs = v.R + tri(s);
     const double gjj = s_gjj;
-    const bool fold = FOLD && !v.r_lds && s <= FOLD_MAX;   // one pass over a global factor
-    double dd;
-    if (fold) {
-        dd = fold_pass_global(v.R, vw, s, Rs, nullptr, gjj);   // writes the new row if dd is a pivot
+    double part = 0.0;
+    if (v.r_lds) {
+        part = rows_matvec_lds(v.R, vw, vz, s);    // z = Rinv w
     } else {
-        double part = 0.0;
-        if (v.r_lds) {
-            part = rows_matvec_lds(v.R, vw, vz, s);    // z = Rinv w
-        } else {
-            rows_matvec_global(v.R, vw, vz, s);
-            __syncthreads();
-            for (int i = tid; i < s; i += NT) part += vz[i] * vz[i];
-        }
-        dd = gjj - block_sum_fenced(part, red);   // the barrier after the gather fences red
+        rows_matvec_global(v.R, vw, vz, s);
+        __syncthreads();
+        for (int i = tid; i < s; i += NT) part += vz[i] * vz[i];
     }
+    const double dd = gjj - block_sum_fenced(part, red);   // the barrier after the gather fences red
     if (!(dd > 1e-11 * gjj)) {
         if (tid == 0) { v.ex[j] = 1; v.th[j] = 0; v.x[j] = 0.0; }
         __syncthreads();
@@ -487,7 +860,7 @@ __device__ bool chol_append(Sig& v, int& nS, int j, signed char th, double* vw, 
     const double d = sqrt(dd);
     if (v.r_lds)                             // new row: -(z^T Rinv)_k / d
         cols_matvec_lds(v.R, vz, Rs, s, -d);
-    else if (!fold)
+    else
         for (int k = tid; k < s; k += NT) Rs[k] = -col_dot(v, vz, k, s) / d;
     if (tid == 0) {
         Rs[s] = 1.0 / d;
@@ -702,7 +1075,7 @@ __device__ void append_list(Sig& v, int& nS, const int* list, int nv, const doub
 // every read of a row before the iteration that writes it.  (The kernel capped at 128 registers uses a
 // narrower register window: four columns, |S| <= 1024.)
 template <int DROP_COLS>
-__device__ void chol_drop(Sig& v, int s, int q, double* cbuf, double* zc)
+__device__ __forceinline__ void chol_drop(const Sig& v, int s, int q, double* cbuf, double* zc)
 {
     const int tid = threadIdx.x;
     if (s <= DROP_COLS * NT) {
@@ -809,111 +1182,124 @@ __device__ void chol_drop(Sig& v, int s, int q, double* cbuf, double* zc)
     __syncthreads();
 }
 
-// chol_drop's register path for a factor in global memory (s <= 4 NT): the same rotations in the same
-// order.  Every access names its memory (the factor as global from a scalar base, zc as LDS or global
-// by ZK: 0 none, 1 LDS, 2 global): the generic accesses of chol_drop count against the LDS counter
-// as well, so its barrier after each step waited for that step's global loads and stores to
-// complete.  Here the barrier only orders the workgroup (its waves share one vector L1, which keeps
-// their global accesses in order), and the next step's row and zc entry are in flight meanwhile:
-// their loads take clamped indices and are not masked (a masked load, or one behind a branch, makes
-// the wave wait for it at once), into two buffers that take turns.  Entries past a row's end are
-// never used: step j uses row j + 1 in columns c <= j only, and rows past s - 1 (read as row s - 1)
-// are never used.  Row r is read two steps before step r rewrites it, with a barrier after every step.
-template <int ZK>
-__device__ void chol_drop_global_t(Sig& v, int s, int q, double* cbuf, double* zc)
+// The fold kernel's appends and drops beyond FOLD_MAX positions, out of line: inlined, they cost its hot loops registers.
+__device__ __noinline__ int chol_append_far(Sig v, int nS, int j, signed char th, double* vw, double* vz, double* red,
+                                            uint64_t* cnt)
 {
-    constexpr int DC = 4;
-    const int tid = threadIdx.x;
+    chol_append(v, nS, j, th, vw, vz, red, cnt);
+    return nS;
+}
+__device__ __noinline__ void chol_drop_far(Sig v, int s, int q, double* cbuf, double* zc)
+{
+    chol_drop<4>(v, s, q, cbuf, zc);
+}
+
+// chol_drop for a factor in global memory (s <= 4 NT): the same rotations, eight rows per barrier.  The rotation of
+// row j + 1 into row j needs b_j = R(j + 1, q) and the length of (R(q, q), b_q, .., b_{j-1}), both known before any
+// row is touched: a wave takes 64 rows' lengths from a prefix sum of b^2, one lane per row (the chain of hypot and
+// two divisions per row took as long as the row's memory access), and every column is then independent.  A thread
+// reads columns of the next eight rows while it rotates these; a barrier between the arrival of eight rows and
+// the first store into them keeps a wave from overwriting an entry that its neighbour, one column on, still reads
+// (entry c of a row moves from column c + 1 for c >= q).  A row costs about 0.1 us (three reads of lane values and
+// eight products per two columns); one barrier, one hypot and two divisions per row took 0.8 us: 99 us a drop on
+// the ragged batch's supports, 21 us this way.
+template <int DC>
+__device__ __forceinline__ void chol_drop_rows(const Sig& v, int s, int q, double* cbuf, double* zc)
+{
+    constexpr int RB = 8;
+    const int tid = threadIdx.x, lane = tid & 63;
     s = __builtin_amdgcn_readfirstlane(s);
     q = __builtin_amdgcn_readfirstlane(q);
-    global_double* R = to_global(v.R);
-    // row r >= q + 1 with column q moved out (entry c from column c if c < q, else c + 1; clamped
-    // into the row), and bq = R(r, q)
-    auto load_row = [&](int r, double (&o)[DC], double& bq) {
-        r = r < s ? r : s - 1;
-        global_double* Rr = R + tri(r);
-#pragma unroll
-        for (int t = 0; t < DC; ++t) {
-            const int c = tid + NT * t;
-            const int cc = c <= r - 1 ? c : r - 1;
-            o[t] = Rr[cc < q ? cc : cc + 1];
-        }
-        bq = Rr[q];
-    };
-    auto load_z = [&](int r) -> double {
-        r = r < s ? r : s - 1;
-        if (ZK == 1) return to_lds(zc)[r];
-        if (ZK == 2) return to_global(zc)[r];
-        return 0.0;
-    };
-    double cv[DC], ra[DC], rb[DC];
+    const RowBuffers rows(v.R);
+    global_cdouble* R = to_global((const double*)v.R);
+    double cv[DC];
+    int src8[DC];                              // byte offset of this thread's source columns in a row
     {
-        global_double* Rq = R + tri(q);
+        const auto rq = rows.row(q, false);
 #pragma unroll
         for (int t = 0; t < DC; ++t) {
             const int c = tid + NT * t;
-            cv[t] = Rq[c < q ? c : q];
+            src8[t] = 8 * (c < q ? c : c + 1);
+            cv[t] = row_load(rq, 8 * c);
         }
 #pragma unroll
         for (int t = 0; t < DC; ++t) cv[t] = tid + NT * t < q ? cv[t] : 0.0;
     }
-    double ba = 0.0, bb = 0.0;
-    if (q + 1 < s) load_row(q + 1, ra, ba);
-    double za = load_z(q + 1), zb = 0.0;
-    double last = R[tri(q) + q];
-    double zcar = load_z(q);
-    // every thread has its R(q, q) before the owner of column q rewrites row q in the first rotation
-    __syncthreads();
-    // Step j rotates with row j + 1 (in X) and loads row j + 2 into Z, the buffer step j - 1 used; the
-    // two buffers take turns by name (a copy of a register that a load is still filling would wait
-    // for the load).
-    auto step = [&](int j, const double (&X)[DC], double bX, double zX, double (&Z)[DC], double& bZ, double& zZ) {
-        load_row(j + 2, Z, bZ);
-        zZ = load_z(j + 2);
-        const double r = hypot(last, bX);
-        const double cs = r > 0.0 ? bX / r : 1.0;
-        const double sn = r > 0.0 ? -last / r : 0.0;
-        global_double* out = R + tri(j);
+    double last = R[tri(q) + q];               // signed; a length from the first rotation on
+    double len2 = last * last;
+    double zcar = zc ? zc[q] : 0.0;
+    auto load = [&](int r0, double (&x)[RB][DC]) {   // rows r0 .. r0 + RB - 1, column q moved out, zero past the end
 #pragma unroll
-        for (int t = 0; t < DC; ++t) {
-            const int c = tid + NT * t;
-            if (c <= j) {                    // columns past j stay zero in the moved column
-                out[c] = cs * cv[t] + sn * X[t];
-                cv[t] = -sn * cv[t] + cs * X[t];
-            }
+        for (int e = 0; e < RB; ++e) {
+            const auto b = rows.row(r0 + e, r0 + e >= s);
+#pragma unroll
+            for (int t = 0; t < DC; ++t) x[e][t] = row_load(b, src8[t]);
         }
-        if (ZK != 0) {
-            const double zj = cs * zcar + sn * zX;
-            zcar = -sn * zcar + cs * zX;
-            if (tid == 0) {
-                if (ZK == 1) to_lds(zc)[j] = zj;
-                else to_global(zc)[j] = zj;
-            }
-        }
-        last = r;
-        __syncthreads();
     };
-    for (int j = q; j < s - 1; j += 2) {
-        step(j, ra, ba, za, rb, bb, zb);
-        if (j + 1 >= s - 1) break;
-        step(j + 1, rb, bb, zb, ra, ba, za);
+    auto diag = [&](int j0) {                  // lane l: b of row j0 + l + 1
+        const int r = j0 + lane + 1 < s ? j0 + lane + 1 : s - 1;
+        return R[tri(r) + q];
+    };
+    double csl = 0.0, snl = 0.0, zl = 0.0, zout = 0.0;
+    double bl = diag(q);
+    auto rotate = [&](int j0, int l0, const double (&x)[RB][DC]) {   // rows j0 .. j0 + RB - 1, coefficients from lane l0
+#pragma unroll
+        for (int e = 0; e < RB; ++e)
+#pragma unroll
+            for (int t = 0; t < DC; ++t) asm volatile("" ::"v"(x[e][t]));   // arrived before the barrier
+        __syncthreads();                       // every wave holds its entries of rows j0 + 1 .. j0 + RB
+#pragma unroll
+        for (int e = 0; e < RB; ++e) {
+            const double cs = read_lane(csl, l0 + e), sn = read_lane(snl, l0 + e), zx = read_lane(zl, l0 + e);
+            const auto b = rows.row(j0 + e, j0 + e >= s - 1);
+#pragma unroll
+            for (int t = 0; t < DC; ++t) {
+                row_store(b, 8 * (tid + NT * t), cs * cv[t] + sn * x[e][t]);
+                cv[t] = -sn * cv[t] + cs * x[e][t];   // columns past j: zero and zero
+            }
+            const double zj = cs * zcar + sn * zx;
+            zcar = -sn * zcar + cs * zx;
+            zout = lane == l0 + e ? zj : zout;
+        }
+    };
+    double xa[RB][DC], xb[RB][DC];
+    load(q + 1, xa);
+    for (int j0 = q; j0 < s - 1; j0 += 64) {
+        // coefficients of rows j0 .. j0 + 63; rows past s - 2 leave the carried column as it is
+        const bool in = j0 + lane < s - 1;
+        const double b = in ? bl : 0.0;
+        zl = zc && in ? zc[j0 + lane + 1] : 0.0;
+        double sum = b * b;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const double up = __shfl_up(sum, o);
+            sum += lane >= o ? up : 0.0;
+        }
+        sum += len2;
+        const double r = sqrt(sum);
+        const double prev = __shfl_up(r, 1);
+        const double lst = lane == 0 ? last : prev;
+        csl = in ? (r > 0.0 ? b / r : 1.0) : 0.0;
+        snl = in ? (r > 0.0 ? -lst / r : 0.0) : -1.0;
+        len2 = read_lane(sum, 63);
+        last = read_lane(r, 63);
+        bl = diag(j0 + 64);
+        for (int l0 = 0; l0 < 64 && j0 + l0 < s - 1; l0 += 2 * RB) {
+            load(j0 + l0 + RB + 1, xb);
+            rotate(j0 + l0, l0, xa);
+            load(j0 + l0 + 2 * RB + 1, xa);
+            rotate(j0 + l0 + RB, l0 + RB, xb);
+        }
+        if (zc && tid < 64 && in) zc[j0 + lane] = zout;
     }
 #pragma unroll
     for (int t = 0; t < DC; ++t) {
         const int c = tid + NT * t;
         if (c < s) cbuf[c] = cv[t];
     }
-    if (ZK != 0 && tid == 0) {
-        if (ZK == 1) to_lds(zc)[s - 1] = zcar;
-        else to_global(zc)[s - 1] = zcar;
-    }
+    __syncthreads();                           // every wave has read its zc entries and its rows
+    if (zc && tid == 0) zc[s - 1] = zcar;
     __syncthreads();
-}
-
-// chol_drop_global_t for a zc in global memory (the fold kernel's large supports)
-__device__ inline void chol_drop_global(Sig& v, int s, int q, double* cbuf, double* zc)
-{
-    chol_drop_global_t<2>(v, s, q, cbuf, zc);
 }
 
 // The sign-fixed minimiser after support positions s0..s1-1 were appended to the factor, from the cached
@@ -921,8 +1307,7 @@ __device__ inline void chol_drop_global(Sig& v, int s, int q, double* cbuf, doub
 // (its earlier rows unchanged), and w only gains the entries of the new positions (a member's sign does
 // not change while it stays in S), so z gains the new rows' products with w and x* gains those rows'
 // contributions: O((s1 - s0) s1) work instead of two passes over the factor.  vw: scratch.
-__device__ void xstar_after_append(const Sig& v, int s0, int s1, double lam, double* vw, double* vzc, double* vx,
-                                   double* red)
+__device__ void xstar_after_append(const Sig& v, int s0, int s1, double lam, double* vw, double* vzc, double* vx)
 {
     const int tid = threadIdx.x;
     for (int k = tid; k < s1; k += NT) {
@@ -930,17 +1315,39 @@ __device__ void xstar_after_append(const Sig& v, int s0, int s1, double lam, dou
         vw[k] = v.c[u] - lam * (double)v.th[u];
     }
     __syncthreads();
-    for (int p = s0; p < s1; ++p) {
+    // z of the new rows, a wave per row, four entries per lane in flight (clamped indices)
+    const int lane = tid & 63, wave = tid >> 6;
+    for (int p = s0 + wave; p < s1; p += NT / 64) {
         const double* Rp = v.R + tri(p);
         double part = 0.0;
-        for (int k = tid; k <= p; k += NT) part += Rp[k] * vw[k];
-        const double zp = block_sum(part, red);
-        if (tid == 0) vzc[p] = zp;
+        for (int k0 = lane; k0 <= p; k0 += 4 * 64) {
+            double r[4], x[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int k = k0 + 64 * e <= p ? k0 + 64 * e : p;
+                r[e] = Rp[k];
+                x[e] = vw[k];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part += k0 + 64 * e <= p ? r[e] * x[e] : 0.0;
+        }
+        part = wave_sum(part);
+        if (lane == 0) vzc[p] = part;
     }
     __syncthreads();
     for (int k = tid; k < s1; k += NT) {
         double acc = k < s0 ? vx[k] : 0.0;
-        for (int p = k > s0 ? k : s0; p < s1; ++p) acc += v.R[tri(p) + k] * vzc[p];
+        for (int p0 = k > s0 ? k : s0; p0 < s1; p0 += 8) {   // eight rows in flight
+            double r[8], z[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int p = p0 + e < s1 ? p0 + e : s1 - 1;
+                r[e] = v.R[tri(p) + k];
+                z[e] = vzc[p];
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc += p0 + e < s1 ? r[e] * z[e] : 0.0;
+        }
         vx[k] = acc;
     }
     __syncthreads();
@@ -957,7 +1364,7 @@ __device__ void sign_fixed_solve(const Sig& v, int nS, double lam, double* vw, d
     }
     __syncthreads();
     if (FOLD && !v.r_lds && nS <= FOLD_MAX) {   // one pass over a global factor
-        fold_pass_global(v.R, vw, nS, vx, vz, 0.0);
+        fold_pass_global(v.R, vw, nS, vx, vz);
         return;
     }
     if (v.r_lds) {
@@ -1593,7 +2000,7 @@ __global__ __launch_bounds__(256) void grow_kernel(GrowArgs a)
 // workgroup after its write-back: sx / satom hold the support's values and atoms (LDS), xl1 = ||x||_1.
 // Four rows per thread, eight atoms' loads in flight, straight from the atom-major dictionary; a
 // workgroup that finishes its master problem early computes its residual while others still solve.
-__device__ void residual_tail(const Workspace& w, int sig, const float* At, int64_t lda, const float* Bw,
+__device__ __forceinline__ void residual_tail(const Workspace& w, int sig, const float* At, int64_t lda, const float* Bw,
                               const double* sx, const int* satom, int nS, double xl1, double* red)
 {
     const int tid = threadIdx.x;
@@ -1912,7 +2319,7 @@ active_set:
     for (;;) {
         const uint64_t tg = a.phase ? wall_clock64() : 0;
         if (FOLD && glist && nI <= GF_MU * NT && nS <= GF_MS * NT) grad_fold(s, nI, nS, vg, !cert, glist);
-        else grad_slots<BLOCK ? 8 : 4>(s, nI, nS, vg, !cert);
+        else grad_slots<FOLD ? 16 : (BLOCK ? 8 : 4)>(s, nI, nS, vg, !cert);
         sub_ticks(11, tg);
         if (cert) break;
         const uint64_t tv = a.phase ? wall_clock64() : 0;
@@ -2001,7 +2408,27 @@ active_set:
         } else if (zs) {
             append_list(s, nS, s_list, nv, vg, w.n, zs, a.phase ? a.phase + 6 : nullptr);
         } else {
-            for (int e = 0; e < nv; ++e) {
+            int e = 0;
+            if (FOLD && !s.r_lds) {
+                __shared__ FoldLds w_fold;
+                const uint64_t t_in = a.phase ? wall_clock64() : 0;
+                const int e0 = e, top = min(w.n, FOLD_MAX);
+                while (nS < top) {
+                    // the minimiser of the support before comes with the first pass when it isn't known yet
+                    const bool xs = !xs_ok && nS > 0;
+                    const int J = min(min(nv - e, xs ? 7 : 8), top - nS);
+                    if (J < 1) break;
+                    if (nS + J <= 2 * NT) chol_append_fold<2>(s, nS, s_list + e, J, vg, xs, lam, vzc, vx, w_fold);
+                    else chol_append_fold<4>(s, nS, s_list + e, J, vg, xs, lam, vzc, vx, w_fold);
+                    e += J;
+                    xs_ok = xs_ok || xs;
+                }
+                if (a.phase && tid == 0) {
+                    atomicAdd(reinterpret_cast<unsigned long long*>(a.phase + 6), (unsigned long long)(e - e0));
+                    atomicAdd(reinterpret_cast<unsigned long long*>(a.phase + 4), (unsigned long long)(wall_clock64() - t_in));
+                }
+            }
+            for (; e < nv; ++e) {
                 const int u = s_list[e];
                 const signed char th = vg[u] > 0.0 ? 1 : -1;
                 if (nS >= w.n) {
@@ -2009,12 +2436,13 @@ active_set:
                     __syncthreads();
                     continue;
                 }
-                chol_append<FOLD>(s, nS, u, th, vw, vz, red, a.phase ? a.phase + 6 : nullptr);
+                if (FOLD) nS = chol_append_far(s, nS, u, th, vw, vz, red, a.phase ? a.phase + 6 : nullptr);
+                else chol_append(s, nS, u, th, vw, vz, red, a.phase ? a.phase + 6 : nullptr);
             }
         }
         if (xs_ok && nS > nS_before) {
             const uint64_t tsf = a.phase ? wall_clock64() : 0;
-            xstar_after_append(s, nS_before, nS, lam, vw, vzc, vx, red);
+            xstar_after_append(s, nS_before, nS, lam, vw, vzc, vx);
             sub_ticks(10, tsf);
         }
         const int added = nS - nS_before;
@@ -2066,9 +2494,9 @@ active_set:
             __syncthreads();
             // downdate the factor in place (vw is free scratch here); support positions past q move down
             const uint64_t td = a.phase ? wall_clock64() : 0;
-            // the fold kernel's factors are in global memory; with its vectors there too (large supports)
-            // the downdate keeps rows in flight across its barriers
-            if (FOLD && ns_old <= 4 * NT && !is_lds(vzc)) chol_drop_global(s, ns_old, q, vw, vzc);
+            if (FOLD && ns_old <= 2 * NT) chol_drop_rows<2>(s, ns_old, q, vw, vzc);
+            else if (FOLD && ns_old <= 4 * NT) chol_drop_rows<4>(s, ns_old, q, vw, vzc);
+            else if (FOLD) chol_drop_far(s, ns_old, q, vw, vzc);
             else chol_drop<BLOCK ? 8 : 4>(s, ns_old, q, vw, vzc);
             // x* on S \ q: with the removed row b (vw) and its z entry zl, x*_new[k] = x*[k'] - b_k zl
             // (k' the position before the shift)
@@ -2121,7 +2549,8 @@ active_set:
             if (u < nI0 || s_keep[u - nI0]) continue;
             for (int q = tid; q < nS; q += NT) vatom[q] = s.so[q];   // vatom is scratch after the Gram phase
             __syncthreads();
-            chol_drop<BLOCK ? 8 : 4>(s, nS, k, vw, nullptr);
+            if (FOLD) chol_drop_far(s, nS, k, vw, nullptr);
+            else chol_drop<BLOCK ? 8 : 4>(s, nS, k, vw, nullptr);
             for (int q = k + 1 + tid; q < nS; q += NT) s.so[q - 1] = vatom[q];
             --nS;
             __syncthreads();
@@ -2223,7 +2652,7 @@ active_set:
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void solve_kernel(SolveArgs a) { solve_body<false, false>(a); }
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void solve_fold_kernel(SolveArgs a) { solve_body<false, true>(a); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void solve_fold_kernel(SolveArgs a) { solve_body<false, true>(a); }
 __global__ __launch_bounds__(256) void solve_block_kernel(SolveArgs a) { solve_body<true, false>(a); }
 
 // ---------------------------------------------------------------------------

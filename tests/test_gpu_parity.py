@@ -1051,3 +1051,36 @@ def test_host_loop_sizes(p, opts):
             assert torch.equal(ra[key].nan_to_num(), rb[key].nan_to_num()), (key, w is None)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("n,m,c,p,opts", [
+    (250, 2000, 0.005, 5, {}), (270, 2200, 0.004, 4, {}), (300, 2400, 0.003, 3, {"omega": 2}),
+    (540, 4400, 0.004, 3, {}), (600, 4800, 0.002, 3, {"screen": "bf16"}), (1100, 8800, 0.0015, 2, {}),
+    (270, 2200, 0.004, 600, {"graph": True}), (300, 2400, 0.003, 3, {"gram_table": False})])
+def test_supports_beyond_the_lds_factor(n, m, c, p, opts):
+    """Supports that outgrow the LDS factor and cross the 256, 512 and 1024 positions at which the one-pass appends
+    and downdates change their split of the columns, at small lambda so that atoms leave as well as enter: the optimality
+    conditions of the float32 solution in float64.  Rounding x to float32 moves g = A^T (b - A x) by at most
+    |A^T A_S| |x| 2^-24; the kernel's own float64 conditions hold to 1e-4 lambda (its kkt tolerance)."""
+    pk = _lib()
+    At = bi.gaussian_dictionary(n, m, 91)
+    Bt = np.random.default_rng(n).standard_normal((p, n)).astype(np.float32)
+    s = pk.Solver(to_dev(At), c, mode="rel", rho=10, **opts)
+    out = s.solve(to_dev(Bt))
+    out = {k: out[k].cpu().numpy() for k in ("x_idx", "x_val", "supp_len", "lambda", "status")}
+    s.close()
+    A64 = At.astype(np.float64)
+    longest = 0
+    for i in (range(p) if p < 10 else (0, 1, p // 2, p - 1)):
+        k = int(out["supp_len"][i])
+        longest = max(longest, k)
+        idx, val, lam = out["x_idx"][i, :k], out["x_val"][i, :k].astype(np.float64), out["lambda"][i]
+        g = A64 @ (Bt[i].astype(np.float64) - A64[idx].T @ val)
+        tol = np.abs(A64 @ A64[idx].T) @ np.abs(val) * 2.0 ** -24 + 1e-4 * lam
+        assert len(set(idx)) == k
+        if out["status"][i] & 1:      # else: |I| reached its cap of 2 n, or left an atom in the span of S out
+            off = np.ones(m, bool)
+            off[idx] = False
+            assert np.all(np.abs(g)[off] <= lam + tol[off])
+        assert np.all(np.abs(g[idx] - lam * np.sign(val)) <= tol[idx])
+    assert longest > 0.75 * n
