@@ -45,7 +45,8 @@ PEAK_HBM_GBS = 8000.0
 KERNEL_SOURCES = ("paper_1302_5010_amd/csrc/corr_gemm.hip", "paper_1302_5010_amd/csrc/gemm_tile.h")
 
 
-SOLVE_SOURCES = ("paper_1302_5010_amd/csrc/pursuit.hip", "paper_1302_5010_amd/csrc/pursuit.h",
+SOLVE_SOURCES = ("paper_1302_5010_amd/csrc/pursuit.hip", "paper_1302_5010_amd/csrc/pursuit_wave.hip",
+                 "paper_1302_5010_amd/csrc/master_body.h", "paper_1302_5010_amd/csrc/pursuit.h",
                  "paper_1302_5010_amd/csrc/bmpl_internal.h", "paper_1302_5010_amd/csrc/wave_ops.h")
 
 

@@ -99,11 +99,11 @@ typedef enum {
 #define BMPL_FLAG_PHASES 16         /* with TIMING: also count the master-problem kernel's phases, factor
                                        appends, drops and solves (device atomics and clock reads inside the
                                        kernel, which slow it; the per-kernel times of TIMING alone do not) */
-#define BMPL_FLAG_BLOCK_APPEND 8    /* grow the master problem's inverse Cholesky factor in blocks of up
-                                       to 8 atoms when it lives in global memory, instead of one atom at
-                                       a time (same factor in exact arithmetic).  Off by default: on the
-                                       4096-signal ragged batch (1024 x 32768, supports up to ~980)
-                                       single appends take 14.4 s against 17.0 s */
+#define BMPL_FLAG_BLOCK_APPEND 8    /* grow the master problem's inverse Cholesky factor through a Schur
+                                       complement of up to 8 atoms when it lives in global memory, instead
+                                       of one atom after the other from one pass over the factor (same
+                                       factor in exact arithmetic).  Off by default: its passes take
+                                       longer */
 
 /* Tile shapes of the correlation kernel (bmpl_autotune, bmpl_set_tuning), signals x atoms (waves of
  * 64 lanes, each computing the sub-tile in parentheses): 0 128x128 (64x64), 1 256x256 (64x64, 16 waves),

@@ -680,6 +680,7 @@ bmpl_status bmpl_create(const float* A_dev, int64_t lda, int32_t n, int32_t m, b
         // the solve kernels get the largest dynamic LDS the device allows; the budget is the smallest
         size_t dyn = SIZE_MAX;
         for (const void* fn : {reinterpret_cast<const void*>(solve_kernel), reinterpret_cast<const void*>(solve_fold_kernel),
+                               reinterpret_cast<const void*>(solve_fold_far_kernel),
                                reinterpret_cast<const void*>(solve_block_kernel)}) {
             e = hipFuncGetAttributes(&fa, fn);
             if (e != hipSuccess) break;
@@ -692,7 +693,7 @@ bmpl_status bmpl_create(const float* A_dev, int64_t lda, int32_t n, int32_t m, b
             const size_t left = total > fa.sharedSizeBytes + 256 ? total - fa.sharedSizeBytes - 256 : (size_t)0;
             // (the fold kernel's own LDS does not narrow the others': it takes at most VEC_LDS_QUARTER)
             if (fn == reinterpret_cast<const void*>(solve_fold_kernel)) c->lds_fold_max = std::min(left, VEC_LDS_QUARTER);
-            else dyn = std::min(dyn, left);
+            else if (fn != reinterpret_cast<const void*>(solve_fold_far_kernel)) dyn = std::min(dyn, left);
         }
         if (e == hipSuccess) c->lds_dyn_max = dyn;
     }
@@ -1145,8 +1146,7 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         so.vec_lds = vec_bytes + stage <= (rinv_fits ? c->lds_dyn_max : c->lds_fold_max) ? 1 : 0;
         so.rinv_lds = (so.vec_lds && rinv_fits) ? 1 : 0;
         size_t lds = (so.rinv_lds ? rinv_bytes : 0) + (so.vec_lds ? vec_bytes : 0) + stage;
-        // block appends pay off when the factor streams from global memory; with an LDS-resident
-        // factor single appends are cheaper and keep the workgroup's LDS (and occupancy) smaller
+        // the opt-in block appends' scratch, for factors in global memory
         so.zs_lds = (c->block_append && !so.rinv_lds && lds + block_scratch_bytes(kp) <= c->lds_dyn_max) ? 1 : 0;
         if (so.zs_lds) lds += block_scratch_bytes(kp);
         so.act = c->act[idx]; so.n_act_dev = c->n_act_dev + idx;
@@ -1158,7 +1158,14 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         if (so.zs_lds)
             hipLaunchKernelGGL(solve_block_kernel, dim3(n_grid), dim3(256), lds, q, so);
         else if (!so.rinv_lds)
-            hipLaunchKernelGGL(solve_fold_kernel, dim3(n_grid), dim3(256), lds, q, so);
+            hipLaunchKernelGGL(so.vec_lds ? solve_fold_kernel : solve_fold_far_kernel, dim3(n_grid), dim3(256), lds, q, so);
+        // A wave per signal for many small problems: no barriers, and sixteen or more of a CU's signals at once instead
+        // of four; but the products with b and the residual, kpad values long, get a quarter of the threads.
+        // 1024 x 20000, |S| around 8: 4096 signals 3.15 ms per solve with 256 threads and 2.67 with a wave, 2048
+        // signals 2.08 and 1.91, 1024 signals the same; 2048 x 16384, |S| to 30: 2.84 and 2.91 with 4096 signals;
+        // 128 x 512: 8192 signals 2.01 and 1.40, 512 signals 0.53 and 0.51.
+        else if (so.kv <= 64 && c->Q && c->kpad <= 1024 && n_grid >= 2 * c->kpad)
+            hipLaunchKernelGGL(solve_wave_kernel, dim3(n_grid), dim3(64), lds, q, so);
         else
             hipLaunchKernelGGL(solve_kernel, dim3(n_grid), dim3(256), lds, q, so);
         HIPC(hipGetLastError());

@@ -106,9 +106,11 @@ struct PackArgs {
 __global__ void prep_kernel(PrepArgs a);
 __global__ void status_compact_kernel(StatusArgs a);
 __global__ void warm_select_kernel(WarmArgs a);
-__global__ void solve_kernel(SolveArgs a);         // single appends only (zs_lds ignored)
-__global__ void solve_fold_kernel(SolveArgs a);    // solve_kernel with one-pass appends and solves on
-                                                   // factors in global memory (launches with rinv_lds = 0)
+// The master problem, by where the factor and the vectors by slot and position live:
+__global__ void solve_kernel(SolveArgs a);            // both in LDS
+__global__ void solve_wave_kernel(SolveArgs a);       // both in LDS, one wave per signal, |I| <= 64 (pursuit_wave.hip)
+__global__ void solve_fold_kernel(SolveArgs a);       // the factor in global memory (one-pass appends), the vectors in LDS
+__global__ void solve_fold_far_kernel(SolveArgs a);   // both in global memory
 __global__ void solve_block_kernel(SolveArgs a);   // block appends when zs_lds
 __global__ void pack_kernel(PackArgs a);
 __global__ void grow_kernel(GrowArgs a);

@@ -1084,3 +1084,31 @@ def test_supports_beyond_the_lds_factor(n, m, c, p, opts):
             assert np.all(np.abs(g)[off] <= lam + tol[off])
         assert np.all(np.abs(g[idx] - lam * np.sign(val)) <= tol[idx])
     assert longest > 0.75 * n
+
+
+@pytest.mark.parametrize("n,m,p,k,rho,c", [
+    (60, 400, 127, 6, 1, 0.05), (60, 400, 128, 6, 1, 0.05),       # kpad 64: 256 threads, then a wave per signal
+    (64, 500, 700, 20, 7, 0.02), (64, 500, 700, 20, 8, 0.02),     # blocks of 7 and 8, |I| past 64 back to 256 threads
+    (200, 900, 512, 30, 9, 0.03), (200, 900, 60, 40, 20, 0.02),   # a block and a remainder; three blocks
+    (33, 70, 300, 10, 30, 0.01)])                                 # nearly every atom proposed at once
+def test_lds_factor_kernels(n, m, p, k, rho, c):
+    """The kernels of factors in LDS around the sizes at which one takes over from the other, with appends in blocks
+    of up to eight, and with atoms that occur twice (the copy's pivot vanishes: it is left out)."""
+    P = bi.tiny_gaussian(n=n, m=m, p=p, k=k, sigma=0.01, seed=n + rho, lambda_rel=c, rho=rho)
+    rows = sorted(set([0, 1, p // 2, p - 1]) | set(range(2, p, max(1, p // 12))))
+    lam = lam_rel(P.At, P.Bt, c)
+    s, out, ref, lam, st = _solve_and_check(P, rows=rows, lam=lam)
+    pk = _lib()
+    # (a support close to n atoms can stop with an atom of I in its span left out: status 0)
+    both = [q for q, i in enumerate(rows) if st[i] == pk.BMPL_SIG_CONVERGED and ref["status"][q] == oracle.ST_CONVERGED]
+    assert 2 * len(both) > len(rows)
+    sig = [rows[q] for q in both]
+    check_batch(P.At, P.Bt, lam[sig], out, {"X": ref["X"][both]}, gpu_rows=sig)
+    # every atom twice: the same objective, whichever copy carries the coefficient
+    twice = pk.Solver(to_dev(np.repeat(P.At, 2, axis=0)), 0.0, rho=rho)
+    two = twice.solve(to_dev(P.Bt), lam=to_dev(lam))
+    ok = (two["status"] == pk.BMPL_SIG_CONVERGED) & (out["status"] == pk.BMPL_SIG_CONVERGED)
+    assert bool(ok.any())
+    torch.testing.assert_close(two["objective"][ok], out["objective"][ok], rtol=1e-7, atol=0.0)
+    s.close()
+    twice.close()
