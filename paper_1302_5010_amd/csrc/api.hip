@@ -122,8 +122,6 @@ struct bmpl_ctx {
     float* vmax8 = nullptr;       // [p_cap] scratch of the ranking pass
     double* zeros = nullptr;      // [p_cap] zero thresholds for the ranking pass
     int* cert = nullptr;          // [p_cap] left for the certified pass
-    int* cert32 = nullptr;        // [p_cap] float32 product: rows whose stop needs the exact re-score
-    int* n_cert32 = nullptr;      // their count
     int* grow_list = nullptr;     // [p_cap] signals whose slot block grows before the next master problem
     int* n_grow = nullptr;        // their count
     unsigned long long* grow_off = nullptr;   // [p_cap] their new blocks' offsets from arena->grow_base
@@ -307,7 +305,7 @@ void free_signals(bmpl_ctx* c)
     dfree(w.R8); dfree(w.rscale8); dfree(c->cand8); dfree(c->ncand8); dfree(c->vmax8); dfree(c->zeros);
     dfree(c->cert); dfree(c->cert_act); dfree(c->n_cert_dev);
     dfree(c->spill); dfree(c->spill_act); dfree(c->n_spill_dev);
-    dfree(c->cert32); dfree(c->n_cert32); dfree(c->grow_list); dfree(c->n_grow); dfree(c->grow_off);
+    dfree(c->grow_list); dfree(c->n_grow); dfree(c->grow_off);
     dfree(c->beta);
     c->p_cap = 0;
 }
@@ -405,13 +403,10 @@ bmpl_status ensure_workspace(bmpl_ctx* c, int p, int selcap)
     HIPC(dalloc(&c->Gc, P * (size_t)c->ldg));
     HIPC(dalloc(&c->act[0], P));
     HIPC(dalloc(&c->act[1], P));
-    HIPC(dalloc(&c->cert32, P));
-    HIPC(dalloc(&c->n_cert32, 1));
     HIPC(dalloc(&c->grow_list, P));
     HIPC(dalloc(&c->grow_off, P));
     HIPC(dalloc(&c->n_grow, 1));
     HIPC(hipMemset(c->n_grow, 0, sizeof(int)));
-    HIPC(hipMemset(c->n_cert32, 0, sizeof(int)));
     if (c->opt.screen != BMPL_PREC_FP32) {
         HIPC(dalloc(&w.R16, (P + 1) * c->kpad));
         HIPC(hipMemset(w.R16 + P * c->kpad, 0, c->kpad * sizeof(uint16_t)));
@@ -932,7 +927,6 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
     // slot-block reserve for the iterations up to the next read-back (a graph segment at most)
     sa.reserve_iters = full ? 0 : (graph ? GRAPH_DEPTH : 1); sa.rho_pass = rho; sa.slack = slack;
     sa.kcap = max_active;
-    sa.clear_cert = c->n_cert32;
     sa.grow_list = c->grow_list; sa.n_grow = c->n_grow; sa.grow_off = c->grow_off; sa.kmin = kfull;
     hipLaunchKernelGGL(status_compact_kernel, dim3(1), dim3(1024), 0, s, sa);
     HIPC(hipGetLastError());
@@ -1072,21 +1066,10 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         } else if (c->A16) {
             HIPC(screen_pass(c->act[cur], c->n_act_dev + cur));
         } else {
-            a.rr2 = w.rr2; a.band = c->band32; a.cert_list = c->cert32; a.n_cert = c->n_cert32;
+            // with the natural stop certified against the float32 product's rounding
+            a.rr2 = w.rr2; a.band = c->band32;
+            a.At = c->At; a.lda = c->kpad; a.n = c->n; a.R = w.R; a.ldr = c->kpad;
             HIPC(launch_select(a, q));
-            // the natural stop certified against the float32 product's rounding (exact re-score of the
-            // atoms within the band of lambda when nothing was admitted)
-            CertifyArgs cf{};
-            cf.G = c->Gc; cf.ldg = c->ldg; cf.m = c->m;
-            cf.act = c->act[cur]; cf.n_act_dev = c->n_act_dev + cur; cf.p_grid = n_grid;
-            cf.lam = w.lam; cf.rr2 = w.rr2; cf.band = c->band32;
-            cf.excl = w.inI; cf.words = w.words;
-            cf.At = c->At; cf.lda = c->kpad; cf.n = c->n;
-            cf.R = w.R; cf.ldr = c->kpad;
-            cf.k = rho; cf.nI = w.nI; cf.max_active = max_active;
-            cf.sel = w.sel; cf.selcap = w.selcap; cf.nsel = w.nsel; cf.vmax = w.vmax;
-            cf.cert_list = c->cert32; cf.n_cert = c->n_cert32;
-            HIPC(launch_certify(cf, q));
         }
         if (ev) {
             const size_t e1 = mark(c, q);
@@ -1121,8 +1104,10 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
     // |I|'s bound for ordinary passes, where most of I is in S, and smaller after a warm start.
     // `explore`: the pass before selected omega rho candidates (not a warm-start proposal)
     // `ibound`: |I| after this pass's selection is at most this (the LDS vectors are sized by it)
+    // `grow`: a signal may need a larger block (in full depth only before the first master problem, whose blocks
+    // hold the whole solve)
     auto enqueue_master = [&](hipStream_t q, int idx, int n_grid, int kl, int ibound, bool gated,
-                              bool explore) -> bmpl_status {
+                              bool explore, bool grow = true) -> bmpl_status {
         const bool ev = tm && !gated;
         size_t e0 = ev ? mark(c, q) : 0;
         SolveArgs so{};
@@ -1150,9 +1135,11 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         so.zs_lds = (c->block_append && !so.rinv_lds && lds + block_scratch_bytes(kp) <= c->lds_dyn_max) ? 1 : 0;
         if (so.zs_lds) lds += block_scratch_bytes(kp);
         so.act = c->act[idx]; so.n_act_dev = c->n_act_dev + idx;
-        GrowArgs ga{w, c->grow_list, c->n_grow, c->grow_off, slack, max_active, kfull};
-        hipLaunchKernelGGL(grow_kernel, dim3(std::min(n_grid, 512)), dim3(256), 0, q, ga);
-        HIPC(hipGetLastError());
+        if (grow) {
+            GrowArgs ga{w, c->grow_list, c->n_grow, c->grow_off, slack, max_active, kfull};
+            hipLaunchKernelGGL(grow_kernel, dim3(std::min(n_grid, 512)), dim3(256), 0, q, ga);
+            HIPC(hipGetLastError());
+        }
         // factors that start in global memory take the kernel whose appends and solves read them in
         // one pass (its larger register footprint stays out of the LDS-factor kernel)
         if (so.zs_lds)
@@ -1227,7 +1214,7 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
             for (int d = 0; d < max_outer; ++d) {
                 const bool wd = warm && d == 0;   // the master problem on a warm start's proposal
                 im = std::min(max_active, im + (wd ? first_add : rho));
-                bmpl_status r = enqueue_master(q, cc, p, wd ? std::min(im, WARM_KL) : im, im, true, !wd);
+                bmpl_status r = enqueue_master(q, cc, p, wd ? std::min(im, WARM_KL) : im, im, true, !wd, d == 0);
                 if (r != BMPL_OK) return r;
                 r = enqueue_select_pass(q, cc, p, false, wd, true);
                 if (r != BMPL_OK) return r;

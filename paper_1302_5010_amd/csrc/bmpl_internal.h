@@ -35,53 +35,35 @@ struct Arena {
 };
 
 // N chunks of four consecutive correlations of a row per thread (thread t: g[base0 + 1024 q + 4 t ..
-// + 3], q < N) with their bits of the I bitmap (bit set: in I; `absent` for lanes past the vector part
-// of the row, m4, whose values read as zeros).  When every lane's chunks lie inside the row (a test that
-// is the same for the whole workgroup) the loads are unconditional, so all of a thread's loads are in
-// flight at once: a guarded load compiles to a branch that waits for its data at the branch's end.
+// + 3], q < N) with the words of the I bitmap that hold their bits (chunk_bits).  The loads are only issued here:
+// every lane takes clamped indices (lanes past the vector part of the row, m4, read its last entries), no load is
+// guarded (a guarded load compiles to a branch whose end waits for it) and no word is shifted (which would wait for
+// it, and so for the values loaded before it).
 template <int N>
-__device__ __forceinline__ void row_chunks(const float* g, const uint32_t* ex, int base0, int m4, uint32_t absent,
-                                           float4 (&f)[N], uint32_t (&w)[N])
+__device__ __forceinline__ void row_chunks(const float* g, const uint32_t* ex, int base0, int m4, float4 (&f)[N],
+                                           uint32_t (&w)[N])
 {
     const int t4 = 4 * (int)threadIdx.x;
-    if (base0 + 1024 * N <= m4) {
-#pragma unroll
-        for (int q = 0; q < N; ++q) f[q] = *reinterpret_cast<const float4*>(g + base0 + 1024 * q + t4);
-        if (ex) {
-#pragma unroll
-            for (int q = 0; q < N; ++q) {
-                const int j0 = base0 + 1024 * q + t4;
-                w[q] = ex[j0 >> 5] >> (j0 & 31);
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < N; ++q) w[q] = 0u;
-        }
-        return;
-    }
-    // the row's tail: clamped indices, so the loads are still issued together (a guarded load compiles to
-    // a branch whose end waits for it); lanes past the vector part read as zeros
-    if (m4 == 0 || base0 >= m4) {
+    if (base0 >= m4) {   // (m4 = 0 too; the same for the whole workgroup)
 #pragma unroll
         for (int q = 0; q < N; ++q) {
             f[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-            w[q] = absent;
+            w[q] = 0u;
         }
         return;
     }
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
-        const int j0 = base0 + 1024 * q + t4;
-        const int jl = j0 < m4 ? j0 : m4 - 4;
-        f[q] = *reinterpret_cast<const float4*>(g + jl);
-        w[q] = ex ? (ex[jl >> 5] >> (jl & 31)) : 0u;
-    }
+    for (int q = 0; q < N; ++q) f[q] = *reinterpret_cast<const float4*>(g + min(base0 + 1024 * q + t4, m4 - 4));
+    // (without a bitmap the row's own words, which chunk_bits' mask drops: the number of loads stays known)
+    const uint32_t* words = ex ? ex : reinterpret_cast<const uint32_t*>(g);
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
-        const bool in = base0 + 1024 * q + t4 < m4;
-        f[q] = in ? f[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-        w[q] = in ? w[q] : absent;
-    }
+    for (int q = 0; q < N; ++q) w[q] = words[min(base0 + 1024 * q + t4, m4 - 4) >> 5];
+}
+
+// The bits of the chunk at j0 from its word: set for entries in I (none without a bitmap), all set past m4.
+__device__ __forceinline__ uint32_t chunk_bits(const uint32_t* ex, uint32_t w, int j0, int m4)
+{
+    return j0 < m4 ? (ex ? w >> (j0 & 31) : 0u) : 0xFu;
 }
 
 // One signal's slot block for capacity K (slots of I) and signal length n:
@@ -217,28 +199,14 @@ struct SelectArgs {
     // pursuit bookkeeping (may be null in the diagnostic entry point)
     const int* nI; int max_active;
     int* clear_count;      // set to 0 by workgroup 0 before anything else (or null)
-    // float32 band (0 = off): signals whose stop needs the exact re-score are appended (their rows)
-    const double* rr2; double band; int* cert_list; int* n_cert;
-};
-hipError_t launch_select(const SelectArgs& a, hipStream_t stream);
-
-// Certification of the natural stop under the float32 product (select.hip): for running signals whose
-// selection admitted nothing, the atoms whose float32 |g~| lies within eps_i = band sqrt(rr2[sig]) of
-// lambda are re-scored exactly (float32 data, float64 sums); exact violators are admitted (sel, nsel),
-// otherwise vmax becomes the exact maximum over them.
-struct CertifyArgs {
-    const float* G; int64_t ldg; int m;     // the float32 product, one row per running signal
-    const int* act; const int* n_act_dev; int p_grid;
-    const double* lam; const double* rr2;   // lambda_i and ||xi_i||^2
-    double band;                            // eps_i = band ||xi_i||
-    const uint32_t* excl; int words;        // I bitmaps
+    // float32 band (0 = off) ||xi_i||^2 and eps_i = band ||xi_i||: signals whose stop lies within it get the exact
+    // re-score of the atoms whose |g~| lies within eps_i of lambda (float32 data, float64 sums); exact violators
+    // are admitted, otherwise vmax becomes the exact maximum over them
+    const double* rr2; double band;
     const float* At; int64_t lda; int n;    // float32 atoms
     const float* R; int64_t ldr;            // float32 residuals (row per signal)
-    int k; const int* nI; int max_active;
-    int* sel; int selcap; int* nsel; float* vmax;
-    const int* cert_list; const int* n_cert;   // the rows the selection listed
 };
-hipError_t launch_certify(const CertifyArgs& a, hipStream_t stream);
+hipError_t launch_select(const SelectArgs& a, hipStream_t stream);
 
 // Reduced-precision screening (screen.hip).
 struct ScreenArgs {

@@ -36,7 +36,6 @@ struct StatusArgs {
     // slot-block reserve: the doubles the kept signals may request from the arena during the next
     // reserve_iters outer iterations (rho_pass slots each at most), written to arena->reserve
     int reserve_iters; int rho_pass; int slack; int kcap;
-    int* clear_cert;    // the selection's certification list count, set to 0 at the end (or null)
     int* grow_list; int* n_grow;   // kept signals whose block must grow for this pass's selection
     unsigned long long* grow_off;  // their new blocks' offsets from arena->grow_base (one fetch-and-add)
     int kmin;                      // smallest capacity handed out (as GrowArgs::kmin)

@@ -133,94 +133,148 @@ __global__ __launch_bounds__(1024) void status_compact_kernel(StatusArgs a)
     __syncthreads();
     unsigned long long res = 0;   // this thread's share of the slot-block reserve
     int mbk = 0;                  // largest support bucket among this thread's kept signals
-    for (int r0 = 0; r0 < n_in; r0 += 1024) {
-        const int r = r0 + threadIdx.x;
-        int keep = 0, sig = -1;
-        if (r < n_in) {
-            sig = a.act_in ? a.act_in[r] : r;
-            int st = w.status[sig];
-            if (a.initial) {
-                keep = !(st & BMPL_SIG_NONFINITE);
-            } else {
-                const double lam = w.lam[sig];
-                const int ns = w.nsel[sig];
-                const double vm = (double)w.vmax[sig];
-                const int it = w.iters[sig];
-                if (it == 0) w.g0max[sig] = w.vmax[sig];   // first pass: I is empty, so this is ||A^T b||_inf
-                const bool natural = ns == 0 && vm <= lam;
-                bool early = false;
-                if (!natural) {
-                    const double bb = w.bnorm2[sig];
-                    if (a.r_inf_rel > 0.0 && vm <= a.r_inf_rel * (double)w.g0max[sig])
-                        early = true;                                             // Eq. (10), correlations
-                    else if (a.r2_rel > 0.0 && sqrt(w.rr2[sig]) <= a.r2_rel * sqrt(bb))
-                        early = true;                                             // Eq. (10), residual norm
-                    else if (a.eps_early > 0.0 && it >= 1 &&
-                             fabs(w.obj_prev[sig] - w.obj[sig]) <= a.eps_early * a.rho * bb)
-                        early = true;                                             // Eq. (13)
-                }
-                const bool halt = (st & ST_HALT) != 0;   // the solve kernel stopped it (reported inexact)
-                st &= ~ST_HALT;
-                if (ns == 0 || it >= a.max_outer || early || halt) {
-                    double off = vm - lam;
-                    off = off > 0.0 ? off : 0.0;
-                    double kk = fmax(off, w.kkt_on[sig]);
-                    kk = lam > 0.0 ? kk / lam : kk;
-                    w.kkt[sig] = kk;
-                    if (a.warm_check && ns != 0) st |= BMPL_SIG_FALLBACK;
-                    if (halt) {
-                        // INEXACT is set already
-                    } else if (natural) {
-                        if (kk <= a.kkt_tol) st |= BMPL_SIG_CONVERGED;
-                    } else if (early) {
-                        st |= BMPL_SIG_EARLY;
-                    } else if (ns == 0) {
-                        if (!(st & BMPL_SIG_INEXACT)) st |= BMPL_SIG_CAP_ACTIVE;
-                    } else {
-                        st |= BMPL_SIG_CAP_ITERS;
-                    }
-                    w.status[sig] = st;
-                    if (ns != 0) w.nsel[sig] = 0;
+    // RPT signals per thread at a time (thread t: r0 + 1024 j + t): their state is loaded together, so a long list
+    // waits for memory a few times and not once per 1024 signals (8192 signals: 62 us a call with one at a time)
+    auto round = [&](auto rpt, int r0) {
+        constexpr int RPT = decltype(rpt)::value;
+        int sg[RPT], st[RPT], ns[RPT], it[RPT], nI[RPT], nS[RPT], cap[RPT], keep[RPT];
+        double lam[RPT];
+        float vm[RPT];
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {          // clamped, so that no load is guarded
+            const int r = min(r0 + 1024 * j + (int)threadIdx.x, n_in - 1);
+            sg[j] = a.act_in ? a.act_in[r] : r;
+        }
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            st[j] = w.status[sg[j]];
+            ns[j] = w.nsel[sg[j]];
+            it[j] = w.iters[sg[j]];
+            nI[j] = w.nI[sg[j]];
+            nS[j] = w.nS[sg[j]];
+            cap[j] = w.cap[sg[j]];
+            lam[j] = w.lam[sg[j]];
+            vm[j] = w.vmax[sg[j]];
+        }
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            const int sig = sg[j];
+            keep[j] = 0;
+            if (r0 + 1024 * j + (int)threadIdx.x < n_in) {
+                if (a.initial) {
+                    keep[j] = !(st[j] & BMPL_SIG_NONFINITE);
                 } else {
-                    if (a.warm_check) w.status[sig] = st | BMPL_SIG_FALLBACK;
-                    keep = 1;
+                    int s1 = st[j];
+                    const double vmd = (double)vm[j];
+                    if (it[j] == 0) w.g0max[sig] = vm[j];   // first pass: I is empty, so this is ||A^T b||_inf
+                    const bool natural = ns[j] == 0 && vmd <= lam[j];
+                    bool early = false;
+                    if (!natural && (a.r_inf_rel > 0.0 || a.r2_rel > 0.0 || a.eps_early > 0.0)) {
+                        const double bb = w.bnorm2[sig];
+                        const float g0 = it[j] == 0 ? vm[j] : w.g0max[sig];
+                        if (a.r_inf_rel > 0.0 && vmd <= a.r_inf_rel * (double)g0)
+                            early = true;                                             // Eq. (10), correlations
+                        else if (a.r2_rel > 0.0 && sqrt(w.rr2[sig]) <= a.r2_rel * sqrt(bb))
+                            early = true;                                             // Eq. (10), residual norm
+                        else if (a.eps_early > 0.0 && it[j] >= 1 &&
+                                 fabs(w.obj_prev[sig] - w.obj[sig]) <= a.eps_early * a.rho * bb)
+                            early = true;                                             // Eq. (13)
+                    }
+                    const bool halt = (s1 & ST_HALT) != 0;   // the solve kernel stopped it (reported inexact)
+                    s1 &= ~ST_HALT;
+                    if (ns[j] == 0 || it[j] >= a.max_outer || early || halt) {
+                        double off = vmd - lam[j];
+                        off = off > 0.0 ? off : 0.0;
+                        double kk = fmax(off, w.kkt_on[sig]);
+                        kk = lam[j] > 0.0 ? kk / lam[j] : kk;
+                        w.kkt[sig] = kk;
+                        if (a.warm_check && ns[j] != 0) s1 |= BMPL_SIG_FALLBACK;
+                        if (halt) {
+                            // INEXACT is set already
+                        } else if (natural) {
+                            if (kk <= a.kkt_tol) s1 |= BMPL_SIG_CONVERGED;
+                        } else if (early) {
+                            s1 |= BMPL_SIG_EARLY;
+                        } else if (ns[j] == 0) {
+                            if (!(s1 & BMPL_SIG_INEXACT)) s1 |= BMPL_SIG_CAP_ACTIVE;
+                        } else {
+                            s1 |= BMPL_SIG_CAP_ITERS;
+                        }
+                        w.status[sig] = s1;
+                        if (ns[j] != 0) w.nsel[sig] = 0;
+                    } else {
+                        if (a.warm_check) w.status[sig] = s1 | BMPL_SIG_FALLBACK;
+                        keep[j] = 1;
+                    }
+                }
+            }
+            if (keep[j]) mbk = max(mbk, min(3, nS[j] / 256));
+            const bool grows = keep[j] && a.grow_list && nI[j] + ns[j] > cap[j];
+            const unsigned long long gb = __ballot(grows);
+            if (gb) {   // the same on every lane
+                // their blocks grow before the master problem; the new blocks of the whole list are placed here
+                // with one fetch-and-add on the arena's offset (below), each at its share of the total: a sum
+                // over the wave's lanes before, and one LDS atomic per wave
+                const int ln = threadIdx.x & 63;
+                const int K2 = max(grow_capacity(cap[j], nI[j] + ns[j], a.slack, a.kcap), min(a.kmin, a.kcap));
+                const unsigned long long sz = grows ? (unsigned long long)block_doubles(K2, w.n) : 0ull;
+                unsigned long long inc = sz;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const unsigned long long up = __shfl_up(inc, o);
+                    inc += ln >= o ? up : 0ull;
+                }
+                int e0 = 0;
+                unsigned long long off0 = 0;
+                if (ln == 63) {
+                    e0 = atomicAdd(&s_ng, __popcll(gb));
+                    off0 = atomicAdd(&s_goff, inc);
+                }
+                e0 = __shfl(e0, 63);
+                off0 = __shfl(off0, 63);
+                if (grows) {
+                    const int e = e0 + __popcll(gb & ((1ull << ln) - 1ull));
+                    a.grow_list[e] = sig;
+                    a.grow_off[e] = off0 + inc - sz;
+                }
+            }
+            if (keep[j] && a.reserve_iters > 0) {
+                // the blocks this signal may take while its |I| grows by up to reserve_iters * rho_pass slots
+                int Kc = cap[j];
+                const int target = min(a.kcap, nI[j] + a.reserve_iters * a.rho_pass);
+                while (Kc < target) {
+                    Kc = grow_capacity(Kc, min(target, Kc + a.rho_pass), a.slack, a.kcap);
+                    res += (unsigned long long)block_doubles(Kc, w.n);
                 }
             }
         }
-        if (keep) mbk = max(mbk, min(3, w.nS[sig] / 256));
-        if (keep && a.grow_list && w.nI[sig] + w.nsel[sig] > w.cap[sig]) {
-            // its block grows before the master problem; the new blocks of the whole list are placed here
-            // with one fetch-and-add on the arena's offset (below), each at its share of the total
-            const int K2 = max(grow_capacity(w.cap[sig], w.nI[sig] + w.nsel[sig], a.slack, a.kcap),
-                               min(a.kmin, a.kcap));
-            const int e = atomicAdd(&s_ng, 1);
-            a.grow_list[e] = sig;
-            a.grow_off[e] = atomicAdd(&s_goff, (unsigned long long)block_doubles(K2, w.n));
-        }
-        if (keep && a.reserve_iters > 0) {
-            // the blocks this signal may take while its |I| grows by up to reserve_iters * rho_pass slots
-            int Kc = w.cap[sig];
-            const int target = min(a.kcap, w.nI[sig] + a.reserve_iters * a.rho_pass);
-            while (Kc < target) {
-                Kc = grow_capacity(Kc, min(target, Kc + a.rho_pass), a.slack, a.kcap);
-                res += (unsigned long long)block_doubles(Kc, w.n);
-            }
-        }
-        // order-preserving compaction: position = kept signals before this one in the round (a ballot
-        // within the wave, the counts of the earlier waves from LDS), two barriers per round
+        // order-preserving compaction: position = kept signals before this one (a ballot within the wave, the
+        // counts of the earlier waves and rows from LDS), two barriers
         const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-        const unsigned long long bal = __ballot(keep);
-        if (lane == 0) s_scan[wv] = __popcll(bal);
-        __syncthreads();
-        int before = s_base, total = 0;
-        for (int q = 0; q < 16; ++q) {
-            const int c = s_scan[q];
-            before += q < wv ? c : 0;
-            total += c;
+        unsigned long long bal[RPT];
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            bal[j] = __ballot(keep[j]);
+            if (lane == 0) s_scan[16 * j + wv] = __popcll(bal[j]);
         }
-        if (keep) a.act_out[before + __popcll(bal & ((1ull << lane) - 1ull))] = sig;
+        __syncthreads();
+        int total = 0;
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            int before = s_base + total;
+            for (int q = 0; q < 16; ++q) {
+                const int c = s_scan[16 * j + q];
+                before += q < wv ? c : 0;
+                total += c;
+            }
+            if (keep[j]) a.act_out[before + __popcll(bal[j] & ((1ull << lane) - 1ull))] = sg[j];
+        }
         __syncthreads();   // every wave has read s_scan and s_base
         if (threadIdx.x == 0) s_base += total;
+    };
+    if (n_in <= 1024) {
+        if (n_in > 0) round(std::integral_constant<int, 1>{}, 0);
+    } else {
+        for (int r0 = 0; r0 < n_in; r0 += 4096) round(std::integral_constant<int, 4>{}, r0);
     }
     if (mbk > 0) atomicMax(&s_maxb, mbk);
     __syncthreads();
@@ -268,7 +322,6 @@ __global__ __launch_bounds__(1024) void status_compact_kernel(StatusArgs a)
         *a.n_out_dev = s_base;
         if (a.n_grow) *a.n_grow = s_ng;
         if (s_ng > 0) w.arena->grow_base = atomicAdd(&w.arena->top, s_goff);
-        if (a.clear_cert) *a.clear_cert = 0;   // this pass's certification list is consumed
     }
     if (a.reserve_iters > 0) {
         for (int o = 32; o > 0; o >>= 1) res += __shfl_xor(res, o);

@@ -28,22 +28,18 @@ __device__ inline bool better(float v, int i, float w, int j)
 }
 
 // With a float32 band: a signal that admitted nothing although it had room, and whose largest |g~| is
-// within its band eps_i of lambda, is listed for the exact re-score of certify_kernel.
-__device__ inline void list_for_certification(const SelectArgs& a, int row, int sig, int k, int nsel, float vmax,
-                                              double lam)
+// within its band eps_i of lambda, takes the exact re-score of certify_row.
+__device__ inline bool needs_certification(const SelectArgs& a, int sig, int k, int nsel, float vmax, double lam)
 {
-    if (a.band > 0.0 && nsel == 0 && k > 0 && (double)vmax + a.band * sqrt(a.rr2[sig]) > lam)
-        a.cert_list[atomicAdd(a.n_cert, 1)] = row;
+    return a.band > 0.0 && nsel == 0 && k > 0 && (double)vmax + a.band * sqrt(a.rr2[sig]) > lam;
 }
 
+// The selection of one signal; *certify is set by thread 0.
+// Latency bounds it, not the bytes: 1024 rows of 16 384 are 22 us (3 TB/s), a short row 8 us (10.6 before the loads of
+// its tail were issued together and the words of the bitmap stopped waiting for the values before them).
 template <int KMAX>
-__global__ __launch_bounds__(256) void select_kernel(SelectArgs a)
+__device__ __forceinline__ void select_row(const SelectArgs& a, int row, int sig, bool* certify)
 {
-    if (a.clear_count && blockIdx.x == 0 && threadIdx.x == 0) *a.clear_count = 0;   // a later kernel's list
-    const int n_act = a.n_act_dev ? *a.n_act_dev : a.p_grid;
-    const int row = blockIdx.x;
-    if (row >= n_act) return;
-    const int sig = a.act ? a.act[row] : row;
     const float* g = a.G + (int64_t)row * a.ldg;
     const uint32_t* ex = a.excl ? a.excl + (int64_t)sig * a.words : nullptr;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -69,14 +65,14 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a)
     constexpr int CH = 8;
     float4 f0[CH];
     uint32_t w0[CH];
-    row_chunks<CH>(g, ex, 0, m4, 0xFu, f0, w0);   // 4 atoms share one word; 0xF: absent
+    row_chunks<CH>(g, ex, 0, m4, f0, w0);   // 4 atoms share one word
     // The rest of the row streams in chunks of CS float4 per thread, each chunk's loads issued one chunk
     // ahead (the first before the bound is computed), so a workgroup waits for memory about once.
     constexpr int CS = 4;
     float4 fa[CS];
     uint32_t wa[CS];
     auto load_chunk = [&](int base0, float4 (&f)[CS], uint32_t (&word)[CS]) {
-        row_chunks<CS>(g, ex, base0, m4, 0xFu, f, word);
+        row_chunks<CS>(g, ex, base0, m4, f, word);
     };
     load_chunk(1024 * CH, fa, wa);
 
@@ -111,6 +107,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a)
     float tmax = -1.f;
 #pragma unroll
     for (int q = 0; q < CH; ++q) {
+        w0[q] = chunk_bits(ex, w0[q], 4 * tid + 1024 * q, m4);
         if (!(w0[q] & 1u)) tmax = fmaxf(tmax, fabsf(f0[q].x));
         if (!(w0[q] & 2u)) tmax = fmaxf(tmax, fabsf(f0[q].y));
         if (!(w0[q] & 4u)) tmax = fmaxf(tmax, fabsf(f0[q].z));
@@ -166,38 +163,37 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a)
             if (t && pos < CAP) { s_cv[pos] = v; s_ci[pos] = j; }
         };
         auto ok = [&](float v) { return v > lamf && v >= T; };
+        // Most groups of four hold neither an entry nor a value above the largest of the registered ones: one
+        // comparison of their largest value decides that for the wave.
+        const float quick = fminf(fmaxf(T, lamf), wave_max(vmx));
+        auto four = [&](const float4& f, uint32_t w, int j0) {
+            const float v0 = fabsf(f.x), v1 = fabsf(f.y), v2 = fabsf(f.z), v3 = fabsf(f.w);
+            if (!__ballot(fmaxf(fmaxf(v0, v1), fmaxf(v2, v3)) >= quick)) return;
+            if (!(w & 1u)) vmx = fmaxf(vmx, v0);
+            if (!(w & 2u)) vmx = fmaxf(vmx, v1);
+            if (!(w & 4u)) vmx = fmaxf(vmx, v2);
+            if (!(w & 8u)) vmx = fmaxf(vmx, v3);
+            take(!(w & 1u) && ok(v0), j0, v0);
+            take(!(w & 2u) && ok(v1), j0 + 1, v1);
+            take(!(w & 4u) && ok(v2), j0 + 2, v2);
+            take(!(w & 8u) && ok(v3), j0 + 3, v3);
+        };
 #pragma unroll
-        for (int q = 0; q < CH; ++q) {
-            const int j0 = 4 * tid + 1024 * q;
-            take(!(w0[q] & 1u) && ok(fabsf(f0[q].x)), j0, fabsf(f0[q].x));
-            take(!(w0[q] & 2u) && ok(fabsf(f0[q].y)), j0 + 1, fabsf(f0[q].y));
-            take(!(w0[q] & 4u) && ok(fabsf(f0[q].z)), j0 + 2, fabsf(f0[q].z));
-            take(!(w0[q] & 8u) && ok(fabsf(f0[q].w)), j0 + 3, fabsf(f0[q].w));
-        }
-        // every lane runs the same number of steps (the ballots need the whole wave)
-        for (int base0 = 1024 * CH; base0 < m4; base0 += 1024 * CS) {
-            const int base = base0 + 4 * tid;
+        for (int q = 0; q < CH; ++q) four(f0[q], w0[q], 4 * tid + 1024 * q);
+        // two chunks that take turns by name (a copied register would wait for its load); every lane runs the same
+        // number of steps (the ballots need the whole wave)
+        auto chunk = [&](const float4 (&f)[CS], const uint32_t (&w)[CS], int base0) {
+#pragma unroll
+            for (int q = 0; q < CS; ++q) four(f[q], chunk_bits(ex, w[q], base0 + 4 * tid + 1024 * q, m4), base0 + 4 * tid + 1024 * q);
+        };
+        for (int base0 = 1024 * CH; base0 < m4; base0 += 2 * 1024 * CS) {
             float4 fb[CS];
             uint32_t wb[CS];
             load_chunk(base0 + 1024 * CS, fb, wb);   // the next chunk (past the row: zeros, no load)
-#pragma unroll
-            for (int q = 0; q < CS; ++q) {
-                const int j0 = base + 1024 * q;
-                const float v0 = fabsf(fa[q].x), v1 = fabsf(fa[q].y), v2 = fabsf(fa[q].z), v3 = fabsf(fa[q].w);
-                if (!(wa[q] & 1u)) vmx = fmaxf(vmx, v0);
-                if (!(wa[q] & 2u)) vmx = fmaxf(vmx, v1);
-                if (!(wa[q] & 4u)) vmx = fmaxf(vmx, v2);
-                if (!(wa[q] & 8u)) vmx = fmaxf(vmx, v3);
-                take(!(wa[q] & 1u) && ok(v0), j0, v0);
-                take(!(wa[q] & 2u) && ok(v1), j0 + 1, v1);
-                take(!(wa[q] & 4u) && ok(v2), j0 + 2, v2);
-                take(!(wa[q] & 8u) && ok(v3), j0 + 3, v3);
-            }
-#pragma unroll
-            for (int q = 0; q < CS; ++q) {
-                fa[q] = fb[q];
-                wa[q] = wb[q];
-            }
+            chunk(fa, wa, base0);
+            if (base0 + 1024 * CS >= m4) break;
+            load_chunk(base0 + 2 * 1024 * CS, fa, wa);
+            chunk(fb, wb, base0 + 1024 * CS);
         }
         for (int j0 = m4; j0 < a.m; j0 += 256) {
             const int j = j0 + tid;
@@ -227,7 +223,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a)
                 const float vm = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
                 a.nsel[sig] = nsel;
                 a.vmax[sig] = vm;
-                list_for_certification(a, row, sig, k, nsel, vm, lam);
+                *certify = needs_certification(a, sig, k, nsel, vm, lam);
             }
             return;
         }
@@ -259,7 +255,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a)
                 const float vm = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
                 a.nsel[sig] = nsel;
                 a.vmax[sig] = vm;
-                list_for_certification(a, row, sig, k, nsel, vm, lam);
+                *certify = needs_certification(a, sig, k, nsel, vm, lam);
             }
             return;
         }
@@ -303,7 +299,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a)
         if (tid == 0) {
             a.nsel[sig] = nsel;
             a.vmax[sig] = vmax_all;
-            list_for_certification(a, row, sig, k, nsel, vmax_all, lam);
+            *certify = needs_certification(a, sig, k, nsel, vmax_all, lam);
         }
         return;
     }
@@ -318,20 +314,8 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a)
 // with none, vmax becomes the largest exact value (<= lambda), so the stop and the certificate's
 // off-I term are exact.  The row is swept in chunks of the LDS buffer, so any number of atoms in the
 // band is handled; at most EXB exact violators are kept (the lowest-indexed ones, all of them violators).
-// The signals come from the list the selection kernel wrote (usually empty or a handful), so a fixed
-// small grid loops over it.
-__device__ void certify_row(const CertifyArgs& a, int row, int sig);
-
-__global__ __launch_bounds__(256) void certify_kernel(CertifyArgs a)
-{
-    const int n_list = *a.n_cert;
-    for (int li = blockIdx.x; li < n_list; li += gridDim.x) {
-        const int row = a.cert_list[li];
-        certify_row(a, row, a.act ? a.act[row] : row);
-    }
-}
-
-__device__ void certify_row(const CertifyArgs& a, int row, int sig)
+// (Usually no signal or a handful of them: a kernel of its own over their list took longer to launch, 4 us a pass.)
+__device__ __forceinline__ void certify_row(const SelectArgs& a, int row, int sig)
 {
     int k = a.k;
     if (a.nI && a.max_active > 0) {
@@ -414,18 +398,23 @@ __device__ void certify_row(const CertifyArgs& a, int row, int sig)
         // with no violator every exact |g_j| is <= lambda: round down, so the stop test in float64 holds
         a.vmax[sig] = nsel > 0 ? (float)vmx : __double2float_rd(vmx);
     }
-    __syncthreads();   // the shared buffers are reused for the next listed signal
+}
+
+template <int KMAX>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void select_kernel(SelectArgs a)
+{
+    __shared__ bool s_certify;
+    if (a.clear_count && blockIdx.x == 0 && threadIdx.x == 0) *a.clear_count = 0;   // a later kernel's list
+    const int n_act = a.n_act_dev ? *a.n_act_dev : a.p_grid;
+    const int row = blockIdx.x;
+    if (row >= n_act) return;
+    const int sig = a.act ? a.act[row] : row;
+    select_row<KMAX>(a, row, sig, &s_certify);
+    __syncthreads();
+    if (s_certify) certify_row(a, row, sig);
 }
 
 }  // namespace
-
-hipError_t launch_certify(const CertifyArgs& a, hipStream_t stream)
-{
-    if (a.p_grid <= 0) return hipSuccess;
-    if (a.k <= 0 || a.k > a.selcap) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(certify_kernel, dim3(a.p_grid < 64 ? a.p_grid : 64), dim3(256), 0, stream, a);
-    return hipGetLastError();
-}
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t stream)
 {

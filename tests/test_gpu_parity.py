@@ -1112,3 +1112,23 @@ def test_lds_factor_kernels(n, m, p, k, rho, c):
     torch.testing.assert_close(two["objective"][ok], out["objective"][ok], rtol=1e-7, atol=0.0)
     s.close()
     twice.close()
+
+
+@pytest.mark.parametrize("p", [1024, 1025, 4097, 9000])
+@pytest.mark.parametrize("graph", [False, True])
+def test_long_running_lists(p, graph):
+    """The stop test's rounds over long lists (1024 signals, then 4096 at a time): the same signals in slices of 700
+    give the same results, whatever their place in the list."""
+    pk = _lib()
+    n, m = 32, 130
+    At = to_dev(bi.gaussian_dictionary(n, m, 17))
+    Bt = torch.randn(p, n, generator=torch.Generator().manual_seed(p)).cuda()
+    Bt[:: 97, 3] = float("nan")
+    s = pk.Solver(At, 0.3, mode="rel", rho=3, graph=graph)
+    whole = s.solve(Bt)
+    for a in range(0, p, 700):
+        part = s.solve(Bt[a:a + 700].contiguous())
+        for key in ("x_idx", "supp_len", "iters", "status"):
+            assert torch.equal(part[key], whole[key][a:a + 700]), (key, a)
+        torch.testing.assert_close(part["objective"], whole["objective"][a:a + 700], rtol=1e-12, atol=0.0, equal_nan=True)
+    s.close()
