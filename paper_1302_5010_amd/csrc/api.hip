@@ -162,7 +162,14 @@ struct bmpl_ctx {
 
     // correlation tile shape per running-signal bucket (>= 512, 64..511, < 64), set by bmpl_autotune
     int corr_shape[3] = {0, 3, 4};
-    int corr_variant(int n_act) const { return corr_shape[n_act >= 512 ? 0 : (n_act >= 64 ? 1 : 2)]; }
+    bool shape_set[3] = {false, false, false};   // timed or set; else by the size (corr_default_shape)
+    int corr_variant(int n_act) const
+    {
+        const int b = n_act >= 512 ? 0 : (n_act >= 64 ? 1 : 2);
+        return shape_set[b] || A8 ? corr_shape[b] : corr_default_shape(A16 != nullptr, m, kpad, n_act);
+    }
+    // the shape of a captured segment's bucket, whose count is known on the device only, p at most
+    int bucket_variant(int b, int p) const { return b == 2 ? corr_shape[2] : corr_variant(b == 1 ? std::min(p, 511) : p); }
 
     // bmpl_correlate's staged residuals, diag_cap + 1 rows: float32 (float32 product, and the e4m3 one's source),
     // bfloat16 or e4m3 with its scales.  Kept between calls; a call on another stream than the last one waits
@@ -467,7 +474,7 @@ template <class F>
 bmpl_status segment_graph(bmpl_ctx* c, int p, int cur, int i0, int kl, int variant, hipGraphExec_t* out,
                           F&& enqueue)
 {
-    bmpl_ctx::GraphKey key{p, cur, i0, kl, {c->corr_shape[0], c->corr_shape[1], c->corr_shape[2]}, c->ws_gen,
+    bmpl_ctx::GraphKey key{p, cur, i0, kl, {c->bucket_variant(0, p), c->bucket_variant(1, p), c->bucket_variant(2, p)}, c->ws_gen,
                            variant};
     for (auto& e : c->graphs)
         if (e.key == key) {
@@ -970,7 +977,7 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
                     if (b == 1 && merge_mid) continue;
                     const int grid = std::min(n_grid, hi[b] - 1);
                     if (grid < lo[b]) continue;
-                    const hipError_t e = gemm(c->corr_shape[b], grid, lo[b], hi[b]);
+                    const hipError_t e = gemm(c->bucket_variant(b, n_grid), grid, lo[b], hi[b]);
                     if (e != hipSuccess) return e;
                 }
                 return hipSuccess;
@@ -1400,6 +1407,7 @@ bmpl_status bmpl_autotune(bmpl_ctx* c, int32_t p, int32_t* shapes, double* ms, v
                 if (t > 0.0 && t < best) {
                     best = t;
                     c->corr_shape[b] = v;
+                    c->shape_set[b] = true;
                 }
             }
             if (ms) ms[b * CORR_VARIANTS + v] = t;
@@ -1419,7 +1427,10 @@ bmpl_status bmpl_set_tuning(bmpl_ctx* c, const int32_t* shapes)
     for (int b = 0; b < 3; ++b)
         if (shapes[b] < 0 || shapes[b] >= CORR_VARIANTS || (shapes[b] >= 8 && shapes[b] <= 10 && !bf16_only))
             return fail(BMPL_E_INVALID, "bmpl_set_tuning: shape %d out of range for this precision", shapes[b]);
-    for (int b = 0; b < 3; ++b) c->corr_shape[b] = shapes[b];
+    for (int b = 0; b < 3; ++b) {
+        c->corr_shape[b] = shapes[b];
+        c->shape_set[b] = true;
+    }
     return BMPL_OK;
 }
 

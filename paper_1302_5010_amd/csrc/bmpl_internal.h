@@ -161,6 +161,7 @@ struct Workspace {
 // `variant` selects the tile shape (see corr_shape_name; 8..10 exist for bfloat16 only).
 constexpr int CORR_VARIANTS = 15;  // == BMPL_CORR_SHAPES (8..10: bfloat16 only)
 const char* corr_shape_name(int variant);
+int corr_default_shape(bool bf16, int m, int kpad, int p);   // float32 or bfloat16 product of p signals
 hipError_t launch_corr_gemm_f32(int variant, const float* At, int64_t lda, int m, int kpad,
                                 const float* Rbuf, int64_t ldr, const int* act,
                                 const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row,

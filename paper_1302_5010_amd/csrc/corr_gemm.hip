@@ -641,6 +641,32 @@ const char* corr_shape_name(int v)
     }
 }
 
+// The tile shape of p signals when none was set.  A launch takes rounds of tiles over the card's 256 CUs, so the best
+// shape follows from how many rounds its tile count leaves: each candidate's time is modelled as a start plus
+// the rounds times a round's time, both measured at kpad = 2048 and scaled by kpad.  Measured at 1000 signals
+// (us): float32, 1024 x 20000: shape 13 337, 5 363, 12 493 (two rounds for 316 tiles); 2048 x 16384: 12 491, 13 521,
+// 5 572, and 0, which every batch from 512 on took, 542; bfloat16: 62, 79, 75 and 77, 117, 75 (11: 72).  100 signals
+// of 512 x 4096, float32: 4 18, 5 19, 3 27; 64: 4 13.5, 5 18, 3 26.5; 40 signals of 2048 x 16384: 5 56, 4 93.
+int corr_default_shape(bool bf16, int m, int kpad, int p)
+{
+    struct Shape { int id, bm, bn, at_once; double start, round; };
+    static const Shape f32[] = {{5, 64, 64, 256, 20.0, 34.5}, {3, 64, 128, 256, 20.0, 67.0},
+                                {13, 128, 128, 256, 20.0, 126.0}, {12, 256, 256, 256, 5.0, 487.0}};
+    static const Shape b16[] = {{5, 64, 64, 256, 6.0, 6.5}, {3, 64, 128, 256, 8.0, 11.0},
+                                {13, 128, 128, 512, 0.0, 33.0}, {11, 256, 256, 256, 0.0, 61.0}};
+    // the few-signals shape: the dictionary once per 32 signals, at about 3 TB/s
+    const int groups = (p + 31) / 32;
+    int best = 4;
+    double t = 5.0 + (bf16 ? 2.0 : 4.0) * m * kpad * groups / (bf16 ? 2.0e6 : 2.9e6);
+    if (p <= 32) return best;
+    for (const Shape& c : bf16 ? b16 : f32) {
+        const int64_t tiles = (int64_t)((p + c.bm - 1) / c.bm) * ((m + c.bn - 1) / c.bn);
+        const double u = (c.start + c.round * (double)((tiles + c.at_once - 1) / c.at_once)) * kpad / 2048.0;
+        if (u < t) { t = u; best = c.id; }
+    }
+    return best;
+}
+
 hipError_t launch_corr_gemm_f32(int variant, const float* At, int64_t lda, int m, int kpad,
                                 const float* Rbuf, int64_t ldr, const int* act,
                                 const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row,

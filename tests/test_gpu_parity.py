@@ -1132,3 +1132,18 @@ def test_long_running_lists(p, graph):
             assert torch.equal(part[key], whole[key][a:a + 700]), (key, a)
         torch.testing.assert_close(part["objective"], whole["objective"][a:a + 700], rtol=1e-12, atol=0.0, equal_nan=True)
     s.close()
+
+
+@pytest.mark.parametrize("screen", ["fp32", "bf16"])
+@pytest.mark.parametrize("n,m", [(40, 130), (500, 4096), (1030, 9000)])
+def test_default_product_shapes(n, m, screen):
+    """The shape picked by the size against a fixed one: every shape sums in the same order, so the bits agree."""
+    pk = _lib()
+    At = to_dev(bi.gaussian_dictionary(n, m, 29))
+    a, b = pk.Solver(At, 0.1, screen=screen, gram_table=False), pk.Solver(At, 0.1, screen=screen, gram_table=False)
+    b.set_tuning([0, 0, 0])
+    for p in (1, 32, 33, 63, 64, 65, 128, 129, 300, 511, 512, 513, 1000):
+        R = torch.randn(p, n, generator=torch.Generator().manual_seed(p)).cuda()
+        assert torch.equal(a.correlate(R), b.correlate(R)), p
+    a.close()
+    b.close()
