@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstddef>
 #include <cmath>
 #include <cstdarg>
@@ -154,6 +155,7 @@ struct bmpl_ctx {
     unsigned long long arena_total = 0;   // doubles over all chunks
     float* Bw = nullptr;          // [p_cap][kpad]
     float* Gc = nullptr;          // [p_cap][ldg] correlations
+    float* Gm = nullptr;          // [p_cap][corr_groups(m)] the largest |g| of each group of atoms (null: not kept)
     int64_t ldg = 0;
     int* act[2] = {nullptr, nullptr};
     int* n_act_dev = nullptr;     // [2] running counts (inside the arena header)
@@ -307,7 +309,7 @@ void free_signals(bmpl_ctx* c)
     dfree(w.nS); dfree(w.nsel); dfree(w.sel); dfree(w.vmax); dfree(w.kkt_on); dfree(w.obj);
     dfree(w.kkt); dfree(w.inI); dfree(w.glazy); dfree(w.jadd); dfree(w.obj_prev); dfree(w.rr2); dfree(w.g0max);
     dfree(w.cap); dfree(w.blk);
-    dfree(c->Bw); dfree(c->Gc); dfree(c->act[0]); dfree(c->act[1]);
+    dfree(c->Bw); dfree(c->Gc); dfree(c->Gm); dfree(c->act[0]); dfree(c->act[1]);
     dfree(w.R16); dfree(w.rnorm); dfree(w.dxnorm); dfree(c->cand); dfree(c->ncand);
     dfree(w.R8); dfree(w.rscale8); dfree(c->cand8); dfree(c->ncand8); dfree(c->vmax8); dfree(c->zeros);
     dfree(c->cert); dfree(c->cert_act); dfree(c->n_cert_dev);
@@ -408,6 +410,13 @@ bmpl_status ensure_workspace(bmpl_ctx* c, int p, int selcap)
     w.arena = c->arena_dev;
     HIPC(dalloc(&c->Bw, P * c->kpad));
     HIPC(dalloc(&c->Gc, P * (size_t)c->ldg));
+    // Worth it for rows longer than the selection's registers hold (8192 values): a shorter row is one round trip
+    // already, and the groups make it three (301 signals of 80 x 390, one graph per solve: 611 us without, 629 with;
+    // 1024 rows of 16 384: 22 us a selection without, 12 with).
+    if (c->m > 8192 && dalloc(&c->Gm, P * corr_groups(c->m)) != hipSuccess) {   // without it whole rows are read
+        (void)hipGetLastError();
+        c->Gm = nullptr;
+    }
     HIPC(dalloc(&c->act[0], P));
     HIPC(dalloc(&c->act[1], P));
     HIPC(dalloc(&c->grow_list, P));
@@ -957,6 +966,7 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         size_t e0 = ev ? mark(c, q) : 0;
         // One correlation product over a running list (prec 0 float32, 1 bfloat16, 2 e4m3).  Gated:
         // every tile shape is enqueued and runs only for its own bucket of the device-side count.
+        int gm_lo = INT_MAX;
         auto product = [&](int prec, const int* lst, const int* cnt, bool gate) -> hipError_t {
             auto gemm = [&](int shape, int grid, int lo, int hi) -> hipError_t {
                 if (prec == 2)
@@ -964,10 +974,13 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
                                                 c->Gc, c->ldg, c->p_cap, lo, hi, c->ascale8, w.rscale8, q);
                 if (prec == 1)
                     return launch_corr_gemm_bf16(shape, c->A16, c->A16p, c->kpad, c->m, c->kpad, w.R16, c->kpad, lst, cnt,
-                                                 grid, c->Gc, c->ldg, c->p_cap, lo, hi, q);
+                                                 grid, c->Gc, c->ldg, c->p_cap, lo, hi, q, c->Gm, corr_groups(c->m));
                 return launch_corr_gemm_f32(shape, c->At, c->kpad, c->m, c->kpad, w.R, c->kpad, lst, cnt, grid,
-                                            c->Gc, c->ldg, c->p_cap, lo, hi, q);
+                                            c->Gc, c->ldg, c->p_cap, lo, hi, q, c->Gm, corr_groups(c->m));
             };
+            // the selection may use the groups' largest values from gm_lo rows on: the shapes of the buckets down to
+            // there write them
+            gm_lo = INT_MAX;
             if (gate) {
                 // count buckets of the three tile shapes; in a segment that starts with 512 or more running
                 // signals the large tile also takes the middle bucket (one launch less per iteration: the
@@ -977,11 +990,15 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
                     if (b == 1 && merge_mid) continue;
                     const int grid = std::min(n_grid, hi[b] - 1);
                     if (grid < lo[b]) continue;
-                    const hipError_t e = gemm(c->bucket_variant(b, n_grid), grid, lo[b], hi[b]);
+                    const int shape = c->bucket_variant(b, n_grid);
+                    if (corr_shape_has_groups(shape) && (gm_lo == hi[b] || (gm_lo == INT_MAX && grid == n_grid)))
+                        gm_lo = lo[b];
+                    const hipError_t e = gemm(shape, grid, lo[b], hi[b]);
                     if (e != hipSuccess) return e;
                 }
                 return hipSuccess;
             }
+            if (corr_shape_has_groups(c->corr_variant(n_grid))) gm_lo = 0;
             return gemm(c->corr_variant(n_grid), n_grid, 0, 1 << 30);
         };
         const bool qr = c->qroute && !first;
@@ -1015,6 +1032,7 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
             sc.k = rho; sc.nI = w.nI; sc.max_active = max_active;
             sc.cand = c->cand; sc.candcap = CANDCAP_DEF; sc.ncand = c->ncand;
             sc.clear_count = c->n_spill_dev;
+            sc.gm = c->Gm; sc.ldgm = corr_groups(c->m); sc.gm_lo = gm_lo;
             hipError_t e = launch_screen(sc, q);
             if (e != hipSuccess) return e;
             RescoreArgs rs{};
@@ -1075,6 +1093,7 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         } else {
             // with the natural stop certified against the float32 product's rounding
             a.rr2 = w.rr2; a.band = c->band32;
+            a.gm = qr ? nullptr : c->Gm; a.ldgm = corr_groups(c->m); a.gm_lo = gm_lo;
             a.At = c->At; a.lda = c->kpad; a.n = c->n; a.R = w.R; a.ldr = c->kpad;
             HIPC(launch_select(a, q));
         }

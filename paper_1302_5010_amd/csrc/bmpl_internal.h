@@ -66,6 +66,68 @@ __device__ __forceinline__ uint32_t chunk_bits(const uint32_t* ex, uint32_t w, i
     return j0 < m4 ? (ex ? w >> (j0 & 31) : 0u) : 0xFu;
 }
 
+// Groups of 32 atoms: group 2 b + s holds atoms 64 b + 16 s + {0..15} and 64 b + 32 + 16 s + {0..15}.
+__host__ __device__ inline int corr_groups(int m) { return 2 * ((m + 63) / 64); }
+__device__ inline int group_atom(int group, int i) { return 64 * (group >> 1) + 16 * (group & 1) + (i & 15) + 32 * (i >> 4); }
+
+// Largest values over the groups of a row's product (gm): each thread's over the groups with no atom in I (tmax, at
+// most the k-th largest |g| outside I for the k-th largest thread), and this thread's over all (gall).
+__device__ __forceinline__ void group_maxima(const float* gm, int groups, const uint32_t* ex, int words, float& tmax,
+                                             float& gall)
+{
+    constexpr int U = 4;
+    for (int g0 = threadIdx.x; g0 < groups; g0 += 256 * U) {
+        float v[U];
+        uint32_t w0[U], w1[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {            // clamped, so that all loads are in flight
+            const int g = min(g0 + 256 * q, groups - 1);
+            v[q] = gm[g];
+            w0[q] = ex[min(g & ~1, words - 1)];
+            w1[q] = ex[min(g | 1, words - 1)];
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int g = min(g0 + 256 * q, groups - 1);
+            const uint32_t in = ((w0[q] | w1[q]) >> (16 * (g & 1))) & 0xffffu;
+            gall = fmaxf(gall, v[q]);
+            if (in == 0u && g0 + 256 * q < groups) tmax = fmaxf(tmax, v[q]);   // every group in one thread only
+        }
+    }
+}
+
+// Lists the groups whose largest |g| reaches `quick` (up to cap; *n counts them all) and, after a barrier, visits
+// the atoms of the listed ones: visit(atom, |g|, counted) is called by whole waves (counted: an atom outside I).
+template <int CAPG, class VISIT>
+__device__ __forceinline__ void visit_groups(const float* gm, int groups, const float* g, const uint32_t* ex, int m,
+                                             float quick, int* s_list, int* n, VISIT&& visit)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int g0 = tid; g0 < groups; g0 += 256)
+        if (gm[g0] >= quick) {
+            const int e = atomicAdd(n, 1);
+            if (e < CAPG) s_list[e] = g0;
+        }
+    __syncthreads();
+    const int nl = min(*n, CAPG);
+    constexpr int U = 4;                          // two groups per wave and step, U steps in flight
+    for (int e0 = 2 * U * wave; e0 < nl; e0 += 2 * U * 4) {
+        float v[U];
+        uint32_t w[U];
+        int at[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int e = e0 + 2 * q + (lane >> 5);
+            at[q] = e < nl ? group_atom(s_list[e], lane & 31) : m;
+            const int j = min(at[q], m - 1);
+            v[q] = g[j];
+            w[q] = ex[j >> 5];
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) visit(at[q], fabsf(v[q]), at[q] < m && !((w[q] >> (at[q] & 31)) & 1u));
+    }
+}
+
 // One signal's slot block for capacity K (slots of I) and signal length n:
 //   G [K][K] float64 (Gram of I, row-major by slot) | Rinv [tri(min(K, n))] float64 (inverse Cholesky
 //   factor of G_SS, packed by support position; |S| <= n) | x [K] | c [K] | vs [8K] float64 scratch |
@@ -165,7 +227,10 @@ int corr_default_shape(bool bf16, int m, int kpad, int p);   // float32 or bfloa
 hipError_t launch_corr_gemm_f32(int variant, const float* At, int64_t lda, int m, int kpad,
                                 const float* Rbuf, int64_t ldr, const int* act,
                                 const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row,
-                                int n_lo, int n_hi, hipStream_t stream);   // runs only if n_lo <= count < n_hi
+                                int n_lo, int n_hi, hipStream_t stream,    // runs only if n_lo <= count < n_hi
+                                float* gm = nullptr, int64_t ldgm = 0);
+// gm (row a: ldgm floats), for shapes with corr_shape_has_groups: the largest |G| of each group of a row's atoms.
+bool corr_shape_has_groups(int variant);
 
 // Q = A^T A in float64 (m x m, leading dimension ldq), from the padded float32 atoms.
 hipError_t launch_gram_table(const float* At, int64_t lda, int m, int kpad, double* Q, int64_t ldq,
@@ -179,7 +244,8 @@ hipError_t launch_pack_bf16(const uint16_t* A16, int64_t lda, int m, int kpad, u
 hipError_t launch_corr_gemm_bf16(int variant, const uint16_t* At, const uint16_t* Apk, int64_t lda, int m, int kpad,
                                  const uint16_t* Rbuf, int64_t ldr, const int* act,
                                  const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row,
-                                 int n_lo, int n_hi, hipStream_t stream);
+                                 int n_lo, int n_hi, hipStream_t stream,
+                                 float* gm = nullptr, int64_t ldgm = 0);
 
 // The same product with e4m3 operands (raw bytes), per-atom and per-signal power-of-two scales
 // applied in the epilogue: G = (A8 R8^T) * ascale[j] * rscale[signal].  kpad % 128 == 0.
@@ -199,6 +265,7 @@ struct SelectArgs {
     int* sel; int selcap; int* nsel; float* vmax;
     // pursuit bookkeeping (may be null in the diagnostic entry point)
     const int* nI; int max_active;
+    const float* gm; int64_t ldgm; int gm_lo;   // groups' largest |G| (null: none), there from gm_lo rows on
     int* clear_count;      // set to 0 by workgroup 0 before anything else (or null)
     // float32 band (0 = off) ||xi_i||^2 and eps_i = band ||xi_i||: signals whose stop lies within it get the exact
     // re-score of the atoms whose |g~| lies within eps_i of lambda (float32 data, float64 sums); exact violators
@@ -219,6 +286,7 @@ struct ScreenArgs {
     const uint32_t* excl; int words;
     int k; const int* nI; int max_active;
     int* cand; int candcap; int* ncand;
+    const float* gm; int64_t ldgm; int gm_lo;   // as in SelectArgs
     int* clear_count;                         // set to 0 by workgroup 0 before anything else (or null)
 };
 struct RescoreArgs {

@@ -23,6 +23,7 @@
 
 #include "bmpl_internal.h"
 #include "gemm_tile.h"
+#include "wave_ops.h"
 
 namespace bmpl {
 namespace {
@@ -33,11 +34,45 @@ namespace {
 // lane (scalar arithmetic), the lane's part of it one 32-bit offset, so a store is one instruction; with the test
 // and a 64-bit address per store each was a dozen (bfloat16, 4096 x 20000 x 1024: 215 -> 207 us with the loop below).
 // The float32 64 x 64 waves keep the tests: 16 of them share a CU and cover each other's (without: 491 -> 494 us).
+struct CorrEpi {
+    const float* ascale; const float* rscale;   // e4m3: power-of-two scales, one per atom and one per signal
+    float* gm; int64_t ldgm;                    // the groups' largest |g| of each row, or null (not e4m3)
+};
+
 template <class E, int TI, int TJ>
 __device__ __forceinline__ void store_tile(const floatx16 (&acc)[TI][TJ], int sig0, int ws, int atom0, int wa, int l32,
                                            int h, int m, int n_act, const int* __restrict__ act, float* __restrict__ G,
-                                           int64_t ldg, const float* __restrict__ ascale, const float* __restrict__ rscale)
+                                           int64_t ldg, CorrEpi epi)
 {
+    if constexpr (sizeof(E) != 1 && TJ % 2 == 0) {
+        if (epi.gm) {   // the largest |g| of every group, for the selection: a row of 16 lanes by 2 columns of blocks
+            const int l16 = l32 & 15;
+            const bool b0 = l16 & 1, b1 = (l16 >> 1) & 1, b2 = (l16 >> 2) & 1, b3 = (l16 >> 3) & 1;
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; j += 2) {
+                    // sixteen rows over sixteen lanes: every exchange halves the rows a lane carries (of its
+                    // partners across the row, the half and the quads), lane l16 ends with register l16's row
+                    float x8[8], x4[4], x2[2];
+                    auto top = [&](int r) { return fmaxf(fabsf(acc[i][j][r]), fabsf(acc[i][j + 1][r])); };
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        const float lo = top(r), hi = top(r + 8);
+                        x8[r] = fmaxf(b3 ? hi : lo, lane_move<DPP_MIRROR>(b3 ? lo : hi));
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        x4[r] = fmaxf(b2 ? x8[r + 4] : x8[r], lane_move<DPP_HALF_MIRROR>(b2 ? x8[r] : x8[r + 4]));
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+                        x2[r] = fmaxf(b1 ? x4[r + 2] : x4[r], lane_move<DPP_XOR2>(b1 ? x4[r] : x4[r + 2]));
+                    const float mine = fmaxf(b0 ? x2[1] : x2[0], lane_move<DPP_XOR1>(b0 ? x2[0] : x2[1]));
+                    const int a = sig0 + ws + 32 * i + 8 * (l16 >> 2) + 4 * h + (l16 & 3), atom = atom0 + wa + 32 * j;
+                    if (a < n_act && atom < m) epi.gm[(int64_t)a * epi.ldgm + 2 * (atom / 64) + (l32 >> 4)] = mine;
+                }
+        }
+    }
     if constexpr (sizeof(E) == 2 || (sizeof(E) == 4 && TI * TJ > 4)) {
         const int r0 = __builtin_amdgcn_readfirstlane(sig0 + ws);
         if (r0 + 32 * TI <= n_act && ldg <= (1 << 26)) {      // the same for the whole wave
@@ -63,13 +98,13 @@ __device__ __forceinline__ void store_tile(const floatx16 (&acc)[TI][TJ], int si
         for (int j = 0; j < TJ; ++j) {
             const int atom = atom0 + wa + 32 * j + l32;
             if (atom >= m) continue;
-            const float sa = sizeof(E) == 1 ? ascale[atom] : 1.f;
+            const float sa = sizeof(E) == 1 ? epi.ascale[atom] : 1.f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int a = sig0 + ws + 32 * i + 8 * (r >> 2) + 4 * h + (r & 3);
                 if (a < n_act) {
                     if constexpr (sizeof(E) == 1)
-                        G[(int64_t)a * ldg + atom] = acc[i][j][r] * sa * rscale[act ? act[a] : a];
+                        G[(int64_t)a * ldg + atom] = acc[i][j][r] * sa * epi.rscale[act ? act[a] : a];
                     else
                         G[(int64_t)a * ldg + atom] = acc[i][j][r];
                 }
@@ -82,7 +117,7 @@ __global__ __launch_bounds__((TileShape<BM, BN, WM, WN>::THREADS)) void corr_gem
     const E* __restrict__ At, int64_t lda, int m, int kpad,
     const E* __restrict__ Rbuf, int64_t ldr, const int* __restrict__ act,
     const int* __restrict__ n_act_dev, int p_grid, float* __restrict__ G, int64_t ldg, int tiles_n, int zero_row,
-    int n_lo, int n_hi, const float* __restrict__ ascale, const float* __restrict__ rscale)
+    int n_lo, int n_hi, CorrEpi epi)
 {
     using S = TileShape<BM, BN, WM, WN>;
     const int n_act = n_act_dev ? *n_act_dev : p_grid;
@@ -130,7 +165,7 @@ __global__ __launch_bounds__((TileShape<BM, BN, WM, WN>::THREADS)) void corr_gem
     floatx16 acc[S::TI][S::TJ];
     mfma_tile_loop<E, BM, BN, WM, WN, DEPTH>(Rbuf, oR, At, oA, kpad, lds, ws, wa, acc);
 
-    store_tile<E, S::TI, S::TJ>(acc, sig0, ws, atom0, wa, l32, h, m, n_act, act, G, ldg, ascale, rscale);
+    store_tile<E, S::TI, S::TJ>(acc, sig0, ws, atom0, wa, l32, h, m, n_act, act, G, ldg, epi);
 }
 
 // The same product with both operand tiles copied straight into swizzled LDS buffers (mfma_tile_loop_dma; bfloat16
@@ -140,7 +175,7 @@ __global__ __launch_bounds__((TileShape<BM, BN, WM, WN>::THREADS)) void corr_gem
     const E* __restrict__ At, int64_t lda, int m, int kpad,
     const E* __restrict__ Rbuf, int64_t ldr, const int* __restrict__ act,
     const int* __restrict__ n_act_dev, int p_grid, float* __restrict__ G, int64_t ldg, int tiles_n, int zero_row,
-    int n_lo, int n_hi, const float* __restrict__ ascale, const float* __restrict__ rscale)
+    int n_lo, int n_hi, CorrEpi epi)
 {
     using S = TileShape<BM, BN, WM, WN>;
     using D = DmaShape<BM, BN, WM, WN>;
@@ -188,7 +223,7 @@ __global__ __launch_bounds__((TileShape<BM, BN, WM, WN>::THREADS)) void corr_gem
         mfma_tile_loop_pipe<BM, BN, WM, WN, 2>(Rbuf, oR, At, oA, kpad, lds, ws, wa, acc);
     else
         mfma_tile_loop_dma<E, BM, BN, WM, WN>(Rbuf, oR, At, oA, kpad, lds, ws, wa, acc);
-    store_tile<E, S::TI, S::TJ>(acc, sig0, ws, atom0, wa, l32, h, m, n_act, act, G, ldg, ascale, rscale);
+    store_tile<E, S::TI, S::TJ>(acc, sig0, ws, atom0, wa, l32, h, m, n_act, act, G, ldg, epi);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -226,7 +261,7 @@ template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__((TileShape<BM, BN, WM, WN>::THREADS)) void corr_gemm_direct_kernel(
     const uint4* __restrict__ Apk, int m, int kpad, const __bf16* __restrict__ Rbuf, int64_t ldr,
     const int* __restrict__ act, const int* __restrict__ n_act_dev, int p_grid, float* __restrict__ G,
-    int64_t ldg, int tiles_n, int zero_row, int n_lo, int n_hi)
+    int64_t ldg, int tiles_n, int zero_row, int n_lo, int n_hi, CorrEpi epi)
 {
     using S = TileShape<BM, BN, WM, WN>;
     constexpr int TI = S::TI, TJ = S::TJ;
@@ -328,7 +363,7 @@ __global__ __launch_bounds__((TileShape<BM, BN, WM, WN>::THREADS)) void corr_gem
         __syncthreads();
         cur ^= 1;
     }
-    store_tile<__bf16, TI, TJ>(acc, sig0, ws, atom0, wa, l32, h, m, n_act, act, G, ldg, nullptr, nullptr);
+    store_tile<__bf16, TI, TJ>(acc, sig0, ws, atom0, wa, l32, h, m, n_act, act, G, ldg, epi);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -454,7 +489,7 @@ template <class E>
 __global__ __launch_bounds__(64) void corr_few_kernel(
     const E* __restrict__ At, int64_t lda, int m, int kpad, const E* __restrict__ Rbuf, int64_t ldr,
     const int* __restrict__ act, const int* __restrict__ n_act_dev, int p_grid, float* __restrict__ G, int64_t ldg,
-    int tiles_n, int zero_row, int n_lo, int n_hi, const float* __restrict__ ascale, const float* __restrict__ rscale)
+    int tiles_n, int zero_row, int n_lo, int n_hi, CorrEpi epi)
 {
     const int n_act = n_act_dev ? *n_act_dev : p_grid;
     if (n_act < n_lo || n_act >= n_hi) return;   // another tile shape serves this running count
@@ -518,13 +553,13 @@ __global__ __launch_bounds__(64) void corr_few_kernel(
 #pragma unroll
     for (int d = 0; d < BUF - 1; ++d)
         if (s0 + d < stages) compute(a[d], r[d]);
-    store_tile<E, 1, 1>(acc, sig0, 0, atom0, 0, l32, h, m, n_act, act, G, ldg, ascale, rscale);
+    store_tile<E, 1, 1>(acc, sig0, 0, atom0, 0, l32, h, m, n_act, act, G, ldg, epi);
 }
 
 template <class E>
 hipError_t launch_few(const E* At, int64_t lda, int m, int kpad, const E* Rbuf, int64_t ldr, const int* act,
                       const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row, int n_lo, int n_hi,
-                      const float* ascale, const float* rscale, hipStream_t stream)
+                      CorrEpi epi, hipStream_t stream)
 {
     constexpr int BN = sizeof(E) == 4 ? 16 : 32;
     const int tiles_m = (p_grid + FEW_M - 1) / FEW_M;
@@ -537,7 +572,7 @@ hipError_t launch_few(const E* At, int64_t lda, int m, int kpad, const E* Rbuf, 
                            n_act_dev, p_grid, G, ldg, tiles_n, zero_row, n_lo, n_hi);
     } else {
         hipLaunchKernelGGL(corr_few_kernel<E>, dim3((unsigned)nwg), dim3(64), 0, stream, At, lda, m, kpad, Rbuf, ldr, act,
-                           n_act_dev, p_grid, G, ldg, tiles_n, zero_row, n_lo, n_hi, ascale, rscale);
+                           n_act_dev, p_grid, G, ldg, tiles_n, zero_row, n_lo, n_hi, epi);
     }
     return hipGetLastError();
 }
@@ -545,7 +580,7 @@ hipError_t launch_few(const E* At, int64_t lda, int m, int kpad, const E* Rbuf, 
 template <int BM, int BN, int WM, int WN>
 hipError_t launch_direct(const uint16_t* Apk, int m, int kpad, const uint16_t* Rbuf, int64_t ldr, const int* act,
                          const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row, int n_lo, int n_hi,
-                         hipStream_t stream)
+                         CorrEpi epi, hipStream_t stream)
 {
     static_assert(PACK_ATOMS % BN == 0, "atom tiles must lie inside the packed padding");
     const int tiles_m = (p_grid + BM - 1) / BM;
@@ -555,14 +590,14 @@ hipError_t launch_direct(const uint16_t* Apk, int m, int kpad, const uint16_t* R
     hipLaunchKernelGGL((corr_gemm_direct_kernel<BM, BN, WM, WN>), dim3((unsigned)nwg),
                        dim3(TileShape<BM, BN, WM, WN>::THREADS), 0, stream, reinterpret_cast<const uint4*>(Apk), m,
                        kpad, reinterpret_cast<const __bf16*>(Rbuf), ldr, act, n_act_dev, p_grid, G, ldg, tiles_n,
-                       zero_row, n_lo, n_hi);
+                       zero_row, n_lo, n_hi, epi);
     return hipGetLastError();
 }
 
 template <class E, int BM, int BN, int WM, int WN, int DEPTH = 1>
 hipError_t launch_shape(const E* At, int64_t lda, int m, int kpad, const E* Rbuf, int64_t ldr,
                         const int* act, const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row,
-                        int n_lo, int n_hi, const float* ascale, const float* rscale, hipStream_t stream)
+                        int n_lo, int n_hi, CorrEpi epi, hipStream_t stream)
 {
     const int tiles_m = (p_grid + BM - 1) / BM;
     const int tiles_n = (m + BN - 1) / BN;
@@ -570,14 +605,14 @@ hipError_t launch_shape(const E* At, int64_t lda, int m, int kpad, const E* Rbuf
     if (nwg > 0x7fffffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL((corr_gemm_kernel<E, BM, BN, WM, WN, DEPTH>), dim3((unsigned)nwg),
                        dim3(TileShape<BM, BN, WM, WN>::THREADS), 0, stream, At, lda, m, kpad, Rbuf, ldr, act,
-                       n_act_dev, p_grid, G, ldg, tiles_n, zero_row, n_lo, n_hi, ascale, rscale);
+                       n_act_dev, p_grid, G, ldg, tiles_n, zero_row, n_lo, n_hi, epi);
     return hipGetLastError();
 }
 
 template <class E, int BM, int BN, int WM, int WN>
 hipError_t launch_dma(const E* At, int64_t lda, int m, int kpad, const E* Rbuf, int64_t ldr, const int* act,
                       const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row, int n_lo, int n_hi,
-                      const float* ascale, const float* rscale, hipStream_t stream)
+                      CorrEpi epi, hipStream_t stream)
 {
     const int tiles_m = (p_grid + BM - 1) / BM;
     const int tiles_n = (m + BN - 1) / BN;
@@ -585,15 +620,14 @@ hipError_t launch_dma(const E* At, int64_t lda, int m, int kpad, const E* Rbuf, 
     if (nwg > 0x7fffffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL((corr_gemm_dma_kernel<E, BM, BN, WM, WN>), dim3((unsigned)nwg),
                        dim3(TileShape<BM, BN, WM, WN>::THREADS), 0, stream, At, lda, m, kpad, Rbuf, ldr, act,
-                       n_act_dev, p_grid, G, ldg, tiles_n, zero_row, n_lo, n_hi, ascale, rscale);
+                       n_act_dev, p_grid, G, ldg, tiles_n, zero_row, n_lo, n_hi, epi);
     return hipGetLastError();
 }
 
 template <class E>
 hipError_t launch_variant(int variant, const E* At, int64_t lda, int m, int kpad, const E* Rbuf, int64_t ldr,
                           const int* act, const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row,
-                          int n_lo, int n_hi, hipStream_t stream, const float* ascale = nullptr,
-                          const float* rscale = nullptr)
+                          int n_lo, int n_hi, hipStream_t stream, CorrEpi epi)
 {
     if (p_grid <= 0 || m <= 0) return hipSuccess;
     if (kpad % (TILE_ROW_BYTES / (int)sizeof(E))) return hipErrorInvalidValue;
@@ -601,18 +635,18 @@ hipError_t launch_variant(int variant, const E* At, int64_t lda, int m, int kpad
     // for the 256 x 128 tile at 1024 signals); 16- and 8-bit stages measured slower that way
     constexpr int DEEP = sizeof(E) == 4 ? 2 : 1;
     switch (variant) {
-    case 0: return launch_shape<E, 128, 128, 64, 64, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 1: return launch_shape<E, 256, 256, 64, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 2: return launch_shape<E, 256, 128, 64, 64, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 3: return launch_shape<E, 64, 128, 32, 64, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 4: return launch_few<E>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 5: return launch_shape<E, 64, 64, 32, 32, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 6: return launch_shape<E, 256, 256, 128, 128>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 7: return launch_shape<E, 256, 256, 128, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 11: return launch_dma<E, 256, 256, 128, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 12: return launch_dma<E, 256, 256, 64, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 13: return launch_dma<E, 128, 128, 64, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
-    case 14: return launch_dma<E, 256, 256, 128, 128>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, ascale, rscale, stream);
+    case 0: return launch_shape<E, 128, 128, 64, 64, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+    case 1: return launch_shape<E, 256, 256, 64, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+    case 2: return launch_shape<E, 256, 128, 64, 64, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+    case 3: return launch_shape<E, 64, 128, 32, 64, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+    case 4: return launch_few<E>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+    case 5: return launch_shape<E, 64, 64, 32, 32, DEEP>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+    case 6: return launch_shape<E, 256, 256, 128, 128>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+    case 7: return launch_shape<E, 256, 256, 128, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+    case 11: return launch_dma<E, 256, 256, 128, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+    case 12: return launch_dma<E, 256, 256, 64, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+    case 13: return launch_dma<E, 128, 128, 64, 64>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+    case 14: return launch_dma<E, 256, 256, 128, 128>(At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
     default: return hipErrorInvalidValue;
     }
 }
@@ -640,6 +674,8 @@ const char* corr_shape_name(int v)
     default: return "?";
     }
 }
+
+bool corr_shape_has_groups(int variant) { return variant != 4 && variant != 5; }   // waves of 64 atoms or more
 
 // The tile shape of p signals when none was set.  A launch takes rounds of tiles over the card's 256 CUs, so the best
 // shape follows from how many rounds its tile count leaves: each candidate's time is modelled as a start plus
@@ -670,10 +706,10 @@ int corr_default_shape(bool bf16, int m, int kpad, int p)
 hipError_t launch_corr_gemm_f32(int variant, const float* At, int64_t lda, int m, int kpad,
                                 const float* Rbuf, int64_t ldr, const int* act,
                                 const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row,
-                                int n_lo, int n_hi, hipStream_t stream)
+                                int n_lo, int n_hi, hipStream_t stream, float* gm, int64_t ldgm)
 {
     return launch_variant<float>(variant, At, lda, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row,
-                                 n_lo, n_hi, stream);
+                                 n_lo, n_hi, stream, CorrEpi{nullptr, nullptr, gm, ldgm});
 }
 
 hipError_t launch_corr_gemm_fp8(int variant, const uint8_t* A8, int64_t lda, int m, int kpad,
@@ -683,7 +719,7 @@ hipError_t launch_corr_gemm_fp8(int variant, const uint8_t* A8, int64_t lda, int
 {
     if (!ascale || !rscale) return hipErrorInvalidValue;
     return launch_variant<uint8_t>(variant, A8, lda, m, kpad, R8, ldr, act, n_act_dev, p_grid, G, ldg, zero_row,
-                                   n_lo, n_hi, stream, ascale, rscale);
+                                   n_lo, n_hi, stream, CorrEpi{ascale, rscale, nullptr, 0});
 }
 
 size_t packed_bf16_elems(int m, int kpad)
@@ -705,21 +741,22 @@ hipError_t launch_pack_bf16(const uint16_t* A16, int64_t lda, int m, int kpad, u
 hipError_t launch_corr_gemm_bf16(int variant, const uint16_t* At, const uint16_t* Apk, int64_t lda, int m, int kpad,
                                  const uint16_t* Rbuf, int64_t ldr, const int* act,
                                  const int* n_act_dev, int p_grid, float* G, int64_t ldg, int zero_row,
-                                 int n_lo, int n_hi, hipStream_t stream)
+                                 int n_lo, int n_hi, hipStream_t stream, float* gm, int64_t ldgm)
 {
+    const CorrEpi epi{nullptr, nullptr, gm, ldgm};
     if (variant >= 8 && variant <= 10) {
         if (!Apk || p_grid <= 0 || m <= 0) return Apk ? hipSuccess : hipErrorInvalidValue;
         if (kpad % 64) return hipErrorInvalidValue;
         switch (variant) {
-        case 8: return launch_direct<256, 256, 128, 64>(Apk, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, stream);
-        case 9: return launch_direct<128, 256, 64, 64>(Apk, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, stream);
-        case 10: return launch_direct<256, 128, 128, 64>(Apk, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, stream);
+        case 8: return launch_direct<256, 256, 128, 64>(Apk, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+        case 9: return launch_direct<128, 256, 64, 64>(Apk, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
+        case 10: return launch_direct<256, 128, 128, 64>(Apk, m, kpad, Rbuf, ldr, act, n_act_dev, p_grid, G, ldg, zero_row, n_lo, n_hi, epi, stream);
         default: return hipErrorInvalidValue;
         }
     }
     return launch_variant<__bf16>(variant, reinterpret_cast<const __bf16*>(At), lda, m, kpad,
                                   reinterpret_cast<const __bf16*>(Rbuf), ldr, act, n_act_dev, p_grid, G, ldg,
-                                  zero_row, n_lo, n_hi, stream);
+                                  zero_row, n_lo, n_hi, stream, epi);
 }
 
 }  // namespace bmpl

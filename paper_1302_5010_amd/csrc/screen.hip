@@ -275,8 +275,9 @@ __device__ void screen_sweeps(const ScreenArgs& a, int row, int sig, int k, floa
 // the k-th largest has U <= lambda, so tau <= lambda = thr.  A buffer overflow falls back to the sweeps.
 // 8192 rows of 20 000: 183 us (3.6 TB/s; 216 before the chunks took turns and a quick test skipped most groups);
 // five waves per SIMD instead of four.
-template <int KMAX>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 32 ? 5 : 3))) void screen_select_kernel(ScreenArgs a)
+// GROUPS: the launch may have them (the kernel without them keeps its registers).
+template <int KMAX, bool GROUPS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX > 32 ? 3 : (GROUPS ? 4 : 5)))) void screen_select_kernel(ScreenArgs a)
 {
     constexpr int CH = 8;       // float4 per thread held in registers
     constexpr int CAP = 2048;   // buffered entries
@@ -305,9 +306,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 32 
     const bool vec4 = ((a.ldg & 3) == 0) && ((reinterpret_cast<uintptr_t>(a.G) & 15) == 0);
     const int m4 = vec4 ? (a.m & ~3) : 0;
 
+    // with the groups' largest values only the groups that can hold an entry are read (8192 rows of 20 000: 65 to
+    // 83 us instead of 183; the product's epilogue takes 25 us longer for it)
+    constexpr int CAPG = GROUPS ? 1024 : 1;
+    __shared__ int s_gl[CAPG];
+    const bool grouped = GROUPS && ex != nullptr && n_act >= a.gm_lo;   // the same for the whole launch
+    const float* gm = a.gm + (int64_t)row * a.ldgm;
     float4 f0[CH];
     uint32_t w0[CH];
-    row_chunks<CH>(g, ex, 0, m4, f0, w0);
+    if (!grouped) row_chunks<CH>(g, ex, 0, m4, f0, w0);
     // The rest of the row streams in chunks of CS float4 per thread, each chunk's loads issued one chunk
     // ahead (the first before the bound is computed), so a workgroup waits for memory about once.
     constexpr int CS = 4;
@@ -316,15 +323,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 32 
     auto load_chunk = [&](int base0, float4 (&f)[CS], uint32_t (&word)[CS]) {
         row_chunks<CS>(g, ex, base0, m4, f, word);
     };
-    load_chunk(1024 * CH, fa, wa);
+    if (!grouped) load_chunk(1024 * CH, fa, wa);
     float gall = 0.f, tmax = -1.f;   // largest |g~| over every atom; over the registered atoms outside I
+    if (grouped) {
+        group_maxima(gm, corr_groups(a.m), ex, a.words, tmax, gall);
+    } else {
 #pragma unroll
-    for (int q = 0; q < CH; ++q) {
-        w0[q] = chunk_bits(ex, w0[q], 4 * tid + 1024 * q, m4);   // bit set: in I or past the row
-        if (!(w0[q] & 1u)) tmax = fmaxf(tmax, fabsf(f0[q].x));
-        if (!(w0[q] & 2u)) tmax = fmaxf(tmax, fabsf(f0[q].y));
-        if (!(w0[q] & 4u)) tmax = fmaxf(tmax, fabsf(f0[q].z));
-        if (!(w0[q] & 8u)) tmax = fmaxf(tmax, fabsf(f0[q].w));
+        for (int q = 0; q < CH; ++q) {
+            w0[q] = chunk_bits(ex, w0[q], 4 * tid + 1024 * q, m4);   // bit set: in I or past the row
+            if (!(w0[q] & 1u)) tmax = fmaxf(tmax, fabsf(f0[q].x));
+            if (!(w0[q] & 2u)) tmax = fmaxf(tmax, fabsf(f0[q].y));
+            if (!(w0[q] & 4u)) tmax = fmaxf(tmax, fabsf(f0[q].z));
+            if (!(w0[q] & 8u)) tmax = fmaxf(tmax, fabsf(f0[q].w));
+        }
     }
     {
         float cur = tmax;
@@ -335,7 +346,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 32 
             if (lane == __ffsll((long long)owners) - 1) cur = -2.f;   // pop one holder
         }
     }
-    if (tid == 0) { s_n = 0; s_T = INFINITY; }
+    if (tid == 0) { s_n = 0; s_cnt = 0; s_T = INFINITY; }
     __syncthreads();
     if (tid < 4 * k) {   // T = the k-th largest of the 4k listed maxima (equal values write the same T)
         const int tw = tid / k;
@@ -380,6 +391,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 32 
         take(!(w & 4u) && ok(v2), j0 + 2, v2);
         take(!(w & 8u) && ok(v3), j0 + 3, v3);
     };
+    if (grouped) {
+        visit_groups<CAPG>(gm, corr_groups(a.m), g, ex, a.m, quick, s_gl, &s_cnt,
+                           [&](int j, float v, bool out) { take(out && ok(v), j, v); });
+        if (s_cnt > CAPG) {                       // (the same in every thread)
+            screen_sweeps<KMAX>(a, row, sig, k, eps);
+            return;
+        }
+        __syncthreads();                          // s_cnt is reused below
+    } else {
 #pragma unroll
     for (int q = 0; q < CH; ++q) four(f0[q], w0[q], 4 * tid + 1024 * q);
     // two chunks that take turns by name (a copied register would wait for its load); the same trip count in every lane
@@ -403,6 +423,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX <= 32 
         gall = fmaxf(gall, v);
         const bool out = in && !(ex && ((ex[j >> 5] >> (j & 31)) & 1u));
         take(out && ok(v), j, v);
+    }
     }
     gall = wave_max(gall);
     if (lane == 0) s_r[wave] = gall;
@@ -730,12 +751,11 @@ hipError_t launch_screen(const ScreenArgs& a, hipStream_t stream)
 {
     if (a.p_grid <= 0) return hipSuccess;
     if (a.k < 0 || a.k > 64) return hipErrorInvalidValue;
-    if (a.k <= 16)
-        hipLaunchKernelGGL(screen_select_kernel<16>, dim3(a.p_grid), dim3(256), 0, stream, a);
-    else if (a.k <= 32)
-        hipLaunchKernelGGL(screen_select_kernel<32>, dim3(a.p_grid), dim3(256), 0, stream, a);
-    else
-        hipLaunchKernelGGL(screen_select_kernel<64>, dim3(a.p_grid), dim3(256), 0, stream, a);
+    const bool groups = a.gm != nullptr && a.gm_lo <= a.p_grid;
+    const auto kernel = a.k <= 16 ? (groups ? screen_select_kernel<16, true> : screen_select_kernel<16, false>)
+                        : a.k <= 32 ? (groups ? screen_select_kernel<32, true> : screen_select_kernel<32, false>)
+                                    : (groups ? screen_select_kernel<64, true> : screen_select_kernel<64, false>);
+    hipLaunchKernelGGL(kernel, dim3(a.p_grid), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -37,8 +37,9 @@ __device__ inline bool needs_certification(const SelectArgs& a, int sig, int k, 
 // The selection of one signal; *certify is set by thread 0.
 // Latency bounds it, not the bytes: 1024 rows of 16 384 are 22 us (3 TB/s), a short row 8 us (10.6 before the loads of
 // its tail were issued together and the words of the bitmap stopped waiting for the values before them).
-template <int KMAX>
-__device__ __forceinline__ void select_row(const SelectArgs& a, int row, int sig, bool* certify)
+// GROUPS: the launch may have the groups' largest values (the kernel without them keeps its registers).
+template <int KMAX, bool GROUPS>
+__device__ __forceinline__ void select_row(const SelectArgs& a, int row, int sig, bool grouped, bool* certify)
 {
     const float* g = a.G + (int64_t)row * a.ldg;
     const uint32_t* ex = a.excl ? a.excl + (int64_t)sig * a.words : nullptr;
@@ -63,9 +64,13 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int row, int sig
     // Each thread's first CH float4 of the row stay in registers (issued before lambda is read, so the
     // loads are in flight meanwhile); the rest is streamed once later.
     constexpr int CH = 8;
+    constexpr int CAPG = GROUPS ? 1024 : 1;
+    __shared__ int s_gl[CAPG];
+    __shared__ int s_ng;
+    const float* gm = a.gm + (int64_t)row * a.ldgm;
     float4 f0[CH];
     uint32_t w0[CH];
-    row_chunks<CH>(g, ex, 0, m4, f0, w0);   // 4 atoms share one word
+    if (!grouped) row_chunks<CH>(g, ex, 0, m4, f0, w0);   // 4 atoms share one word
     // The rest of the row streams in chunks of CS float4 per thread, each chunk's loads issued one chunk
     // ahead (the first before the bound is computed), so a workgroup waits for memory about once.
     constexpr int CS = 4;
@@ -74,17 +79,21 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int row, int sig
     auto load_chunk = [&](int base0, float4 (&f)[CS], uint32_t (&word)[CS]) {
         row_chunks<CS>(g, ex, base0, m4, f, word);
     };
-    load_chunk(1024 * CH, fa, wa);
+    if (!grouped) load_chunk(1024 * CH, fa, wa);
+    float tmax = -1.f, gall = 0.f;
+    if (grouped) group_maxima(gm, corr_groups(a.m), ex, a.words, tmax, gall);
 
     // Pass 1 (relative lambda rule only): lambda_i = c * max_j |g_j|.
     if (a.lam_rel > 0.0) {
-        float mx = 0.f;
+        float mx = gall;
+        if (!grouped) {
 #pragma unroll 4
-        for (int j0 = 4 * tid; j0 < m4; j0 += 1024) {
-            const float4 f = *reinterpret_cast<const float4*>(g + j0);
-            mx = fmaxf(mx, fmaxf(fmaxf(fabsf(f.x), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w))));
+            for (int j0 = 4 * tid; j0 < m4; j0 += 1024) {
+                const float4 f = *reinterpret_cast<const float4*>(g + j0);
+                mx = fmaxf(mx, fmaxf(fmaxf(fabsf(f.x), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w))));
+            }
+            for (int j = m4 + tid; j < a.m; j += 256) mx = fmaxf(mx, fabsf(g[j]));
         }
-        for (int j = m4 + tid; j < a.m; j += 256) mx = fmaxf(mx, fabsf(g[j]));
         mx = wave_max(mx);
         if (lane == 0) s_red[wave] = mx;
         __syncthreads();
@@ -104,7 +113,7 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int row, int sig
     // The k-th largest of the 256 threads' maxima over their registered entries is at most the k-th
     // largest |g_j| of the row (they are k distinct entries of it), so only entries >= T can be among
     // the k largest: the insertions below skip the rest.
-    float tmax = -1.f;
+    if (!grouped) {
 #pragma unroll
     for (int q = 0; q < CH; ++q) {
         w0[q] = chunk_bits(ex, w0[q], 4 * tid + 1024 * q, m4);
@@ -112,6 +121,7 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int row, int sig
         if (!(w0[q] & 2u)) tmax = fmaxf(tmax, fabsf(f0[q].y));
         if (!(w0[q] & 4u)) tmax = fmaxf(tmax, fabsf(f0[q].z));
         if (!(w0[q] & 8u)) tmax = fmaxf(tmax, fabsf(f0[q].w));
+    }
     }
     float vmx = fmaxf(tmax, 0.f);
     {
@@ -151,7 +161,7 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int row, int sig
         __shared__ float s_cv[CAP];
         __shared__ int s_ci[CAP];
         __shared__ int s_n;
-        if (tid == 0) s_n = 0;
+        if (tid == 0) { s_n = 0; s_ng = 0; }
         __syncthreads();
         auto take = [&](bool t, int j, float v) {   // called by the whole wave
             const unsigned long long bal = __ballot(t);
@@ -178,6 +188,18 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int row, int sig
             take(!(w & 4u) && ok(v2), j0 + 2, v2);
             take(!(w & 8u) && ok(v3), j0 + 3, v3);
         };
+        if (grouped) {
+            // the groups that can hold an entry or the largest value outside I
+            visit_groups<CAPG>(gm, corr_groups(a.m), g, ex, a.m, quick, s_gl, &s_ng, [&](int j, float v, bool out) {
+                if (out) vmx = fmaxf(vmx, v);
+                take(out && ok(v), j, v);
+            });
+            if (s_ng > CAPG) {                    // too many (the same in every thread): the rounds of argmax below
+                for (int j = tid; j < a.m; j += 256)
+                    if (!((ex[j >> 5] >> (j & 31)) & 1u)) vmx = fmaxf(vmx, fabsf(g[j]));
+                if (tid == 0) s_n = CAP + 1;
+            }
+        } else {
 #pragma unroll
         for (int q = 0; q < CH; ++q) four(f0[q], w0[q], 4 * tid + 1024 * q);
         // two chunks that take turns by name (a copied register would wait for its load); every lane runs the same
@@ -201,6 +223,7 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int row, int sig
             const float v = in ? fabsf(g[j]) : 0.f;
             if (in) vmx = fmaxf(vmx, v);
             take(in && ok(v), j, v);
+        }
         }
         __syncthreads();
         const int nc = s_n;
@@ -400,7 +423,7 @@ __device__ __forceinline__ void certify_row(const SelectArgs& a, int row, int si
     }
 }
 
-template <int KMAX>
+template <int KMAX, bool GROUPS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void select_kernel(SelectArgs a)
 {
     __shared__ bool s_certify;
@@ -409,7 +432,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void s
     const int row = blockIdx.x;
     if (row >= n_act) return;
     const int sig = a.act ? a.act[row] : row;
-    select_row<KMAX>(a, row, sig, &s_certify);
+    select_row<KMAX, GROUPS>(a, row, sig, GROUPS && a.excl != nullptr && n_act >= a.gm_lo, &s_certify);
     __syncthreads();
     if (s_certify) certify_row(a, row, sig);
 }
@@ -420,10 +443,10 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream)
 {
     if (a.p_grid <= 0) return hipSuccess;
     if (a.k <= 0 || a.k > 64 || a.k > a.selcap) return hipErrorInvalidValue;
-    if (a.k <= 32)
-        hipLaunchKernelGGL(select_kernel<32>, dim3(a.p_grid), dim3(256), 0, stream, a);
-    else
-        hipLaunchKernelGGL(select_kernel<64>, dim3(a.p_grid), dim3(256), 0, stream, a);
+    const bool groups = a.gm != nullptr && a.gm_lo <= a.p_grid;
+    const auto kernel = a.k <= 32 ? (groups ? select_kernel<32, true> : select_kernel<32, false>)
+                                  : (groups ? select_kernel<64, true> : select_kernel<64, false>);
+    hipLaunchKernelGGL(kernel, dim3(a.p_grid), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -1147,3 +1147,28 @@ def test_default_product_shapes(n, m, screen):
         assert torch.equal(a.correlate(R), b.correlate(R)), p
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("screen", ["fp32", "bf16"])
+@pytest.mark.parametrize("n,m,p,kw", [(40, 8193, 70, {}), (40, 8200, 600, {"graph": True}), (64, 12345, 65, {"max_outer": 9, "graph": True}),
+                                      (40, 9000, 130, {"rho": 30}), (40, 33000, 80, {"rho": 64}), (32, 70000, 64, {})])
+def test_selection_by_groups(n, m, p, kw, screen):
+    """The selection that reads only the groups whose largest value can matter, against the one over whole rows
+    (a product shape that keeps no groups): the same atoms, so the same results.  Lengths that are no multiple of a
+    group, a tile or 4, duplicated atoms (equal values across groups), a zero signal and one that is not finite."""
+    pk = _lib()
+    At = bi.gaussian_dictionary(n, m, 51)
+    At[m // 2:m // 2 + 40] = At[:40]
+    Bt = np.random.default_rng(m + p).standard_normal((p, n)).astype(np.float32)
+    Bt[3] = 0.0
+    Bt[5, 1] = np.inf
+    kw = {"rho": 6, **kw}
+    a = pk.Solver(to_dev(At), 0.3, mode="rel", screen=screen, gram_table=False, **kw)
+    b = pk.Solver(to_dev(At), 0.3, mode="rel", screen=screen, gram_table=False, **kw)
+    a.set_tuning([13, 3, 4])
+    b.set_tuning([5, 5, 4])
+    ra, rb = a.solve(to_dev(Bt)), b.solve(to_dev(Bt))
+    for key in ("x_val", "x_idx", "supp_len", "iters", "lambda", "objective", "status"):
+        assert torch.equal(ra[key].nan_to_num(), rb[key].nan_to_num()), key
+    a.close()
+    b.close()
