@@ -1166,8 +1166,9 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
             hipLaunchKernelGGL(grow_kernel, dim3(std::min(n_grid, 512)), dim3(256), 0, q, ga);
             HIPC(hipGetLastError());
         }
-        // factors that start in global memory take the kernel whose appends and solves read them in
-        // one pass (its larger register footprint stays out of the LDS-factor kernel)
+        // Factors that start in global memory take the kernels that append up to eight atoms and solve in one pass
+        // over them (their registers, two waves per SIMD, stay out of the LDS-factor kernels); of these the one that
+        // addresses the per-slot vectors as LDS where they are there.
         if (so.zs_lds)
             hipLaunchKernelGGL(solve_block_kernel, dim3(n_grid), dim3(256), lds, q, so);
         else if (!so.rinv_lds)
