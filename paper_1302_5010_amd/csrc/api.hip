@@ -150,7 +150,7 @@ struct bmpl_ctx {
     int selcap = 0;
     // arena of the per-signal slot blocks (device state, its chunks, and pinned host views)
     Arena* arena_dev = nullptr;
-    Arena* h_arena = nullptr;     // pinned: the chunk list as the host last wrote it
+    Arena* h_arena = nullptr;     // pinned: the host's own copy of the chunk list
     Arena* h_arena_rd = nullptr;  // pinned: top / starved / reserve read back with the running count
     unsigned long long arena_total = 0;   // doubles over all chunks
     float* Bw = nullptr;          // [p_cap][kpad]
@@ -274,6 +274,8 @@ void fold_timing(bmpl_ctx* c, size_t first, size_t last)
 
 namespace {
 
+__global__ void arena_put_kernel(Arena* a, ArenaChunk c) { arena_put(*a, c); }
+
 // A create-time block of `count` values from the block pool; bmpl_destroy puts it back.
 template <class T>
 hipError_t pool_alloc(bmpl_ctx* c, T** p, size_t count)
@@ -320,7 +322,7 @@ void free_signals(bmpl_ctx* c)
 }
 
 // Add a chunk of at least `min_doubles` (preferably `want_doubles`) to the slot-block arena; the
-// device sees the new chunk list from the next kernel on `s` on.
+// device sees the new chunk from the next kernel on `s` on.
 bmpl_status arena_add(bmpl_ctx* c, unsigned long long min_doubles, unsigned long long want_doubles, hipStream_t s)
 {
     Arena& H = *c->h_arena;
@@ -337,16 +339,12 @@ bmpl_status arena_add(bmpl_ctx* c, unsigned long long min_doubles, unsigned long
     if (e != hipSuccess)
         return fail(BMPL_E_NOMEM, "slot-block arena: allocating %.3g GB failed: %s", 8.0 * sz / 1e9,
                     hipGetErrorString(e));
-    const int k = H.nchunks;
-    H.base[k] = p;
-    H.start[k] = k ? H.start[k - 1] + H.size[k - 1] : 0;
-    H.size[k] = sz;
-    H.nchunks = k + 1;
+    const ArenaChunk chunk = arena_next(H, p, sz);
+    arena_put(H, chunk);
     c->arena_total += sz;
-    // the chunk list only (top, starved and reserve stay as the device has them)
-    const size_t off = offsetof(Arena, nchunks);
-    HIPC(hipMemcpyAsync(reinterpret_cast<char*>(c->arena_dev) + off, reinterpret_cast<char*>(c->h_arena) + off,
-                        sizeof(Arena) - off, hipMemcpyHostToDevice, s));
+    // (top, starved and reserve stay as the device has them)
+    hipLaunchKernelGGL(arena_put_kernel, dim3(1), dim3(1), 0, s, c->arena_dev, chunk);
+    HIPC(hipGetLastError());
     return BMPL_OK;
 }
 

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "arena_list.h"
+
 namespace bmpl {
 
 // Packed lower-triangular row-major storage: row i starts at tri(i) and holds
@@ -16,23 +18,6 @@ __device__ inline double sym_at(const double* P, int u, int v)
 {
     return u >= v ? P[tri(u) + v] : P[tri(v) + u];
 }
-
-// Device arena of the per-signal slot blocks: a list of chunks viewed as one range of doubles.  Blocks
-// are handed out by bumping `top` (a block never straddles two chunks); a signal whose active set
-// outgrows its block takes a larger one and copies its state over.  The arena is reset for every solve.
-constexpr int ARENA_CHUNKS = 32;
-struct Arena {
-    int n_act[2];                 // running-signal counts of the two running lists (read back with the rest)
-    unsigned long long top;       // doubles handed out in this solve (offset in the chunk list)
-    unsigned long long starved;   // block requests that found no room (the host adds a chunk)
-    unsigned long long reserve;   // doubles the running signals may request during the next iterations
-    unsigned long long grow_base; // offset of the blocks the last stop test placed for the grow list
-    int nchunks;
-    int pad_;
-    double* base[ARENA_CHUNKS];
-    unsigned long long start[ARENA_CHUNKS];   // offset of each chunk in the list (start[c+1] = start[c] + size[c])
-    unsigned long long size[ARENA_CHUNKS];    // doubles
-};
 
 // N chunks of four consecutive correlations of a row per thread (thread t: g[base0 + 1024 q + 4 t ..
 // + 3], q < N) with the words of the I bitmap that hold their bits (chunk_bits).  The loads are only issued here:

@@ -1172,3 +1172,22 @@ def test_selection_by_groups(n, m, p, kw, screen):
         assert torch.equal(ra[key].nan_to_num(), rb[key].nan_to_num()), key
     a.close()
     b.close()
+
+
+def test_arena_chunks_added_while_an_iteration_runs():
+    """Up to 64 signals without a cap, so that the host loop adds arena chunks with an iteration enqueued behind the
+    one it has read: large supports from a small arena (a first solve of one signal), against captured segments,
+    whose additions wait for the stream."""
+    pk = _lib()
+    n, m, p = 300, 2400, 48
+    At = to_dev(bi.gaussian_dictionary(n, m, 33))
+    Bt = to_dev(np.random.default_rng(34).standard_normal((p, n)).astype(np.float32))
+    res = []
+    for graph in (False, True):
+        s = pk.Solver(At, 0.02, mode="rel", rho=20, graph=graph)
+        s.solve(Bt[:1].contiguous())
+        res.append(s.solve(Bt))
+        s.close()
+    for key in ("x_val", "x_idx", "supp_len", "iters", "objective", "status"):
+        assert torch.equal(res[0][key], res[1][key]), key
+    assert int(res[0]["supp_len"].min()) > 150
