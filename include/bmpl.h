@@ -228,7 +228,10 @@ const char* bmpl_last_error(const bmpl_ctx* c);
  * screening precision with float32 accumulation (FP8 contexts: e4m3 operands
  * with power-of-two scales per atom and per residual, the ranking product).  This is the full
  * matrix-vector product g = A^T xi of Algorithm 1, step 3, for p residuals at
- * once.  ldg >= m.  Errors: BMPL_E_INVALID.
+ * once.  ldg >= m.  Asynchronous on hip_stream in every precision: R must stay unchanged and G is not
+ * valid until the stream has run the call.  The staged residuals belong to the context: float32 calls on
+ * several streams are ordered by the caller, a bfloat16 or FP8 context's call waits on the device for the
+ * call before it, on whatever stream that was.  Errors: BMPL_E_INVALID.
  */
 bmpl_status bmpl_correlate(bmpl_ctx* c, const float* R_dev, int64_t ldr, int32_t p,
                            float* G_dev, int64_t ldg, void* hip_stream);

@@ -291,7 +291,8 @@ class Solver:
         _check(_lib.bmpl_reset_timing(self._h), "bmpl_reset_timing")
 
     def correlate(self, Rt: torch.Tensor, stream=None) -> torch.Tensor:
-        """G (p, m) with G[i, j] = a_j^T r_i for the rows r_i of ``Rt`` ((p, n) float32)."""
+        """G (p, m) with G[i, j] = a_j^T r_i for the rows r_i of ``Rt`` ((p, n) float32), in every precision
+        enqueued on ``stream`` (default: the current one); another stream that reads G waits for that one."""
         Rt = _dev(Rt, torch.float32, "Rt")
         p = Rt.shape[0]
         G = torch.empty((p, self.m), dtype=torch.float32, device=Rt.device)

@@ -1191,3 +1191,45 @@ def test_arena_chunks_added_while_an_iteration_runs():
     for key in ("x_val", "x_idx", "supp_len", "iters", "objective", "status"):
         assert torch.equal(res[0][key], res[1][key]), key
     assert int(res[0]["supp_len"].min()) > 150
+
+
+@pytest.mark.parametrize("screen", ["bf16", "fp8"])
+@pytest.mark.parametrize("per_thread", [False, True])
+def test_correlate_calls_on_two_streams(screen, per_thread):
+    """A call enqueued on another stream while the last one's product runs: both stage their residuals in the same
+    rows, and only the library orders them (the inputs are complete before either).  The second stream is another
+    handle, or the same one for another stream (hipStreamPerThread in two threads).  Bits as one call at a time."""
+    import ctypes
+    import threading
+    pk = _lib()
+    n, m, p = 1024, 20000, 3000
+    s = pk.Solver(to_dev(bi.gaussian_dictionary(n, m, 44)), 0.1, screen=screen, gram_table=False)
+    R = [torch.randn(p, n, generator=torch.Generator().manual_seed(k)).cuda() for k in (1, 2)]
+    ref = []
+    for r in R:
+        ref.append(s.correlate(r))
+        torch.cuda.synchronize()
+    G = [torch.zeros_like(ref[0]) for _ in R]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL("libamdhip64.so")
+    rc, turn = [], [threading.Event(), threading.Event(), threading.Event()]
+
+    def call(k):                                  # the second call after the first, both threads alive until both ran
+        turn[k].wait(30)
+        handle = 2 if per_thread else streams[k].cuda_stream     # hipStreamPerThread
+        rc.append(pk._binding._lib.bmpl_correlate(s._h, R[k].data_ptr(), n, p, G[k].data_ptr(), m, handle))
+        turn[k + 1].set()
+        turn[2].wait(30)
+        rc.append(hip.hipStreamSynchronize(ctypes.c_void_p(handle)))
+
+    threads = [threading.Thread(target=call, args=(k,)) for k in (0, 1)]
+    for t in threads:
+        t.start()
+    turn[0].set()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert rc == [0, 0, 0, 0]
+    assert torch.equal(G[0], ref[0]) and torch.equal(G[1], ref[1])
+    s.close()
