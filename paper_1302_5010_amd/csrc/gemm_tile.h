@@ -516,10 +516,10 @@ __device__ __forceinline__ void mfma_tile_loop_pipe(const __bf16* __restrict__ X
     wait_vm0();   // no copy into this workgroup's LDS is left in flight
 }
 
-// The element `off` bytes past a row address that is the same in every lane (a scalar base and a 32-bit lane offset
-// in the instruction).
-template <class T>
-__device__ __forceinline__ T& at_bytes(T* row, uint32_t off)
+// The element `off` bytes past a row address that is the same in every lane (with a 32-bit offset: a scalar base and
+// the lane's offset in the instruction).
+template <class T, class OFF>
+__device__ __forceinline__ T& at_bytes(T* row, OFF off)
 {
     return *reinterpret_cast<T*>(reinterpret_cast<char*>(row) + off);
 }

@@ -50,15 +50,19 @@ __device__ __forceinline__ T* epi_row(T* base, int64_t ld, int r0, int c0, int r
 {
     return base + (int64_t)(r0 + 8 * (r >> 2) + (r & 3)) * ld + c0;
 }
-template <bool BIAS>
+// The 32-bit lane offset holds for rows of at most EPI_LD_MAX entries (16 ldc + 128 bytes).
+constexpr int64_t EPI_LD_MAX = 1 << 26;
+// FAR: rows longer than that, a 64-bit offset per lane.
+template <bool BIAS, bool FAR = false>
 struct EpiStore {            // C[r][c] = v (+ bias[c])
-    static constexpr bool TILE256 = true;
+    static constexpr bool TILE256 = !FAR;   // (rows of 256 MB: not worth kernels of its own)
     float* C; int64_t ldc; const float* bias;
     __device__ __forceinline__ float col(int c) const { return BIAS ? bias[c] : 0.f; }
     template <bool FULL>
     __device__ __forceinline__ void block(const floatx16& v, float b, int r0, int c0, int h, int l32, int M) const
     {
-        const uint32_t off = 4u * (uint32_t)(4 * h * (int)ldc + l32);
+        using Off = std::conditional_t<FAR, uint64_t, uint32_t>;
+        const Off off = 4 * ((Off)(4 * h) * (Off)ldc + (Off)l32);
 #pragma unroll
         for (int r = 0; r < 16; ++r)
             if (FULL || r0 + 4 * h + 8 * (r >> 2) + (r & 3) < M)
@@ -846,6 +850,8 @@ hipError_t mlp_signals_bf16(const float* B, int64_t ldb, int n, int p, uint16_t*
 hipError_t mlp_gemm_store(const uint16_t* X, int64_t ldx, int M, const uint16_t* W, int64_t ldw, int N, int kpad,
                           float* C, int64_t ldc, const float* bias, hipStream_t s)
 {
+    if (bias && ldc > EPI_LD_MAX) return launch_gemm(X, ldx, M, W, ldw, N, kpad, EpiStore<true, true>{C, ldc, bias}, s);
+    if (ldc > EPI_LD_MAX) return hipErrorInvalidValue;
     if (bias) return launch_gemm(X, ldx, M, W, ldw, N, kpad, EpiStore<true>{C, ldc, bias}, s);
     return launch_gemm(X, ldx, M, W, ldw, N, kpad, EpiStore<false>{C, ldc, nullptr}, s);
 }

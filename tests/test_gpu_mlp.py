@@ -357,3 +357,24 @@ def test_topk_row_lengths_and_strides(L, lds, k):
     ref = mo.propose(S[:, :L].astype(np.float64), kk)
     np.testing.assert_array_equal(got[:, :kk], ref)
     assert np.all(got[:, kk:] == -1)
+
+
+@pytest.mark.parametrize("p,lds", [(8, 1 << 28), (40, (1 << 26) + 64), (40, 1 << 26)])
+def test_forward_into_rows_far_apart(p, lds):
+    """Scores written with a row stride at and past the epilogue's 32-bit lane offset: the bits of the compact call."""
+    pk = _lib()
+    n, m, d, h = 48, 100, 64, 64
+    net = pk.ProposalNet(to_dev(bi.gaussian_dictionary(n, m, 3)), torch.randn(m, d, device="cuda"), h, max_batch=64)
+    net.set_params(0.2 * torch.randn(pk.mlp_param_count(d, h, m), device="cuda"))
+    B = torch.randn(p, n, device="cuda")
+    ref = net.forward(B)
+    S = torch.empty((p - 1) * lds + m, dtype=torch.float32, device="cuda")
+    rows = S.as_strided((p, m), (lds, 1))
+    rows.fill_(float("nan"))
+    rc = pk._binding._lib.bmpl_mlp_forward(net._h, B.data_ptr(), n, p, S.data_ptr(), lds,
+                                           torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0 and torch.equal(rows, ref)
+    net.close()
+    del S, rows
+    torch.cuda.empty_cache()
