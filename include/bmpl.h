@@ -210,8 +210,16 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p,
                        const double* lambda_dev, const int32_t* warm_idx_dev, int32_t warm_k,
                        const bmpl_result* out, void* hip_stream);
 
-/* Release the context and all its device memory.  NULL is accepted. */
+/*
+ * Release the context and its device memory.  NULL is accepted.  Of the blocks that bmpl_create allocated
+ * (dictionary copies, Gram table) up to 1 GiB per device stay with the library for the next context; they
+ * are given back after eight further contexts have been destroyed, when an allocation of the library
+ * fails, or by bmpl_trim.
+ */
 bmpl_status bmpl_destroy(bmpl_ctx* c);
+
+/* Give the blocks kept from destroyed contexts, on every device, back to the driver. */
+bmpl_status bmpl_trim(void);
 
 /* Message describing the last failure of a call made on this thread (kept per thread, so it also
  * covers a bmpl_create that returned no context; c may be NULL); valid until the next call. */

@@ -24,4 +24,5 @@ from ._binding import (  # noqa: F401
     library_path,
     mlp_param_count,
     topk,
+    trim,
 )

@@ -85,6 +85,7 @@ def _load():
                                 ctypes.POINTER(vp)]
     lib.bmpl_solve.argtypes = [vp, vp, i64, i32, vp, vp, i32, ctypes.POINTER(_Result), vp]
     lib.bmpl_destroy.argtypes = [vp]
+    lib.bmpl_trim.argtypes = []
     lib.bmpl_last_error.restype = ctypes.c_char_p
     lib.bmpl_last_error.argtypes = [ctypes.c_void_p]
     lib.bmpl_correlate.argtypes = [vp, vp, i64, i32, vp, i64, vp]
@@ -108,7 +109,7 @@ def _load():
     lib.bmpl_mlp_adam_step.argtypes = [vp, vp, ctypes.POINTER(AdamParams), vp]
     lib.bmpl_mlp_propose.argtypes = [vp, vp, i64, i32, i32, vp, i32, vp]
     lib.bmpl_topk.argtypes = [vp, i64, i32, i32, i32, vp, i32, vp]
-    for f in ("bmpl_options_default", "bmpl_create", "bmpl_solve", "bmpl_destroy", "bmpl_correlate",
+    for f in ("bmpl_options_default", "bmpl_create", "bmpl_solve", "bmpl_destroy", "bmpl_trim", "bmpl_correlate",
               "bmpl_correlate_noalloc",
               "bmpl_select", "bmpl_get_timing", "bmpl_reset_timing", "bmpl_gram_table", "bmpl_autotune",
               "bmpl_set_tuning", "bmpl_mlp_create", "bmpl_mlp_destroy", "bmpl_mlp_set_params",
@@ -332,6 +333,11 @@ class Solver:
                                     sel.data_ptr(), nsel.data_ptr(), vmax.data_ptr(), _stream_ptr(stream)),
                    "bmpl_select")
         return sel, nsel, vmax
+
+
+def trim() -> None:
+    """Give device memory kept from closed solvers (up to 1 GiB per device) back to the driver."""
+    _check(_lib.bmpl_trim(), "bmpl_trim")
 
 
 def topk(S: torch.Tensor, k: int, L: int | None = None, stream=None) -> torch.Tensor:

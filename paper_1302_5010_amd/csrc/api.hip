@@ -743,6 +743,12 @@ bmpl_status bmpl_destroy(bmpl_ctx* c)
     return BMPL_OK;
 }
 
+bmpl_status bmpl_trim(void)
+{
+    (void)block_pool().drop(-1);
+    return BMPL_OK;
+}
+
 bmpl_status bmpl_correlate(bmpl_ctx* c, const float* R_dev, int64_t ldr, int32_t p, float* G_dev, int64_t ldg,
                            void* hip_stream)
 {

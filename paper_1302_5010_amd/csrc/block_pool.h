@@ -5,10 +5,12 @@
 // that each time: mapping and clearing 288 MB for 6000 atoms costs 0.4 ms as long as the driver has cleared memory
 // at hand and 7 ms when it does not, against 0.74 ms for computing the table itself.
 //
-// Bounded: at most POOL_BYTES per device stay here, the oldest block leaves first; a block that no context has
-// taken within POOL_AGE destroyed contexts is given back to the driver, and every block of the device is when an
-// allocation of the library fails (the allocation is then tried again).  Blocks are put here only after the device
-// has been synchronised, so a block taken has no work in flight on any stream; a mutex serialises the threads.
+// Bounded: at most POOL_BYTES per device stay here (a table of 11 000 atoms; larger blocks are freed at once, as
+// allocators of the same process cannot take memory back from here), the oldest block leaves first; a block that no
+// context has taken within POOL_AGE destroyed contexts is given back to the driver, and every block of the device is
+// when an allocation of the library fails (the allocation is then tried again); bmpl_trim gives back all of them.
+// Blocks are put here only after the device has been synchronised, so a block taken has no work in flight on any
+// stream; a mutex serialises the threads.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -18,7 +20,7 @@
 
 namespace bmpl {
 
-constexpr size_t POOL_BYTES = (size_t)4 << 30;
+constexpr size_t POOL_BYTES = (size_t)1 << 30;
 constexpr int POOL_AGE = 8;
 
 class BlockPool {
@@ -96,13 +98,13 @@ public:
         return sum;
     }
 
-    // Give every block of `dev` back; true if there was one.
+    // Give every block of `dev` (-1: of every device) back; true if there was one.
     bool drop(int dev)
     {
         std::lock_guard<std::mutex> lk(mu_);
         bool any = false;
         for (size_t i = 0; i < kept_.size();) {
-            if (kept_[i].dev == dev) {
+            if (dev < 0 || kept_[i].dev == dev) {
                 (void)hipFree(kept_[i].p);
                 kept_.erase(kept_.begin() + i);
                 any = true;

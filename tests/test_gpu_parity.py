@@ -1233,3 +1233,26 @@ def test_correlate_calls_on_two_streams(screen, per_thread):
     assert rc == [0, 0, 0, 0]
     assert torch.equal(G[0], ref[0]) and torch.equal(G[1], ref[1])
     s.close()
+
+
+def test_trim_gives_kept_memory_back():
+    """What destroyed contexts leave behind is bounded (1 GiB a device), and trim() returns all of it to the driver."""
+    pk = _lib()
+    At = to_dev(bi.gaussian_dictionary(64, 9000, 45))       # a table of 648 MB
+    free = lambda: torch.cuda.mem_get_info()[0]
+
+    def use(n):
+        for s in [pk.Solver(At, 0.1) for _ in range(n)]:
+            s.close()
+
+    use(1)
+    pk.trim()
+    before = free()
+    use(3)
+    assert before - free() <= 1 << 30
+    pk.trim()
+    assert free() >= before
+    s = pk.Solver(At, 0.1)                                   # and the library goes on without it
+    assert torch.equal(s.gram_table(), s.gram_table().T)
+    s.close()
+    pk.trim()
