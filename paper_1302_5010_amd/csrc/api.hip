@@ -198,7 +198,8 @@ struct bmpl_ctx {
 
     // the create-time blocks (dictionary copies, Gram table) and their sizes: they return to the block pool
     struct Pooled { void* p; size_t bytes; };
-    std::vector<Pooled> pooled;
+    Pooled pooled[8];
+    int n_pooled = 0;
 
     // graph capture of iteration segments (BMPL_FLAG_GRAPH)
     hipStream_t cap_stream = nullptr;
@@ -285,7 +286,7 @@ hipError_t pool_alloc(bmpl_ctx* c, T** p, size_t count)
     size_t got = 0;
     const hipError_t e = block_pool().take(c->device, &q, count * sizeof(T), &got);
     *p = e == hipSuccess ? static_cast<T*>(q) : nullptr;
-    if (e == hipSuccess) c->pooled.push_back({q, got});
+    if (e == hipSuccess) c->pooled[c->n_pooled++] = {q, got};   // five blocks at most
     return e;
 }
 
@@ -295,11 +296,11 @@ void pool_release(bmpl_ctx* c)
     int cur = 0;
     const bool known = hipGetDevice(&cur) == hipSuccess;
     const bool idle = known && hipSetDevice(c->device) == hipSuccess && hipDeviceSynchronize() == hipSuccess;
-    for (const auto& b : c->pooled) {
-        if (idle) block_pool().put(c->device, b.p, b.bytes);
-        else (void)hipFree(b.p);
+    for (int i = 0; i < c->n_pooled; ++i) {
+        if (idle) block_pool().put(c->device, c->pooled[i].p, c->pooled[i].bytes);
+        else (void)hipFree(c->pooled[i].p);
     }
-    c->pooled.clear();
+    c->n_pooled = 0;
     block_pool().age(c->device);
     if (known) (void)hipSetDevice(cur);
     (void)hipGetLastError();

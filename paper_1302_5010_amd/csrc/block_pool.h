@@ -10,37 +10,38 @@
 // context has taken within POOL_AGE destroyed contexts is given back to the driver, and every block of the device is
 // when an allocation of the library fails (the allocation is then tried again); bmpl_trim gives back all of them.
 // Blocks are put here only after the device has been synchronised, so a block taken has no work in flight on any
-// stream; a mutex serialises the threads.
+// stream; a mutex serialises the threads.  The list is an array of fixed size: bmpl_destroy passes through here, and
+// neither allocates nor throws.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <mutex>
-#include <vector>
 
 namespace bmpl {
 
 constexpr size_t POOL_BYTES = (size_t)1 << 30;
 constexpr int POOL_AGE = 8;
+constexpr int POOL_BLOCKS = 64;
 
 class BlockPool {
 public:
     // A block of at least `bytes` on the current device `dev` (a kept one when its size is at most 1/8 larger).
-    hipError_t take(int dev, void** out, size_t bytes, size_t* got)
+    hipError_t take(int dev, void** out, size_t bytes, size_t* got) noexcept
     {
         *out = nullptr;
         if (bytes == 0) bytes = 1;
         {
             std::lock_guard<std::mutex> lk(mu_);
             int best = -1;
-            for (int i = 0; i < (int)kept_.size(); ++i)
+            for (int i = 0; i < n_; ++i)
                 if (kept_[i].dev == dev && kept_[i].bytes >= bytes && kept_[i].bytes <= bytes + bytes / 8 &&
                     (best < 0 || kept_[i].bytes < kept_[best].bytes))
                     best = i;
             if (best >= 0) {
                 *out = kept_[best].p;
                 *got = kept_[best].bytes;
-                kept_.erase(kept_.begin() + best);
+                erase(best);
                 return hipSuccess;
             }
         }
@@ -54,59 +55,46 @@ public:
     }
 
     // Take over a block (the device is synchronised and `dev` current).
-    void put(int dev, void* p, size_t bytes)
+    void put(int dev, void* p, size_t bytes) noexcept
     {
         std::lock_guard<std::mutex> lk(mu_);
         if (bytes > POOL_BYTES) {
             (void)hipFree(p);
             return;
         }
-        kept_.push_back({p, bytes, dev, 0});
-        size_t sum = 0;
-        for (const auto& b : kept_) sum += b.dev == dev ? b.bytes : 0;
-        for (size_t i = 0; i < kept_.size() && sum > POOL_BYTES;) {
-            if (kept_[i].dev == dev) {
-                sum -= kept_[i].bytes;
-                (void)hipFree(kept_[i].p);
-                kept_.erase(kept_.begin() + i);
-            } else {
-                ++i;
-            }
+        if (n_ == POOL_BLOCKS) free_block(0);
+        kept_[n_++] = {p, bytes, dev, 0};
+        for (int i = 0; i < n_ && sum(dev) > POOL_BYTES;) {
+            if (kept_[i].dev == dev) free_block(i);
+            else ++i;
         }
     }
 
     // One more context of `dev` was destroyed: blocks that have waited too long go back.
-    void age(int dev)
+    void age(int dev) noexcept
     {
         std::lock_guard<std::mutex> lk(mu_);
-        for (size_t i = 0; i < kept_.size();) {
-            if (kept_[i].dev == dev && ++kept_[i].age > POOL_AGE) {
-                (void)hipFree(kept_[i].p);
-                kept_.erase(kept_.begin() + i);
-            } else {
-                ++i;
-            }
+        for (int i = 0; i < n_;) {
+            if (kept_[i].dev == dev && ++kept_[i].age > POOL_AGE) free_block(i);
+            else ++i;
         }
     }
 
     // Bytes kept for `dev`.
-    size_t kept(int dev)
+    size_t kept(int dev) noexcept
     {
         std::lock_guard<std::mutex> lk(mu_);
-        size_t sum = 0;
-        for (const auto& b : kept_) sum += b.dev == dev ? b.bytes : 0;
-        return sum;
+        return sum(dev);
     }
 
     // Give every block of `dev` (-1: of every device) back; true if there was one.
-    bool drop(int dev)
+    bool drop(int dev) noexcept
     {
         std::lock_guard<std::mutex> lk(mu_);
         bool any = false;
-        for (size_t i = 0; i < kept_.size();) {
+        for (int i = 0; i < n_;) {
             if (dev < 0 || kept_[i].dev == dev) {
-                (void)hipFree(kept_[i].p);
-                kept_.erase(kept_.begin() + i);
+                free_block(i);
                 any = true;
             } else {
                 ++i;
@@ -118,7 +106,24 @@ public:
 private:
     struct Block { void* p; size_t bytes; int dev; int age; };
     std::mutex mu_;
-    std::vector<Block> kept_;
+    Block kept_[POOL_BLOCKS];     // the oldest first
+    int n_ = 0;
+
+    void erase(int i) noexcept
+    {
+        for (--n_; i < n_; ++i) kept_[i] = kept_[i + 1];
+    }
+    void free_block(int i) noexcept
+    {
+        (void)hipFree(kept_[i].p);
+        erase(i);
+    }
+    size_t sum(int dev) const noexcept
+    {
+        size_t b = 0;
+        for (int i = 0; i < n_; ++i) b += kept_[i].dev == dev ? kept_[i].bytes : 0;
+        return b;
+    }
 };
 
 // Never destroyed: the HIP runtime may be gone before a static destructor runs (the process's end frees all).

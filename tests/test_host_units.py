@@ -51,3 +51,96 @@ int main()
     return 0;
 }
 """)
+
+
+def test_block_pool_bounds_and_no_allocation_of_its_own(tmp_path):
+    """The pool of device blocks against stand-ins for hipMalloc and hipFree, with every C++ allocation failing (a
+    context's destruction passes through it, and nothing may leave a C entry point as an exception): best fit within an
+    eighth, the bounds in bytes and blocks with the oldest leaving first, ageing, dropping one device and all, and a
+    failed device allocation tried again after a drop.  Every block is freed exactly once."""
+    hip = tmp_path / "hip"
+    hip.mkdir()
+    (hip / "hip_runtime.h").write_text("""
+#pragma once
+#include <cstddef>
+typedef int hipError_t;
+enum { hipSuccess = 0, hipErrorOutOfMemory = 2 };
+hipError_t hipMalloc(void**, size_t);
+hipError_t hipFree(void*);
+hipError_t hipGetLastError();
+""")
+    _run(tmp_path, r"""
+#include <cstdio>
+#include <cstdlib>
+#include <new>
+#include "block_pool.h"
+static bool no_new = false;
+void* operator new(size_t n) { if (no_new) throw std::bad_alloc(); return std::malloc(n); }
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+static char mem[4096];
+static int at = 0, live = 0;
+static bool state[4096], fail_once = false;
+hipError_t hipMalloc(void** p, size_t)
+{
+    if (fail_once) { fail_once = false; return hipErrorOutOfMemory; }
+    state[at] = true; ++live; *p = mem + at++;
+    return hipSuccess;
+}
+hipError_t hipFree(void* p)
+{
+    const int i = (int)((char*)p - mem);
+    if (!state[i]) { std::printf("freed twice\n"); std::exit(1); }
+    state[i] = false; --live;
+    return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+using namespace bmpl;
+int main()
+{
+    BlockPool& pool = block_pool();
+    no_new = true;
+    void* p[200]; size_t got = 0;
+    // best fit within an eighth, on its own device only
+    const size_t sizes[3] = {800, 1000, 1100};
+    for (int i = 0; i < 3; ++i) CHECK(pool.take(0, &p[i], sizes[i], &got) == hipSuccess && got == sizes[i]);
+    for (int i = 0; i < 3; ++i) pool.put(0, p[i], sizes[i]);
+    void* q = nullptr;
+    CHECK(pool.take(1, &q, 1000, &got) == hipSuccess && q != p[1]);
+    pool.put(1, q, got);
+    CHECK(pool.take(0, &q, 990, &got) == hipSuccess && q == p[1] && got == 1000);
+    CHECK(pool.take(0, &q, 990, &got) == hipSuccess && q == p[2] && got == 1100);
+    CHECK(pool.take(0, &q, 600, &got) == hipSuccess && q != p[0]);
+    CHECK(hipFree(q) == hipSuccess);
+    pool.put(0, p[1], 1000);
+    pool.put(0, p[2], 1100);
+    CHECK(pool.kept(0) == 2900 && pool.kept(1) == 1000 && live == 4);
+    // a failed allocation gives the device's blocks back and is tried again
+    fail_once = true;
+    CHECK(pool.take(0, &q, 5000, &got) == hipSuccess && pool.kept(0) == 0 && pool.kept(1) == 1000 && live == 2);
+    pool.put(0, q, got);
+    CHECK(pool.drop(-1) && !pool.drop(-1) && live == 0);
+    // the bound in bytes: the oldest leave first; a block above it never stays
+    const size_t third = POOL_BYTES / 3;
+    for (int i = 0; i < 4; ++i) CHECK(pool.take(0, &p[i], third, &got) == hipSuccess);
+    for (int i = 0; i < 4; ++i) pool.put(0, p[i], third);
+    CHECK(pool.kept(0) == 3 * third && live == 3 && !state[(char*)p[0] - mem]);
+    CHECK(pool.take(0, &q, POOL_BYTES + 1, &got) == hipSuccess);
+    pool.put(0, q, POOL_BYTES + 1);
+    CHECK(live == 3);
+    // ageing, per device
+    for (int i = 0; i < POOL_AGE; ++i) pool.age(0);
+    CHECK(live == 3);
+    pool.age(1);
+    CHECK(live == 3);
+    pool.age(0);
+    CHECK(live == 0 && pool.kept(0) == 0);
+    // the bound in blocks
+    for (int i = 0; i < POOL_BLOCKS + 20; ++i) CHECK(pool.take(0, &p[i], 16, &got) == hipSuccess);
+    for (int i = 0; i < POOL_BLOCKS + 20; ++i) pool.put(0, p[i], 16);
+    CHECK(live == POOL_BLOCKS && !state[(char*)p[19] - mem] && state[(char*)p[20] - mem]);
+    CHECK(pool.drop(0) && live == 0);
+    return 0;
+}
+""", "-I", str(tmp_path))
