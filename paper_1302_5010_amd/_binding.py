@@ -298,8 +298,10 @@ class Solver:
         p = Rt.shape[0]
         G = torch.empty((p, self.m), dtype=torch.float32, device=Rt.device)
         if stream is not None:   # the call returns before the product has run: both stay alive until it has
-            Rt.record_stream(stream)
-            G.record_stream(stream)
+            ts = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(_stream_ptr(stream),
+                                                                                                Rt.device)
+            Rt.record_stream(ts)
+            G.record_stream(ts)
         with torch.cuda.device(Rt.device):
             _check(_lib.bmpl_correlate(self._h, Rt.data_ptr(), self.n, p, G.data_ptr(), self.m,
                                        _stream_ptr(stream)), "bmpl_correlate")

@@ -1256,3 +1256,23 @@ def test_trim_gives_kept_memory_back():
     assert torch.equal(s.gram_table(), s.gram_table().T)
     s.close()
     pk.trim()
+
+
+def test_correlate_takes_any_stream_object():
+    """Anything with a cuda_stream handle is a stream, as in every other call: another library's, the default one's 0."""
+    pk = _lib()
+
+    class Handle:
+        def __init__(self, h):
+            self.cuda_stream = h
+
+    s = pk.Solver(to_dev(bi.gaussian_dictionary(50, 200, 46)), 0.1)
+    R = torch.randn(7, 50, device="cuda")
+    ref = s.correlate(R)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for h in (side.cuda_stream, 0):
+        G = s.correlate(R, stream=Handle(h))
+        torch.cuda.synchronize()
+        assert torch.equal(G, ref)
+    s.close()
