@@ -1188,7 +1188,9 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         // 1024 x 20000, |S| around 8: 4096 signals 3.15 ms per solve with 256 threads and 2.67 with a wave, 2048
         // signals 2.08 and 1.91, 1024 signals the same; 2048 x 16384, |S| to 30: 2.84 and 2.91 with 4096 signals;
         // 128 x 512: 8192 signals 2.01 and 1.40, 512 signals 0.53 and 0.51.
-        else if (so.kv <= 64 && c->Q && c->kpad <= 1024 && n_grid >= 2 * c->kpad)
+        // By the batch's size, not by the signals still running: a captured graph does not know those, and the two
+        // kernels sum in different orders, so the host loop's results would not be the graph's.
+        else if (so.kv <= 64 && c->Q && c->kpad <= 1024 && w.p >= 2 * c->kpad)
             hipLaunchKernelGGL(solve_wave_kernel, dim3(n_grid), dim3(64), lds, q, so);
         else
             hipLaunchKernelGGL(solve_kernel, dim3(n_grid), dim3(256), lds, q, so);

@@ -139,3 +139,22 @@ def test_full_depth_solve_does_not_wait_for_the_device():
             assert busy and dt < 0.1, (busy, dt)
         _assert_same(out, host, cap)
         s.close()
+
+
+@pytest.mark.parametrize("screen", ["fp32", "bf16"])
+@pytest.mark.parametrize("n,p", [(60, 127), (60, 128), (60, 700), (200, 1200)])
+def test_graphs_match_host_loop_while_the_running_count_falls(n, p, screen):
+    """Batches around and above twice the padded signal length, where the master problem takes a wave per signal, with
+    supports of very different sizes so that the running count falls below that in the middle of the solve: one graph,
+    captured segments and the host loop agree bit for bit."""
+    pk = _lib()
+    rng = np.random.default_rng(n + p)
+    At = bi.gaussian_dictionary(n, 8 * n, 19)
+    Bt = np.stack([At[rng.choice(8 * n, 1 + i % 12, replace=False)].sum(0) for i in range(p)]).astype(np.float32)
+    Bt[p // 2:] += 0.02 * rng.standard_normal((p - p // 2, n)).astype(np.float32)
+    At, Bt = to_dev(At), to_dev(Bt)
+    host = pk.Solver(At, 0.05, mode="rel", rho=3, screen=screen).solve(Bt)
+    it = host["iters"].cpu().numpy()
+    assert (it == it.max()).sum() < p // 4 and it.max() < 60
+    for cap in (0, 60):
+        _assert_same(pk.Solver(At, 0.05, mode="rel", rho=3, screen=screen, max_outer=cap, graph=True).solve(Bt), host, cap)
