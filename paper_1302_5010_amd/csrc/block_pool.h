@@ -50,6 +50,7 @@ public:
             (void)hipGetLastError();
             e = hipMalloc(out, bytes);
         }
+        if (e != hipSuccess) (void)hipGetLastError();   // reported by the status: no later launch check may find it
         *got = bytes;
         return e;
     }

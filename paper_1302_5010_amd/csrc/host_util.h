@@ -37,6 +37,7 @@ hipError_t dalloc(T** p, size_t count)
         (void)hipGetLastError();
         e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
     }
+    if (e != hipSuccess) (void)hipGetLastError();   // reported by the status: no later launch check may find it
     return e;
 }
 

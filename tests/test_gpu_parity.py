@@ -1276,3 +1276,47 @@ def test_correlate_takes_any_stream_object():
         torch.cuda.synchronize()
         assert torch.equal(G, ref)
     s.close()
+
+
+class _Hog:
+    """All of the device's free memory but `leave` bytes, taken while the object lives."""
+
+    def __init__(self, leave):
+        import paper_1302_5010_amd as pk
+        pk.trim()
+        torch.cuda.empty_cache()
+        self.held = []
+        while True:
+            n = min(torch.cuda.mem_get_info()[0] - leave, 64 << 30)
+            if n < 2 << 20:
+                break
+            self.held.append(torch.empty(n // (2 << 20) * (2 << 20), dtype=torch.uint8, device="cuda"))
+
+    def free(self):
+        self.held.clear()
+        torch.cuda.empty_cache()
+
+
+def test_out_of_memory_in_the_middle_of_a_solve():
+    """A solve whose slot blocks stop fitting while the host loop runs an iteration ahead: it fails, and
+    the same context solves the same signals once there is memory again."""
+    pk = _lib()
+    n, m, p = 600, 4800, 60
+    At = to_dev(bi.gaussian_dictionary(n, m, 35))
+    Bt = to_dev(np.random.default_rng(36).standard_normal((p, n)).astype(np.float32))
+    other = pk.Solver(At, 0.02, mode="rel", rho=30)
+    ref = other.solve(Bt)
+    other.close()
+    s = pk.Solver(At, 0.02, mode="rel", rho=30)
+    s.solve(Bt, lam=torch.full((p,), 1e3, dtype=torch.float64, device="cuda"))   # the workspace, and little else
+    torch.cuda.synchronize()
+    hog = _Hog(400 << 20)
+    try:
+        with pytest.raises(pk.BmplError, match="arena"):
+            s.solve(Bt)
+    finally:
+        hog.free()
+    out = s.solve(Bt)
+    for key in ("x_val", "x_idx", "supp_len", "iters", "objective", "status"):
+        assert torch.equal(out[key], ref[key]), key
+    s.close()
