@@ -1290,22 +1290,24 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         const unsigned long long seq0 = c->pass_seq;   // the first pass
         int it = 0, read = -1, covered = iters0;       // iterations enqueued, passes read, iterations with blocks
         int cover[2] = {iters0, 0};                    // iterations that the report of an unread pass covers
+        // after an error nothing of an iteration ahead still runs when the call returns
+        auto stopped = [&](bmpl_status r) { (void)hipStreamSynchronize(s); return r; };
         for (;;) {
             const bool ahead = ahead_of(n_act);
             if (it < covered && it - read < (ahead ? 2 : 1)) {
                 st = one_iteration(n_act);
-                if (st != BMPL_OK) return st;
+                if (st != BMPL_OK) return stopped(st);
                 cover[++it % 2] = ahead ? 2 : 1;
                 continue;
             }
             st = wait_report(seq0 + (unsigned long long)++read);
-            if (st != BMPL_OK) return st;
+            if (st != BMPL_OK) return stopped(st);
             const PassReport r = c->h_report[(seq0 + (unsigned long long)read) % PASS_REPORTS];
             n_act = r.n_act;
             if (n_act == 0) break;
             covered = read + cover[read % 2];
             st = arena_ensure(c, r.top, r.reserve, s);
-            if (st != BMPL_OK) return st;
+            if (st != BMPL_OK) return stopped(st);
         }
         if (it > read) unread = seq0 + (unsigned long long)it;
     }

@@ -1298,8 +1298,8 @@ class _Hog:
 
 
 def test_out_of_memory_in_the_middle_of_a_solve():
-    """A solve whose slot blocks stop fitting while the host loop runs an iteration ahead: it fails, and
-    the same context solves the same signals once there is memory again."""
+    """A solve whose slot blocks stop fitting while the host loop runs an iteration ahead: it fails with nothing left
+    on the stream, and the same context solves the same signals once there is memory again."""
     pk = _lib()
     n, m, p = 600, 4800, 60
     At = to_dev(bi.gaussian_dictionary(n, m, 35))
@@ -1314,6 +1314,7 @@ def test_out_of_memory_in_the_middle_of_a_solve():
     try:
         with pytest.raises(pk.BmplError, match="arena"):
             s.solve(Bt)
+        assert torch.cuda.current_stream().query()
     finally:
         hog.free()
     out = s.solve(Bt)
