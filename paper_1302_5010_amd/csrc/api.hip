@@ -920,11 +920,20 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
     // proposal's atoms or rho) and, in graph mode, the iterations of the first segment; in full depth,
     // the whole solve.
     const bool tm = timing_on(c);
-    auto ahead_of = [&](int n) { return !graph && !tm && n <= AHEAD_MAX; };
-    const int iters0 = (graph && !warm) ? 1 + GRAPH_DEPTH : (ahead_of(p) ? 2 : 1);
-    st = arena_ensure(c, 0, (unsigned long long)p *
-                               (full ? (unsigned long long)block_doubles(kfull, c->n)
-                                     : block_reserve(0, 0, first_add, iters0, rho, slack, max_active, c->n)), s);
+    bool ahead_fits = true;   // blocks for two iterations at a time have fitted so far
+    auto ahead_of = [&](int n) { return !graph && !tm && ahead_fits && n <= AHEAD_MAX; };
+    int iters0 = (graph && !warm) ? 1 + GRAPH_DEPTH : (ahead_of(p) ? 2 : 1);
+    auto first_blocks = [&] {
+        return arena_ensure(c, 0, (unsigned long long)p *
+                                      (full ? (unsigned long long)block_doubles(kfull, c->n)
+                                            : block_reserve(0, 0, first_add, iters0, rho, slack, max_active, c->n)), s);
+    };
+    st = first_blocks();
+    if (st == BMPL_E_NOMEM && ahead_of(p)) {   // one iteration at a time may still fit
+        ahead_fits = false;
+        iters0 = 1;
+        st = first_blocks();
+    }
     if (st != BMPL_OK) return st;
     Workspace& w = c->w;
     w.p = p;
@@ -1292,6 +1301,16 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         int cover[2] = {iters0, 0};                    // iterations that the report of an unread pass covers
         // after an error nothing of an iteration ahead still runs when the call returns
         auto stopped = [&](bmpl_status r) { (void)hipStreamSynchronize(s); return r; };
+        // The blocks that the running signals may take in the next iteration alone, from their state (the stream idle).
+        auto next_reserve = [&](unsigned long long* need) -> bmpl_status {
+            std::vector<int> act(n_act), nI(p), cap(p);
+            HIPC(hipMemcpy(act.data(), c->act[cur], sizeof(int) * n_act, hipMemcpyDeviceToHost));
+            HIPC(hipMemcpy(nI.data(), w.nI, sizeof(int) * p, hipMemcpyDeviceToHost));
+            HIPC(hipMemcpy(cap.data(), w.cap, sizeof(int) * p, hipMemcpyDeviceToHost));
+            *need = 0;
+            for (int sig : act) *need += block_reserve(cap[sig], nI[sig], rho, 1, rho, slack, max_active, c->n);
+            return BMPL_OK;
+        };
         for (;;) {
             const bool ahead = ahead_of(n_act);
             if (it < covered && it - read < (ahead ? 2 : 1)) {
@@ -1307,6 +1326,23 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
             if (n_act == 0) break;
             covered = read + cover[read % 2];
             st = arena_ensure(c, r.top, r.reserve, s);
+            if (st == BMPL_E_NOMEM && cover[read % 2] == 2) {
+                // Two iterations' blocks do not fit: catch up with what is enqueued and go on an iteration at a time,
+                // with the memory that takes.
+                ahead_fits = false;
+                while (read < it) {
+                    st = wait_report(seq0 + (unsigned long long)++read);
+                    if (st != BMPL_OK) return stopped(st);
+                }
+                HIPC(hipStreamSynchronize(s));
+                const PassReport last = c->h_report[(seq0 + (unsigned long long)read) % PASS_REPORTS];
+                n_act = last.n_act;
+                if (n_act == 0) break;
+                covered = read + 1;
+                unsigned long long need = 0;
+                st = next_reserve(&need);
+                if (st == BMPL_OK) st = arena_ensure(c, last.top, need, s);
+            }
             if (st != BMPL_OK) return stopped(st);
         }
         if (it > read) unread = seq0 + (unsigned long long)it;

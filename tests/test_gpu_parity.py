@@ -1321,3 +1321,29 @@ def test_out_of_memory_in_the_middle_of_a_solve():
     for key in ("x_val", "x_idx", "supp_len", "iters", "objective", "status"):
         assert torch.equal(out[key], ref[key]), key
     s.close()
+
+
+def test_memory_for_one_iteration_at_a_time_suffices():
+    """The host loop runs an iteration ahead only where the slot blocks of two fit.  256 proposed atoms take blocks of
+    384 slots; the cap ends the solve at 384, but blocks for one more iteration than it does would be 768 slots,
+    64 signals x 0.9 M float64 = 460 MB, and 250 MB are free."""
+    pk = _lib()
+    n, m, p = 600, 4800, 64
+    At = to_dev(bi.gaussian_dictionary(n, m, 37))
+    rng = np.random.default_rng(38)
+    Bt = to_dev(rng.standard_normal((p, n)).astype(np.float32))
+    warm = to_dev(np.stack([rng.choice(m, 256, replace=False) for _ in range(p)]).astype(np.int32))
+    opts = dict(mode="rel", rho=64, max_outer=3)
+    ref = pk.Solver(At, 0.01, **opts).solve(Bt, warm=warm)
+    assert bool((ref["status"] & pk.BMPL_SIG_CAP_ITERS).all())
+    s = pk.Solver(At, 0.01, **opts)
+    s.solve(Bt, lam=torch.full((p,), 1e3, dtype=torch.float64, device="cuda"), warm=warm)   # workspace, first blocks
+    torch.cuda.synchronize()
+    hog = _Hog(250 << 20)
+    try:
+        out = s.solve(Bt, warm=warm)
+    finally:
+        hog.free()
+    for key in ("x_val", "x_idx", "supp_len", "iters", "objective", "status"):
+        assert torch.equal(out[key], ref[key]), key
+    s.close()
