@@ -81,35 +81,41 @@ __device__ __forceinline__ void group_maxima(const float* gm, int groups, const 
     }
 }
 
-// Lists the groups whose largest |g| reaches `quick` (up to cap; *n counts them all) and, after a barrier, visits
-// the atoms of the listed ones: visit(atom, |g|, counted) is called by whole waves (counted: an atom outside I).
+// Lists the groups whose largest |g| reaches `quick`, in windows of CAPG groups (32 768 atoms: one window, and no list
+// that overflows near a stop, where every group with an atom of I passes), and, after a barrier, visits the atoms of
+// the listed ones: visit(atom, |g|, counted) is called by whole waves (counted: an atom outside I).  *n: 0 before.
 template <int CAPG, class VISIT>
 __device__ __forceinline__ void visit_groups(const float* gm, int groups, const float* g, const uint32_t* ex, int m,
                                              float quick, int* s_list, int* n, VISIT&& visit)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int g0 = tid; g0 < groups; g0 += 256)
-        if (gm[g0] >= quick) {
-            const int e = atomicAdd(n, 1);
-            if (e < CAPG) s_list[e] = g0;
-        }
-    __syncthreads();
-    const int nl = min(*n, CAPG);
-    constexpr int U = 4;                          // two groups per wave and step, U steps in flight
-    for (int e0 = 2 * U * wave; e0 < nl; e0 += 2 * U * 4) {
-        float v[U];
-        uint32_t w[U];
-        int at[U];
+    constexpr int U = 4;                              // two groups per wave and step, U steps in flight
+    static_assert(CAPG % 256 == 0 || CAPG == 1, "a thread owns the same groups here as in group_maxima");
+    for (int first = 0; first < groups; first += CAPG) {
+        for (int g0 = first + tid; g0 < min(groups, first + CAPG); g0 += 256)
+            if (gm[g0] >= quick) s_list[atomicAdd(n, 1)] = g0;
+        __syncthreads();
+        const int nl = *n;
+        for (int e0 = 2 * U * wave; e0 < nl; e0 += 2 * U * 4) {
+            float v[U];
+            uint32_t w[U];
+            int at[U];
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int e = e0 + 2 * q + (lane >> 5);
-            at[q] = e < nl ? group_atom(s_list[e], lane & 31) : m;
-            const int j = min(at[q], m - 1);
-            v[q] = g[j];
-            w[q] = ex[j >> 5];
-        }
+            for (int q = 0; q < U; ++q) {
+                const int e = e0 + 2 * q + (lane >> 5);
+                at[q] = e < nl ? group_atom(s_list[e], lane & 31) : m;
+                const int j = min(at[q], m - 1);
+                v[q] = g[j];
+                w[q] = ex[j >> 5];
+            }
 #pragma unroll
-        for (int q = 0; q < U; ++q) visit(at[q], fabsf(v[q]), at[q] < m && !((w[q] >> (at[q] & 31)) & 1u));
+            for (int q = 0; q < U; ++q) visit(at[q], fabsf(v[q]), at[q] < m && !((w[q] >> (at[q] & 31)) & 1u));
+        }
+        if (first + CAPG < groups) {                  // the list is taken again
+            __syncthreads();
+            if (tid == 0) *n = 0;
+            __syncthreads();
+        }
     }
 }
 

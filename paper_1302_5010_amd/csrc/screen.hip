@@ -394,10 +394,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KMAX > 32 ?
     if (grouped) {
         visit_groups<CAPG>(gm, corr_groups(a.m), g, ex, a.m, quick, s_gl, &s_cnt,
                            [&](int j, float v, bool out) { take(out && ok(v), j, v); });
-        if (s_cnt > CAPG) {                       // (the same in every thread)
-            screen_sweeps<KMAX>(a, row, sig, k, eps);
-            return;
-        }
         __syncthreads();                          // s_cnt is reused below
     } else {
 #pragma unroll

@@ -194,11 +194,6 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int row, int sig
                 if (out) vmx = fmaxf(vmx, v);
                 take(out && ok(v), j, v);
             });
-            if (s_ng > CAPG) {                    // too many (the same in every thread): the rounds of argmax below
-                for (int j = tid; j < a.m; j += 256)
-                    if (!((ex[j >> 5] >> (j & 31)) & 1u)) vmx = fmaxf(vmx, fabsf(g[j]));
-                if (tid == 0) s_n = CAP + 1;
-            }
         } else {
 #pragma unroll
         for (int q = 0; q < CH; ++q) four(f0[q], w0[q], 4 * tid + 1024 * q);

@@ -1347,3 +1347,25 @@ def test_memory_for_one_iteration_at_a_time_suffices():
     for key in ("x_val", "x_idx", "supp_len", "iters", "objective", "status"):
         assert torch.equal(out[key], ref[key]), key
     s.close()
+
+
+@pytest.mark.parametrize("screen", ["fp32", "bf16"])
+@pytest.mark.parametrize("m", [32768, 32832, 60000])
+def test_selection_with_most_groups_listed(m, screen):
+    """A dictionary with one atom repeated in most of the groups of 32 that the selection lists by their largest value:
+    one window of the list, a second one of two groups, and two, against whole rows (shapes that keep no groups)."""
+    pk = _lib()
+    n, p = 64, 70
+    At = bi.gaussian_dictionary(n, m, 53)
+    copies = [64 * (g // 2) + 16 * (g % 2) + g % 13 for g in range(m // 32) if g % 20]
+    At[copies] = At[0]
+    Bt = np.random.default_rng(m).standard_normal((p, n)).astype(np.float32)
+    Bt[: p // 2] += 30.0 * At[0]
+    res = []
+    for shapes in ([13, 3, 3], [5, 5, 4]):
+        s = pk.Solver(to_dev(At), 0.2, mode="rel", rho=5, screen=screen, gram_table=False)
+        s.set_tuning(shapes)
+        res.append(s.solve(to_dev(Bt)))
+        s.close()
+    for key in ("x_val", "x_idx", "supp_len", "iters", "lambda", "objective", "status"):
+        assert torch.equal(res[0][key], res[1][key]), key
