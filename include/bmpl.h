@@ -218,6 +218,14 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p,
  */
 bmpl_status bmpl_destroy(bmpl_ctx* c);
 
+/*
+ * Bound the device memory that the context takes for its signals' slot blocks (their Gram matrices and
+ * factors, which grow with the active sets) from now on; 0, the default, for no bound but the device's
+ * memory.  A solve that needs more returns BMPL_E_NOMEM, as it does when the device has no more.  What the
+ * context holds already stays.  Errors: BMPL_E_INVALID for NULL or a negative bound.
+ */
+bmpl_status bmpl_set_arena_limit(bmpl_ctx* c, int64_t bytes);
+
 /* Give the blocks kept from destroyed contexts, on every device, back to the driver. */
 bmpl_status bmpl_trim(void);
 

@@ -86,6 +86,7 @@ def _load():
     lib.bmpl_solve.argtypes = [vp, vp, i64, i32, vp, vp, i32, ctypes.POINTER(_Result), vp]
     lib.bmpl_destroy.argtypes = [vp]
     lib.bmpl_trim.argtypes = []
+    lib.bmpl_set_arena_limit.argtypes = [vp, i64]
     lib.bmpl_last_error.restype = ctypes.c_char_p
     lib.bmpl_last_error.argtypes = [ctypes.c_void_p]
     lib.bmpl_correlate.argtypes = [vp, vp, i64, i32, vp, i64, vp]
@@ -109,7 +110,7 @@ def _load():
     lib.bmpl_mlp_adam_step.argtypes = [vp, vp, ctypes.POINTER(AdamParams), vp]
     lib.bmpl_mlp_propose.argtypes = [vp, vp, i64, i32, i32, vp, i32, vp]
     lib.bmpl_topk.argtypes = [vp, i64, i32, i32, i32, vp, i32, vp]
-    for f in ("bmpl_options_default", "bmpl_create", "bmpl_solve", "bmpl_destroy", "bmpl_trim", "bmpl_correlate",
+    for f in ("bmpl_options_default", "bmpl_create", "bmpl_solve", "bmpl_destroy", "bmpl_trim", "bmpl_set_arena_limit", "bmpl_correlate",
               "bmpl_correlate_noalloc",
               "bmpl_select", "bmpl_get_timing", "bmpl_reset_timing", "bmpl_gram_table", "bmpl_autotune",
               "bmpl_set_tuning", "bmpl_mlp_create", "bmpl_mlp_destroy", "bmpl_mlp_set_params",
@@ -268,6 +269,10 @@ class Solver:
         """Correlation tile shape per running-signal bucket (>= 512, 64..511, < 64), each in 0..7."""
         arr = (ctypes.c_int32 * 3)(*[int(v) for v in shapes])
         _check(_lib.bmpl_set_tuning(self._h, arr), "bmpl_set_tuning")
+
+    def set_arena_limit(self, nbytes: int):
+        """Bound the device memory for the signals' slot blocks (0: none); a solve that needs more fails."""
+        _check(_lib.bmpl_set_arena_limit(self._h, int(nbytes)), "bmpl_set_arena_limit")
 
     def gram_table(self) -> torch.Tensor | None:
         """A copy of the float64 Gram table Q = A^T A held by the context, or None."""

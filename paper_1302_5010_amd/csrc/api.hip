@@ -153,6 +153,7 @@ struct bmpl_ctx {
     Arena* h_arena = nullptr;     // pinned: the host's own copy of the chunk list
     Arena* h_arena_rd = nullptr;  // pinned: top / starved / reserve read back with the running count
     unsigned long long arena_total = 0;   // doubles over all chunks
+    unsigned long long arena_limit = 0;   // the most of them (0: as many as the device has room for)
     float* Bw = nullptr;          // [p_cap][kpad]
     float* Gc = nullptr;          // [p_cap][ldg] correlations
     float* Gm = nullptr;          // [p_cap][corr_groups(m)] the largest |g| of each group of atoms (null: not kept)
@@ -332,6 +333,12 @@ bmpl_status arena_add(bmpl_ctx* c, unsigned long long min_doubles, unsigned long
         return fail(BMPL_E_NOMEM, "slot-block arena: all %d chunks in use", ARENA_CHUNKS);
     double* p = nullptr;
     unsigned long long sz = std::max(want_doubles, min_doubles);
+    if (c->arena_limit) {
+        const unsigned long long room = c->arena_limit - std::min(c->arena_limit, c->arena_total);
+        if (min_doubles > room)
+            return fail(BMPL_E_NOMEM, "slot-block arena: %.3g GB more would pass its limit", 8.0 * min_doubles / 1e9);
+        sz = std::min(sz, room);
+    }
     hipError_t e = dalloc(&p, (size_t)sz);
     if (e != hipSuccess && sz > min_doubles) {
         (void)hipGetLastError();
@@ -741,6 +748,13 @@ bmpl_status bmpl_destroy(bmpl_ctx* c)
     if (c->h_arena_rd) (void)hipHostFree(c->h_arena_rd);
     if (c->arena_dev) (void)hipFree(c->arena_dev);
     delete c;
+    return BMPL_OK;
+}
+
+bmpl_status bmpl_set_arena_limit(bmpl_ctx* c, int64_t bytes)
+{
+    if (!c || bytes < 0) return fail(BMPL_E_INVALID, "bmpl_set_arena_limit: NULL context or negative limit");
+    c->arena_limit = bytes ? std::max<unsigned long long>(1, (unsigned long long)bytes / sizeof(double)) : 0;
     return BMPL_OK;
 }
 

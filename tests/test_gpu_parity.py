@@ -1278,28 +1278,9 @@ def test_correlate_takes_any_stream_object():
     s.close()
 
 
-class _Hog:
-    """All of the device's free memory but `leave` bytes, taken while the object lives."""
-
-    def __init__(self, leave):
-        import paper_1302_5010_amd as pk
-        pk.trim()
-        torch.cuda.empty_cache()
-        self.held = []
-        while True:
-            n = min(torch.cuda.mem_get_info()[0] - leave, 64 << 30)
-            if n < 2 << 20:
-                break
-            self.held.append(torch.empty(n // (2 << 20) * (2 << 20), dtype=torch.uint8, device="cuda"))
-
-    def free(self):
-        self.held.clear()
-        torch.cuda.empty_cache()
-
-
 def test_out_of_memory_in_the_middle_of_a_solve():
-    """A solve whose slot blocks stop fitting while the host loop runs an iteration ahead: it fails with nothing left
-    on the stream, and the same context solves the same signals once there is memory again."""
+    """A solve whose slot blocks stop fitting (a limit below the 1.2 GB they take) while the host loop runs an iteration
+    ahead: it fails with nothing left on the stream, and the same context solves the same signals without the limit."""
     pk = _lib()
     n, m, p = 600, 4800, 60
     At = to_dev(bi.gaussian_dictionary(n, m, 35))
@@ -1308,15 +1289,11 @@ def test_out_of_memory_in_the_middle_of_a_solve():
     ref = other.solve(Bt)
     other.close()
     s = pk.Solver(At, 0.02, mode="rel", rho=30)
-    s.solve(Bt, lam=torch.full((p,), 1e3, dtype=torch.float64, device="cuda"))   # the workspace, and little else
-    torch.cuda.synchronize()
-    hog = _Hog(400 << 20)
-    try:
-        with pytest.raises(pk.BmplError, match="arena"):
-            s.solve(Bt)
-        assert torch.cuda.current_stream().query()
-    finally:
-        hog.free()
+    s.set_arena_limit(400 << 20)
+    with pytest.raises(pk.BmplError, match="arena"):
+        s.solve(Bt)
+    assert torch.cuda.current_stream().query()
+    s.set_arena_limit(0)
     out = s.solve(Bt)
     for key in ("x_val", "x_idx", "supp_len", "iters", "objective", "status"):
         assert torch.equal(out[key], ref[key]), key
@@ -1325,8 +1302,8 @@ def test_out_of_memory_in_the_middle_of_a_solve():
 
 def test_memory_for_one_iteration_at_a_time_suffices():
     """The host loop runs an iteration ahead only where the slot blocks of two fit.  256 proposed atoms take blocks of
-    384 slots; the cap ends the solve at 384, but blocks for one more iteration than it does would be 768 slots,
-    64 signals x 0.9 M float64 = 460 MB, and 250 MB are free."""
+    384 slots, 64 signals x 0.23 M float64 = 116 MB; the cap ends the solve at 384, but blocks for one more iteration
+    than it does would be 768 slots, 460 MB more.  The limit is 250 MB, and too small for the first blocks at 60."""
     pk = _lib()
     n, m, p = 600, 4800, 64
     At = to_dev(bi.gaussian_dictionary(n, m, 37))
@@ -1337,13 +1314,11 @@ def test_memory_for_one_iteration_at_a_time_suffices():
     ref = pk.Solver(At, 0.01, **opts).solve(Bt, warm=warm)
     assert bool((ref["status"] & pk.BMPL_SIG_CAP_ITERS).all())
     s = pk.Solver(At, 0.01, **opts)
-    s.solve(Bt, lam=torch.full((p,), 1e3, dtype=torch.float64, device="cuda"), warm=warm)   # workspace, first blocks
-    torch.cuda.synchronize()
-    hog = _Hog(250 << 20)
-    try:
-        out = s.solve(Bt, warm=warm)
-    finally:
-        hog.free()
+    s.set_arena_limit(60 << 20)
+    with pytest.raises(pk.BmplError, match="arena"):
+        s.solve(Bt, warm=warm)
+    s.set_arena_limit(250 << 20)
+    out = s.solve(Bt, warm=warm)
     for key in ("x_val", "x_idx", "supp_len", "iters", "objective", "status"):
         assert torch.equal(out[key], ref[key]), key
     s.close()

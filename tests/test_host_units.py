@@ -144,3 +144,34 @@ int main()
     return 0;
 }
 """, "-I", str(tmp_path))
+
+
+def test_failed_allocation_leaves_no_error_behind(tmp_path):
+    """dalloc and the pool against a device without memory, with a runtime that keeps the last error until it is asked
+    for it: the status says that there was none, and the next launch check of any call must not find it."""
+    hip = tmp_path / "hip"
+    hip.mkdir()
+    (hip / "hip_runtime.h").write_text("""
+#pragma once
+#include <cstddef>
+typedef int hipError_t;
+enum { hipSuccess = 0, hipErrorOutOfMemory = 2 };
+inline hipError_t& last() { static hipError_t e = hipSuccess; return e; }
+inline hipError_t hipMalloc(void**, size_t) { return last() = hipErrorOutOfMemory; }
+inline hipError_t hipFree(void*) { return hipSuccess; }
+inline hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+inline hipError_t hipGetLastError() { const hipError_t e = last(); last() = hipSuccess; return e; }
+inline const char* hipGetErrorString(hipError_t) { return ""; }
+""")
+    _run(tmp_path, r"""
+#include "host_util.h"
+int main()
+{
+    double* p = nullptr;
+    if (bmpl::dalloc(&p, 10) != hipErrorOutOfMemory || hipGetLastError() != hipSuccess) return 1;
+    void* q = nullptr;
+    size_t got = 0;
+    if (bmpl::block_pool().take(0, &q, 10, &got) != hipErrorOutOfMemory || hipGetLastError() != hipSuccess) return 2;
+    return 0;
+}
+""", "-I", str(tmp_path), "-Wno-unused")
