@@ -469,9 +469,12 @@ struct FoldLds {
     double gl[8][8];                              // Gram entries of the list
     double z[C];                                  // fold_rows_wave: the eighth right-hand side's z
     double zz[NT / 64][8];
-    double g[8][C];                               // fold_rows_wave: the right-hand sides, then the waves' sums;
-                                                  // fold_rows_split: the eighth right-hand side's z
+    union {
+        double g[8][C];                           // fold_rows_wave: the right-hand sides, then the waves' sums
+        double zs[8 * C];                         // fold_rows_split: the eighth right-hand side's z, up to FOLD_MAX
+    };
 };
+static_assert(FOLD_MAX <= 8 * FoldLds::C, "fold_rows_split's z");
 
 // The rows before s0, s0 > 256 NJ / 2 columns split over the waves (wave v, lane l: columns 64 (v + 4 j) + l): eight
 // rows at a time give each right-hand side's z_i by a sum over the wave and one over the waves (a barrier).
@@ -524,7 +527,7 @@ __device__ __forceinline__ void fold_rows_split(const RowBuffers& rows, int s0, 
             for (int v2 = 1; v2 < NW; ++v2) z += w.part[buf][v2][lane];
             buf ^= 1;
             zzl += z * z;                         // zero past s0
-            if (wave == 0 && (lane & 7) == 7) w.g[0][i + (lane >> 3)] = z;
+            if (wave == 0 && (lane & 7) == 7) w.zs[i + (lane >> 3)] = z;
 #pragma unroll
             for (int e = 0; e < NR; ++e) {
 #pragma unroll
@@ -782,7 +785,7 @@ __device__ __forceinline__ void chol_append_fold(Sig& v, int& nS, const int* lis
             const int k = 64 * (wave + NW * j) + lane;
             if (k < s0) vx[k] = acc[NR - 1][j];
         }
-        const double* wz = NJ == 2 ? w.z : w.g[0];
+        const double* wz = NJ == 2 ? w.z : w.zs;
         for (int k = tid; k < s0; k += NT) vzc[k] = wz[k];
     }
     nS = s;
