@@ -982,7 +982,12 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
     // The host does not wait for the running count before the first pass (in graph mode: until the first
     // captured segment has been launched): every kernel reads the count on the device, and p bounds it.
     int n_act = p;
-    if (tm) span(c, ev_first, mark(c, s), K_OTHER);
+    if (tm) {   // the counters take the signals that run: finite ones
+        span(c, ev_first, mark(c, s), K_OTHER);
+        HIPC(hipMemcpyAsync(c->h_arena_rd, c->arena_dev, offsetof(Arena, nchunks), hipMemcpyDeviceToHost, s));
+        HIPC(hipStreamSynchronize(s));
+        n_act = c->h_arena_rd->n_act[0];
+    }
 
     bool merge_mid = false;   // graph segments: see the gated product below
     // One pass of the worst-case analysis on the running list act[cur] (n_grid bounds its
@@ -1258,10 +1263,12 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
 
     // Iteration 0: lambda rule and the first selection (or the warm-start proposal).
     int cur = 0;
-    c->timing.outer_iters += tm ? 1 : 0;
-    st = enqueue_select_pass(s, 0, n_act, true, false, false);
-    if (st != BMPL_OK) return st;
-    cur = 1;
+    if (n_act > 0) {
+        c->timing.outer_iters += tm ? 1 : 0;
+        st = enqueue_select_pass(s, 0, n_act, true, false, false);
+        if (st != BMPL_OK) return st;
+        cur = 1;
+    }
     if (graph && warm && !full) {
         st = read_count(cur);
         if (st != BMPL_OK) return st;
@@ -1309,7 +1316,7 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
     // device and the last count read bounds it; each report reserves blocks for the two iterations after its
     // pass, and the launches after the last stop are empty.
     unsigned long long unread = 0;   // the number of a pass whose report is still to come
-    if (!graph) {
+    if (!graph && n_act > 0) {
         const unsigned long long seq0 = c->pass_seq;   // the first pass
         int it = 0, read = -1, covered = iters0;       // iterations enqueued, passes read, iterations with blocks
         int cover[2] = {iters0, 0};                    // iterations that the report of an unread pass covers

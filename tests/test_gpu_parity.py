@@ -1344,3 +1344,22 @@ def test_selection_with_most_groups_listed(m, screen):
         s.close()
     for key in ("x_val", "x_idx", "supp_len", "iters", "lambda", "objective", "status"):
         assert torch.equal(res[0][key], res[1][key]), key
+
+
+@pytest.mark.parametrize("bad", [0, 7, 40])
+def test_timing_counts_the_signals_that_run(bad):
+    """Signals that are not finite never run: the product's counters and the passes are those of the others alone."""
+    pk = _lib()
+    n, m, p = 100, 700, 40
+    At = to_dev(bi.gaussian_dictionary(n, m, 61))
+    Bt = torch.randn(p, n, generator=torch.Generator().manual_seed(62))
+    Bt[:bad, 5] = float("inf")
+    Bt = Bt.cuda()
+    s = pk.Solver(At, 0.2, mode="rel", rho=4, timing=True)
+    got = []
+    for B in (Bt, Bt[bad:].contiguous()):
+        s.reset_timing()
+        s.solve(B)
+        got.append({k: s.timing()[k] for k in ("corr_launches", "corr_flops", "corr_bytes", "outer_iters", "solve_launches")})
+    assert got[0] == (got[1] if bad < p else {k: 0 for k in got[0]})
+    s.close()
