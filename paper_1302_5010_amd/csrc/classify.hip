@@ -210,8 +210,12 @@ __global__ __launch_bounds__(256) void classify_kernel(ClassifyArgs a)
 hipError_t launch_classify(const ClassifyArgs& a, hipStream_t stream)
 {
     if (a.p <= 0) return hipSuccess;
-    // one wave per signal once that gives every CU eight waves; fewer signals get four each
-    if (a.p >= 2048) hipLaunchKernelGGL(classify_kernel<1>, dim3((a.p + 3) / 4), dim3(256), 0, stream, a);
+    // One wave per signal once that gives every CU eight waves; fewer signals get four each, which a long support (the
+    // class lists) and long rows also repay.  us with one wave and with four, support entries of random classes:
+    // n = 1024: 1536 signals 8 entries 31 and 29, 300 entries 1106 and 849; 2048: 32 and 32, 1161 and 965; 3072: 37 and
+    // 50, 1451 and 1658.  n = 2048: 2048 signals 55 and 43; 4096 80 and 80, 64 entries 498 and 480.  Rows of up to 128
+    // values leave half of four waves idle: n = 64, 8 entries: 1024 signals 22 and 23, 2048 24 and 29 (27 before waves).
+    if (a.p >= (a.n <= 128 ? 1536 : 2048)) hipLaunchKernelGGL(classify_kernel<1>, dim3((a.p + 3) / 4), dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(classify_kernel<4>, dim3(a.p), dim3(256), 0, stream, a);
     return hipGetLastError();
 }

@@ -1363,3 +1363,9 @@ def test_timing_counts_the_signals_that_run(bad):
         got.append({k: s.timing()[k] for k in ("corr_launches", "corr_flops", "corr_bytes", "outer_iters", "solve_launches")})
     assert got[0] == (got[1] if bad < p else {k: 0 for k in got[0]})
     s.close()
+
+
+@pytest.mark.parametrize("n,p", [(64, 1535), (64, 1536), (128, 2047), (129, 2047)])
+def test_classification_of_short_rows(n, p):
+    """Either side of the size from which signals of up to 128 values take one wave each."""
+    test_classification_kernel_forms(n, 300, p, 7, 12)
