@@ -15,6 +15,7 @@
 // with both operands K-contiguous; the backward products that contract over
 // the batch or the output width use bfloat16 transposes made for them.
 #include <float.h>
+#include <limits.h>
 
 #include <algorithm>
 #include <type_traits>
@@ -522,7 +523,9 @@ __global__ __launch_bounds__(256) void params_bf16_kernel(const float* __restric
 //      entries of the row), so every entry of the top k has a key >= T.
 //   2. The entries with a key >= T (typically a few hundred) are appended to an LDS list.
 //   3. A radix select over the list finds the k-th largest key; the entries above it and the lowest-indexed
-//      ones equal to it are the answer, each placed by counting the answer's entries below it.
+//      ones equal to it are the answer, each placed by counting the answer's entries below it.  The indices of equal
+//      entries take a radix select too, and a wave counts a digit's entries at once: with 1400 of 20000 scores equal,
+//      4096 rows, a count per equal entry and a list of 1024 took 602 us, the sorts before them 220, this 107.
 // If more entries pass than the list holds (many equal keys), the row is done by an exact radix select over the
 // keys in global memory instead.
 // With 16-byte rows the whole row stays in registers between steps 1 and 2 (NQ float4 per thread, all loads in flight
@@ -551,7 +554,8 @@ __device__ inline int block_excl_count(bool flag, int* s_wave, int& total)
     return before + within;
 }
 
-constexpr int TOPK_CAP = 1024;   // list entries per row
+constexpr int TOPK_CAP = 2048;   // list entries per row
+static_assert(TOPK_MAX_LDS / 4 <= 65536, "kth_lowest_index takes indices of 16 bits");
 
 struct TopkLds {
     uint32_t key[TOPK_CAP];
@@ -562,6 +566,51 @@ struct TopkLds {
     int wave[4];
     int n, digit, need, ties;
 };
+
+// One entry per lane (`left`: this lane has one) into the digit counts.  Where many entries share a digit (sign and
+// exponent, or equal values) lanes would queue at one address, so a wave adds all entries of a digit at once: for the
+// digit of its first lane, or with ALL for every digit.
+template <bool ALL>
+__device__ __forceinline__ void count_digits(int* hist, bool left, uint32_t d)
+{
+    unsigned long long rest = __ballot(left);
+    while (rest) {
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, __ffsll((long long)rest) - 1);
+        const unsigned long long same = __ballot(left && d == d0);
+        if ((threadIdx.x & 63) == 0) atomicAdd(&hist[d0], __popcll(same));
+        left = left && d != d0;
+        rest &= ~same;
+        if (!ALL) break;
+    }
+    if (!ALL && left) atomicAdd(&hist[d], 1);
+}
+
+// The digit that holds the need-th entry in order of falling digits (s.digit), its rank there (s.need) and how many
+// entries it has (s.ties).  Between barriers, called by the whole workgroup.
+__device__ __forceinline__ void pick_digit(TopkLds& s, int need)
+{
+    const int tid = threadIdx.x;
+    if (tid >= 64) return;
+    // lane l owns digits 255 - 4 l .. 252 - 4 l, so the lanes before it hold the larger ones
+    const int4 hv = *reinterpret_cast<const int4*>(&s.hist[252 - 4 * tid]);
+    const int c[4] = {hv.w, hv.z, hv.y, hv.x};
+    const int own = c[0] + c[1] + c[2] + c[3];
+    int incl = own;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o);
+        incl += tid >= o ? v : 0;
+    }
+    int above = incl - own;
+    if (above < need && need <= incl) {      // exactly one lane
+        int q = 0, cq = c[0];
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (q == e && above + c[e] < need) { above += c[e]; q = e + 1; cq = c[e + 1]; }
+        s.digit = 255 - 4 * tid - q;
+        s.need = need - above;
+        s.ties = cq;
+    }
+}
 
 // The k-th largest of key[0 .. n) (1 <= k <= n) by 8-bit digits from the top; `need` receives how many entries equal to
 // it belong to the k largest, `ties` how many there are.  Called by the whole workgroup (256 threads).
@@ -576,49 +625,41 @@ __device__ inline uint32_t radix_kth(const uint32_t* key, int n, int k, TopkLds&
         for (int e0 = 0; e0 < n; e0 += 256) {
             const int e = e0 + tid;
             const uint32_t u = e < n ? key[e] : 0u;
-            bool left = e < n && (u & mask) == prefix;
+            const bool left = e < n && (u & mask) == prefix;
             const uint32_t d = (u >> shift) & 255u;
-            if (shift == 24) {
-                // sign and exponent: a few distinct values, so one addition per value and wave
-                unsigned long long rest = __ballot(left);
-                while (rest) {
-                    const uint32_t d0 = __shfl(d, __ffsll((long long)rest) - 1);
-                    const unsigned long long same = __ballot(left && d == d0);
-                    if ((tid & 63) == 0) atomicAdd(&s.hist[d0], __popcll(same));
-                    left = left && d != d0;
-                    rest &= ~same;
-                }
-            } else if (left) {
-                atomicAdd(&s.hist[d], 1);
-            }
+            if (shift == 24) count_digits<true>(s.hist, left, d);
+            else count_digits<false>(s.hist, left, d);
         }
         __syncthreads();
-        if (tid < 64) {
-            // lane l owns digits 255 - 4 l .. 252 - 4 l, so the lanes before it hold the larger ones
-            const int4 hv = *reinterpret_cast<const int4*>(&s.hist[252 - 4 * tid]);
-            const int c[4] = {hv.w, hv.z, hv.y, hv.x};
-            const int own = c[0] + c[1] + c[2] + c[3];
-            int incl = own;
-            for (int o = 1; o < 64; o <<= 1) {
-                const int v = __shfl_up(incl, o);
-                incl += tid >= o ? v : 0;
-            }
-            int above = incl - own;
-            if (above < need && need <= incl) {      // exactly one lane
-                int q = 0, cq = c[0];
-#pragma unroll
-                for (int e = 0; e < 3; ++e)
-                    if (q == e && above + c[e] < need) { above += c[e]; q = e + 1; cq = c[e + 1]; }
-                s.digit = 255 - 4 * tid - q;
-                s.need = need - above;
-                s.ties = cq;
-            }
-        }
+        pick_digit(s, need);
         __syncthreads();
         prefix |= (uint32_t)s.digit << shift;
         mask |= 0xFFu << shift;
         need = s.need;
         ties = s.ties;
+    }
+    return prefix;
+}
+
+// The k-th lowest index among the list's entries with key P (at least k of them), by its two bytes.
+__device__ inline int kth_lowest_index(int n, uint32_t P, int k, TopkLds& s)
+{
+    const int tid = threadIdx.x;
+    int prefix = 0, need = k;
+    for (int shift = 8; shift >= 0; shift -= 8) {
+        s.hist[tid] = 0;
+        __syncthreads();
+        for (int e0 = 0; e0 < n; e0 += 256) {
+            const int e = e0 + tid;
+            const int j = e < n ? s.idx[e] : 0;
+            const bool left = e < n && s.key[e] == P && (shift == 8 || (j >> 8) == prefix);
+            count_digits<false>(s.hist, left, 255u - ((uint32_t)(j >> shift) & 255u));   // lowest first
+        }
+        __syncthreads();
+        pick_digit(s, need);
+        __syncthreads();
+        prefix = (prefix << 8) | (255 - s.digit);
+        need = s.need;
     }
     return prefix;
 }
@@ -797,19 +838,14 @@ __global__ __launch_bounds__(256, NQ > 20 ? 2 : 4) void topk_kernel(const float*
     // 3. the kk-th largest key P of the list (n >= kk: T is a lower bound); entries above P are in, and the `need`
     //    lowest-indexed of the entries equal to it
     const uint32_t P = radix_kth(w.key, n, kk, w, need, ties);
+    const int cut = ties > need ? kth_lowest_index(n, P, need, w) : INT_MAX;   // the same test in every thread
     if (tid == 0) w.n = 0;
     __syncthreads();
     for (int e0 = 0; e0 < n; e0 += 256) {          // the same number of steps in every lane
         const int e = e0 + tid;
         const uint32_t u = e < n ? w.key[e] : 0u;
         const int j = e < n ? w.idx[e] : 0;
-        bool in = e < n && u > P;
-        if (e < n && u == P) {
-            int before = 0;
-            if (ties > need)
-                for (int d = 0; d < n; ++d) before += w.key[d] == P && w.idx[d] < j;
-            in = before < need;
-        }
+        const bool in = e < n && (u > P || (u == P && j <= cut));
         const unsigned long long bal = __ballot(in);
         int base = 0;
         if (lane == 0 && bal) base = atomicAdd(&w.n, __popcll(bal));

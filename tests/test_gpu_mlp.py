@@ -378,3 +378,20 @@ def test_forward_into_rows_far_apart(p, lds):
     net.close()
     del S, rows
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("equal", [1, 255, 300, 2047, 2048, 2049])
+@pytest.mark.parametrize("lds", [8192, 8193])
+def test_topk_of_equal_values(equal, lds):
+    """Rows whose k-th largest value occurs `equal` times, up to what the list holds and past it, spread over the row
+    or at its end, with a few larger ones: the lowest-indexed of the equal ones, compared exactly."""
+    pk = _lib()
+    rng = np.random.default_rng(equal)
+    S = -1.0 - rng.random((4, lds)).astype(np.float32)
+    for r in range(4):
+        at = rng.choice(8192, equal, replace=False) if r < 3 else np.arange(8192 - equal, 8192)
+        S[r, at] = [0.25, -0.0, 1e-41, 3.0][r]
+        S[r, rng.choice(8192, 5 * r, replace=False)] = 4.0 + r
+    for k in (1, 40, 256):
+        got = pk.topk(to_dev(S), k, L=8192).cpu().numpy()
+        np.testing.assert_array_equal(got, mo.propose(S[:, :8192].astype(np.float64), k))
