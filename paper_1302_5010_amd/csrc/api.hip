@@ -1465,15 +1465,16 @@ bmpl_status bmpl_autotune(bmpl_ctx* c, int32_t p, int32_t* shapes, double* ms, v
         HIPC(hipMemcpyAsync(w.rscale8, ones.data(), sizeof(float) * p, hipMemcpyHostToDevice, s));
         HIPC(hipStreamSynchronize(s));
     }
+    // with the epilogue that the solve runs it with (the groups' largest values, when they are kept)
     auto gemm = [&](int v, int nb) -> hipError_t {
         if (c->A8)   // the product of every outer iteration after the first
             return launch_corr_gemm_fp8(v, c->A8, c->kpad, c->m, c->kpad, w.R8, c->kpad, nullptr, nullptr, nb,
                                         c->Gc, c->ldg, c->p_cap, 0, 1 << 30, c->ascale8, w.rscale8, s);
         if (c->A16)
             return launch_corr_gemm_bf16(v, c->A16, c->A16p, c->kpad, c->m, c->kpad, w.R16, c->kpad, nullptr, nullptr, nb,
-                                         c->Gc, c->ldg, c->p_cap, 0, 1 << 30, s);
+                                         c->Gc, c->ldg, c->p_cap, 0, 1 << 30, s, c->Gm, corr_groups(c->m));
         return launch_corr_gemm_f32(v, c->At, c->kpad, c->m, c->kpad, w.R, c->kpad, nullptr, nullptr, nb, c->Gc,
-                                    c->ldg, c->p_cap, 0, 1 << 30, s);
+                                    c->ldg, c->p_cap, 0, 1 << 30, s, c->Gm, corr_groups(c->m));
     };
     hipEvent_t e0, e1;
     HIPC(hipEventCreate(&e0));
