@@ -525,7 +525,7 @@ __global__ __launch_bounds__(256) void params_bf16_kernel(const float* __restric
 //   3. A radix select over the list finds the k-th largest key; the entries above it and the lowest-indexed
 //      ones equal to it are the answer, each placed by counting the answer's entries below it.  The indices of equal
 //      entries take a radix select too, and a wave counts a digit's entries at once: with 1400 of 20000 scores equal,
-//      4096 rows, a count per equal entry and a list of 1024 took 602 us, the sorts before them 220, this 107.
+//      4096 rows, a count per equal entry and a list of 1024 took 602 us, the sorts before them 220, this 110.
 // If more entries pass than the list holds (many equal keys), the row is done by an exact radix select over the
 // keys in global memory instead.
 // With 16-byte rows the whole row stays in registers between steps 1 and 2 (NQ float4 per thread, all loads in flight
@@ -555,14 +555,14 @@ __device__ inline int block_excl_count(bool flag, int* s_wave, int& total)
 }
 
 constexpr int TOPK_CAP = 2048;   // list entries per row
-static_assert(TOPK_MAX_LDS / 4 <= 65536, "kth_lowest_index takes indices of 16 bits");
+static_assert(TOPK_MAX_LDS / 4 <= 65536, "the list's indices have 16 bits");
 
+// (Kept small: short rows run as many workgroups per CU as it lets them, 4096 rows of 1000: 26 us with 12 KB, 27 with this, 33
+// with 20.)
 struct TopkLds {
-    uint32_t key[TOPK_CAP];
-    int idx[TOPK_CAP];
-    uint32_t t[512];
-    int hist[256];
-    int sel[256];
+    uint32_t key[TOPK_CAP];      // the threads' two largest first (512), then the list
+    uint16_t idx[TOPK_CAP];
+    int hist[256];               // digit counts, then the answer before it is put in order
     int wave[4];
     int n, digit, need, ties;
 };
@@ -628,7 +628,8 @@ __device__ inline uint32_t radix_kth(const uint32_t* key, int n, int k, TopkLds&
             const bool left = e < n && (u & mask) == prefix;
             const uint32_t d = (u >> shift) & 255u;
             if (shift == 24) count_digits<true>(s.hist, left, d);
-            else count_digits<false>(s.hist, left, d);
+            else if (shift < 16 && ties > 64) count_digits<false>(s.hist, left, d);   // equal in 16 bits: equal values
+            else if (left) atomicAdd(&s.hist[d], 1);
         }
         __syncthreads();
         pick_digit(s, need);
@@ -767,12 +768,12 @@ __global__ __launch_bounds__(256, NQ > 20 ? 2 : 4) void topk_kernel(const float*
             for (int e = 0; e < 8; ++e) top2(j0 + 256 * e < L ? v[e] : NAN);
         }
     }
-    w.t[tid] = order_key(t1);
-    w.t[256 + tid] = order_key(t2);
+    w.key[tid] = order_key(t1);
+    w.key[256 + tid] = order_key(t2);
     if (tid == 0) w.n = 0;
     __syncthreads();
     int need, ties;
-    const uint32_t Tk = radix_kth(w.t, 512, kk, w, need, ties);
+    const uint32_t Tk = radix_kth(w.key, 512, kk, w, need, ties);
     // the value of a key (of +0 for the zeros, which compare equal)
     const float T = __uint_as_float((Tk & 0x80000000u) ? Tk & 0x7fffffffu : ~Tk);
 
@@ -807,7 +808,7 @@ __global__ __launch_bounds__(256, NQ > 20 ? 2 : 4) void topk_kernel(const float*
             for (uint32_t m = bits[v]; m; m &= m - 1u) {
                 const int b = __ffs(m) - 1;
                 const int j = 4 * (tid + 256 * (8 * v + (b >> 2))) + (b & 3);
-                if (pos < TOPK_CAP) { w.key[pos] = order_key(s[j]); w.idx[pos] = j; }
+                if (pos < TOPK_CAP) { w.key[pos] = order_key(s[j]); w.idx[pos] = (uint16_t)j; }
                 ++pos;
             }
     } else {
@@ -825,7 +826,7 @@ __global__ __launch_bounds__(256, NQ > 20 ? 2 : 4) void topk_kernel(const float*
                 if (lane == 0) base = atomicAdd(&w.n, __popcll(bal));
                 base = __builtin_amdgcn_readfirstlane(base);
                 const int pos = base + __popcll(bal & ((1ull << lane) - 1ull));
-                if (t && pos < TOPK_CAP) { w.key[pos] = order_key(v[e]); w.idx[pos] = j; }
+                if (t && pos < TOPK_CAP) { w.key[pos] = order_key(v[e]); w.idx[pos] = (uint16_t)j; }
             }
         }
     }
@@ -839,6 +840,7 @@ __global__ __launch_bounds__(256, NQ > 20 ? 2 : 4) void topk_kernel(const float*
     //    lowest-indexed of the entries equal to it
     const uint32_t P = radix_kth(w.key, n, kk, w, need, ties);
     const int cut = ties > need ? kth_lowest_index(n, P, need, w) : INT_MAX;   // the same test in every thread
+    int* sel = w.hist;
     if (tid == 0) w.n = 0;
     __syncthreads();
     for (int e0 = 0; e0 < n; e0 += 256) {          // the same number of steps in every lane
@@ -850,13 +852,13 @@ __global__ __launch_bounds__(256, NQ > 20 ? 2 : 4) void topk_kernel(const float*
         int base = 0;
         if (lane == 0 && bal) base = atomicAdd(&w.n, __popcll(bal));
         base = __builtin_amdgcn_readfirstlane(base);
-        if (in) w.sel[base + __popcll(bal & ((1ull << lane) - 1ull))] = j;
+        if (in) sel[base + __popcll(bal & ((1ull << lane) - 1ull))] = j;
     }
     __syncthreads();
     if (tid < kk) {
-        const int j = w.sel[tid];
+        const int j = sel[tid];
         int rank = 0;
-        for (int d = 0; d < kk; ++d) rank += w.sel[d] < j;
+        for (int d = 0; d < kk; ++d) rank += sel[d] < j;
         o[rank] = j;
     } else if (tid < k) {
         o[tid] = -1;
