@@ -27,10 +27,11 @@
  *    Concerns").  B is column-major n x p with leading dimension ldb >= n.
  *  - Calls that take a `hip_stream` enqueue their work on that stream
  *    (NULL = the null stream) and may return before it finishes; outputs are
- *    valid once the stream is synchronised.  bmpl_solve reads back how many
- *    signals are still running (a stream synchronisation) once per outer
- *    iteration, or once per captured segment of four iterations with
- *    BMPL_FLAG_GRAPH; with BMPL_FLAG_GRAPH and an iteration cap
+ *    valid once the stream is synchronised.  bmpl_solve waits for the number
+ *    of signals still running once per outer iteration (a report that the
+ *    device writes to pinned memory; with at most 64 running signals the next
+ *    iteration is enqueued already), or once per captured segment of four
+ *    iterations with BMPL_FLAG_GRAPH (a stream synchronisation); with BMPL_FLAG_GRAPH and an iteration cap
  *    (bmpl_options.max_outer) of at most 64 it captures the whole solve as one
  *    graph, sizes every signal's slot memory for that cap up front, and does
  *    not synchronise at all (when that memory fits; see BMPL_FLAG_GRAPH).
@@ -201,6 +202,8 @@ bmpl_status bmpl_create(const float* A_dev, int64_t lda, int32_t n, int32_t m,
  * warm_k atom indices, -1 = unused entry) seeds each active set: the master
  * problem is solved on the proposal first and the pursuit continues from there,
  * so the result is the same LASSO solution; NULL / warm_k = 0 for none.
+ * Host loop, captured segments and one graph give the same bits; a signal solved in a batch of another
+ * size can differ in the last bits of its float64 sums, since the size picks the master problem's kernel.
  * Workspace grows on demand and is kept in the context.  Per-signal outcomes
  * never fail the call; they are reported in sig_status.  Errors:
  * BMPL_E_INVALID (bad pointers, ldb < n, p < 0, ld_x too small),
@@ -431,7 +434,7 @@ int64_t bmpl_mlp_param_count(int32_t d_in, int32_t d_hidden, int32_t m);
  * max_batch bounds the rows of one bmpl_mlp_loss_grad call and the chunk of
  * signals that bmpl_mlp_forward / bmpl_mlp_propose process at once (they
  * accept any p).  Requires d_in and d_hidden to be positive multiples of 64,
- * m <= 38912 (one row of scores fits the selection kernel's LDS), n, m,
+ * m <= 38912 (one row of scores fits the selection kernel's registers), n, m,
  * max_batch >= 1.  Errors: BMPL_E_INVALID, BMPL_E_NOMEM, BMPL_E_HIP.
  */
 bmpl_status bmpl_mlp_create(const float* A_dev, int64_t lda, int32_t n, int32_t m, const float* P_dev,

@@ -467,8 +467,9 @@ bmpl_status ensure_workspace(bmpl_ctx* c, int p, int selcap)
     return BMPL_OK;
 }
 
-// Running signals up to which the host loop enqueues an iteration ahead of the count (the bucket of the product
-// for few signals, so an older count never picks another tile shape).  A few signals' iteration takes 45-75 us
+// Running signals up to which the host loop enqueues an iteration ahead of the count.  The older count bounds that
+// iteration's grids, and may pick another tile shape of the product: every shape takes any count up to its grid and
+// gives the same bits, and the selection follows the shape that was launched.  A few signals' iteration takes 45-75 us
 // on the GPU; waiting for its count and launching the next took 30 us more (16 signals of 128 x 512 with the
 // copy and the stream wait: 396 us per solve, 324 without; one signal of 1000 x 5001: 420 and 369).  With
 // hundreds of signals the older count's larger grids take back what the wait costs.

@@ -10,7 +10,7 @@
 
 namespace bmpl {
 
-constexpr size_t TOPK_MAX_LDS = 152 * 1024;   // row keys of the top-k kernel (rows up to 38912 atoms)
+constexpr int TOPK_MAX = 38912;   // entries per row of the top-k kernel (38 float4 per thread)
 
 hipError_t mlp_project(const float* At, int64_t lda, int n, int m, const float* P, int d, uint16_t* APt, int npad,
                        hipStream_t s);

@@ -555,10 +555,10 @@ __device__ inline int block_excl_count(bool flag, int* s_wave, int& total)
 }
 
 constexpr int TOPK_CAP = 2048;   // list entries per row
-static_assert(TOPK_MAX_LDS / 4 <= 65536, "the list's indices have 16 bits");
+static_assert(TOPK_MAX <= 65536, "the list's indices have 16 bits");
 
-// (Kept small: short rows run as many workgroups per CU as it lets them, 4096 rows of 1000: 26 us with 12 KB, 27 with this, 33
-// with 20.)
+// (Kept small: it decides how many workgroups of short rows share a CU.  4096 rows of 1000: 26 us with 12 KB, 27 with
+// these 13, 33 with 20.)
 struct TopkLds {
     uint32_t key[TOPK_CAP];      // the threads' two largest first (512), then the list
     uint16_t idx[TOPK_CAP];
@@ -738,7 +738,8 @@ __global__ __launch_bounds__(256, NQ > 20 ? 2 : 4) void topk_kernel(const float*
     constexpr int NR = NQ > 0 ? NQ : 1;
     float4 f[NR];
     if constexpr (NQ > 0) {
-        // chunks past the row read its last one (the row is padded to 16 bytes: lds % 4 == 0)
+        // chunks past the row read its last one, the 16 aligned bytes that hold the row's last entry (of the last row
+        // they can lie past the caller's matrix, never past its page: the values are not used)
         const int last = (L - 1) / 4;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
@@ -987,7 +988,7 @@ hipError_t mlp_topk(const float* S, int64_t lds, int rows, int L, int k, int* ou
 {
     if (rows <= 0) return hipSuccess;
     if (k < 1 || k > 256 || L < 1 || ldo < k) return hipErrorInvalidValue;
-    if ((size_t)L * 4 > TOPK_MAX_LDS) return hipErrorInvalidValue;
+    if (L > TOPK_MAX) return hipErrorInvalidValue;
     // rows on 16-byte boundaries stay in registers: 4, 8, 20 or 38 float4 per thread by the row's length
     auto launch = [&](auto nq) {
         hipLaunchKernelGGL(topk_kernel<decltype(nq)::value>, dim3(rows), dim3(256), 0, s, S, lds, L, k, out, ldo);

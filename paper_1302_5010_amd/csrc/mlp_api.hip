@@ -157,9 +157,9 @@ bmpl_status bmpl_mlp_create(const float* A_dev, int64_t lda, int32_t n, int32_t 
     if (d_in < 64 || d_in % 64 || d_hidden < 64 || d_hidden % 64)
         return fail(BMPL_E_INVALID, "bmpl_mlp_create: d_in=%d and d_hidden=%d must be positive multiples of 64", d_in,
                     d_hidden);
-    if ((size_t)m * 4 > TOPK_MAX_LDS)
-        return fail(BMPL_E_INVALID, "bmpl_mlp_create: m=%d exceeds the selection kernel's limit of %zu atoms", m,
-                    TOPK_MAX_LDS / 4);
+    if (m > TOPK_MAX)
+        return fail(BMPL_E_INVALID, "bmpl_mlp_create: m=%d exceeds the selection kernel's limit of %d atoms", m,
+                    TOPK_MAX);
     hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
     bmpl_mlp* q = new bmpl_mlp;
     auto bail = [&](bmpl_status st) { free_all(q); delete q; return st; };
@@ -352,7 +352,7 @@ bmpl_status bmpl_topk(const float* S_dev, int64_t lds, int32_t rows, int32_t L, 
     if (rows < 0 || L < 1 || lds < L || k < 1 || k > 256 || ld_idx < k)
         return fail(BMPL_E_INVALID, "bmpl_topk: bad rows=%d L=%d lds=%lld k=%d ld_idx=%d", rows, L, (long long)lds, k,
                     ld_idx);
-    if ((size_t)L * 4 > TOPK_MAX_LDS) return fail(BMPL_E_INVALID, "bmpl_topk: L=%d above %zu", L, TOPK_MAX_LDS / 4);
+    if (L > TOPK_MAX) return fail(BMPL_E_INVALID, "bmpl_topk: L=%d above %d", L, TOPK_MAX);
     if (rows > 0 && (!S_dev || !idx_dev)) return fail(BMPL_E_INVALID, "bmpl_topk: NULL pointer");
     HIPC(mlp_topk(S_dev, lds, rows, L, k, idx_dev, ld_idx, reinterpret_cast<hipStream_t>(hip_stream)));
     return BMPL_OK;
