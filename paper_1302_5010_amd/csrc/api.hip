@@ -360,13 +360,16 @@ bmpl_status arena_add(bmpl_ctx* c, unsigned long long min_doubles, unsigned long
     return BMPL_OK;
 }
 
-// Make sure `need` doubles of slot blocks (with a margin for chunk tails) can be handed out after the
+// The room that `need` doubles of slot blocks take, with a margin for chunk tails.
+unsigned long long arena_want(unsigned long long need) { return need + need / 8 + (1ull << 20); }
+
+// Make sure `need` doubles of slot blocks can be handed out after the
 // first `used` doubles of this solve.  `used` may lie past the chunks' end: the stop test places the
 // grow list's blocks before the host adds room, and a block placed past the end lies in the next chunk
 // once it is added (grow_kernel finds it there), so the offset is never moved back.
 bmpl_status arena_ensure(bmpl_ctx* c, unsigned long long used, unsigned long long need, hipStream_t s)
 {
-    const unsigned long long want = need + need / 8 + (1ull << 20);
+    const unsigned long long want = arena_want(need);
     if (c->arena_total >= used + want) return BMPL_OK;
     const unsigned long long missing = used + want - c->arena_total;
     return arena_add(c, missing, std::max(missing, c->arena_total / 4), s);
@@ -918,7 +921,7 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
     // the solve as one graph and gives each signal, at its first master problem, a slot block for the
     // largest |I| the cap allows (first_add + (max_outer - 1) rho), so nothing waits for the host: the
     // solve is enqueued and bmpl_solve returns without synchronising.  Used when those blocks take at
-    // most the arena already held plus half of the free device memory; otherwise the segments below.
+    // most the arena already held plus half of the free device memory, and its limit; otherwise the segments below.
     int kfull = 0;
     if (graph && c->opt.max_outer > 0 && c->opt.max_outer <= FULL_DEPTH_MAX) {
         const int bound = std::min(max_active, first_add + (max_outer - 1) * rho);
@@ -930,7 +933,9 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
             free_b = 0;
         }
         free_b += block_pool().kept(c->device);
-        if (8.0 * (double)need <= 8.0 * (double)c->arena_total + 0.5 * (double)free_b) kfull = k;
+        if (8.0 * (double)need <= 8.0 * (double)c->arena_total + 0.5 * (double)free_b &&
+            (!c->arena_limit || arena_want(need) <= c->arena_limit))
+            kfull = k;
     }
     const bool full = kfull > 0;
     // Slot blocks for every signal up to the first host read-back: the first master problem (a
@@ -1325,14 +1330,17 @@ bmpl_status bmpl_solve(bmpl_ctx* c, const float* B_dev, int64_t ldb, int32_t p, 
         int cover[2] = {iters0, 0};                    // iterations that the report of an unread pass covers
         // after an error nothing of an iteration ahead still runs when the call returns
         auto stopped = [&](bmpl_status r) { (void)hipStreamSynchronize(s); return r; };
-        // The blocks that the running signals may take in the next iteration alone, from their state (the stream idle).
+        // The blocks that the running signals (AHEAD_MAX at most) may take in the next iteration alone, from their state
+        // (the stream is idle).
         auto next_reserve = [&](unsigned long long* need) -> bmpl_status {
-            std::vector<int> act(n_act), nI(p), cap(p);
-            HIPC(hipMemcpy(act.data(), c->act[cur], sizeof(int) * n_act, hipMemcpyDeviceToHost));
-            HIPC(hipMemcpy(nI.data(), w.nI, sizeof(int) * p, hipMemcpyDeviceToHost));
-            HIPC(hipMemcpy(cap.data(), w.cap, sizeof(int) * p, hipMemcpyDeviceToHost));
+            int act[AHEAD_MAX], nI = 0, cap = 0;
+            HIPC(hipMemcpy(act, c->act[cur], sizeof(int) * n_act, hipMemcpyDeviceToHost));
             *need = 0;
-            for (int sig : act) *need += block_reserve(cap[sig], nI[sig], rho, 1, rho, slack, max_active, c->n);
+            for (int r = 0; r < n_act; ++r) {
+                HIPC(hipMemcpy(&nI, w.nI + act[r], sizeof(int), hipMemcpyDeviceToHost));
+                HIPC(hipMemcpy(&cap, w.cap + act[r], sizeof(int), hipMemcpyDeviceToHost));
+                *need += block_reserve(cap, nI, rho, 1, rho, slack, max_active, c->n);
+            }
             return BMPL_OK;
         };
         for (;;) {

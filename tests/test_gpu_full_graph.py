@@ -158,3 +158,17 @@ def test_graphs_match_host_loop_while_the_running_count_falls(n, p, screen):
     assert (it == it.max()).sum() < p // 4 and it.max() < 60
     for cap in (0, 60):
         _assert_same(pk.Solver(At, 0.05, mode="rel", rho=3, screen=screen, max_outer=cap, graph=True).solve(Bt), host, cap)
+
+
+def test_memory_limit_takes_segments_instead_of_one_graph():
+    """A bound on the slot blocks below what one graph per solve sets aside (300 signals x 0.24 M float64, 570 MB) and
+    above what the solve takes: captured segments, with the host loop's results."""
+    pk = _lib()
+    P = _problem()
+    lam = to_dev(lam_rel(P.At, P.Bt, P.lambda_rel))
+    At, Bt = to_dev(P.At), to_dev(P.Bt)
+    host = pk.Solver(At, 0.0, rho=P.rho, max_outer=60).solve(Bt, lam=lam)
+    s = pk.Solver(At, 0.0, rho=P.rho, max_outer=60, graph=True)
+    s.set_arena_limit(300 << 20)
+    _assert_same(s.solve(Bt, lam=lam), host, "limit")
+    s.close()
