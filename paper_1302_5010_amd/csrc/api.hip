@@ -600,7 +600,8 @@ bmpl_status bmpl_create(const float* A_dev, int64_t lda, int32_t n, int32_t m, b
     c->w.words = (m + 31) / 32;
     e = pool_alloc(c, &c->At, (size_t)(m + 1) * c->kpad);   // row m stays zero
     if (e == hipSuccess) {
-        e = hipHostMalloc(reinterpret_cast<void**>(&c->h_report), PASS_REPORTS * sizeof(PassReport), hipHostMallocDefault);
+        e = hipHostMalloc(reinterpret_cast<void**>(&c->h_report), PASS_REPORTS * sizeof(PassReport),
+                          hipHostMallocCoherent);   // polled while kernels run
         if (e == hipSuccess) std::memset(c->h_report, 0, PASS_REPORTS * sizeof(PassReport));
     }
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->h_arena), sizeof(Arena), hipHostMallocDefault);
