@@ -47,7 +47,8 @@ KERNEL_SOURCES = ("paper_1302_5010_amd/csrc/corr_gemm.hip", "paper_1302_5010_amd
 
 SOLVE_SOURCES = ("paper_1302_5010_amd/csrc/pursuit.hip", "paper_1302_5010_amd/csrc/pursuit_wave.hip",
                  "paper_1302_5010_amd/csrc/master_body.h", "paper_1302_5010_amd/csrc/pursuit.h",
-                 "paper_1302_5010_amd/csrc/bmpl_internal.h", "paper_1302_5010_amd/csrc/wave_ops.h")
+                 "paper_1302_5010_amd/csrc/bmpl_internal.h", "paper_1302_5010_amd/csrc/arena_list.h",
+                 "paper_1302_5010_amd/csrc/wave_ops.h")
 
 
 def kernel_source_hash(sources=KERNEL_SOURCES) -> str:
